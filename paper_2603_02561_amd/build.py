@@ -13,6 +13,9 @@ LIB = os.path.join(HERE, "libsolar.so")
 SOURCES = ["api", "gram", "eig", "project", "rsvd", "attention", "attention_x32", "linear", "backward", "dense_ref"]
 FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+# eig.hip is bound by chains of dependent instructions on waves that have a SIMD to themselves: its
+# instructions are scheduled for parallelism within a wave, not for occupancy
+EXTRA_FLAGS = {"eig": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]}
 
 
 def build_library(verbose: bool = False) -> str:
@@ -20,7 +23,7 @@ def build_library(verbose: bool = False) -> str:
 
     def compile_one(name: str) -> str:
         obj = os.path.join(BUILD, name + ".o")
-        cmd = ["hipcc", *FLAGS, "-c", os.path.join(CSRC, name + ".hip"), "-o", obj]
+        cmd = ["hipcc", *FLAGS, *EXTRA_FLAGS.get(name, []), "-c", os.path.join(CSRC, name + ".hip"), "-o", obj]
         res = subprocess.run(cmd, capture_output=True, text=True)
         if res.returncode != 0:
             raise RuntimeError(f"hipcc failed for {name}:\n{res.stderr}")

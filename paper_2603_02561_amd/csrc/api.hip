@@ -73,7 +73,7 @@ std::atomic<int> g_debug_force_guarded{0};
 EigParams eig_params() {
     EigParams p = eig_default_params();
     const int cap = g_debug_eig_max_iter.load(std::memory_order_relaxed);
-    if (cap > 0) p.max_iter = cap;
+    if (cap > 0) { p.max_iter = cap; p.direct = false; }
     return p;
 }
 

@@ -8,6 +8,7 @@ namespace solar {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v16f __attribute__((ext_vector_type(16)));
+typedef double v4d __attribute__((ext_vector_type(4)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
@@ -23,6 +24,11 @@ __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w 
 // B[l/16][l%16]; it receives D[4*(l/16)+t][l%16] in component t.
 __device__ __forceinline__ v4f mfma16x16x4(float a, float b, v4f c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// The same in double precision; D differs: a lane receives D[l/16 + 4*t][l%16] in component t.
+__device__ __forceinline__ v4d mfma16x16x4f64(double a, double b, v4d c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
 // D = A(16x32) * B(32x16) + C, bf16 inputs, float accumulate.  Lane l supplies

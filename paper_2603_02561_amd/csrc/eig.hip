@@ -2,15 +2,18 @@
 // user, iterate blocks held in LDS.  S = sqrt(eigenvalues), V = eigenvectors are
 // the s and R that Algorithm 1 ("Randomized SVD with Power Iteration") returns.
 //
-// The iteration is Algorithm 1 expressed on G: a Gaussian start block Omega
+// Wide blocks (r near d) are solved directly, by the double-precision solver of tridiag.h applied to G.
+//
+// Otherwise the iteration is Algorithm 1 expressed on G: a Gaussian start block Omega
 // (d x L, L = r + oversampling), power steps Omega <- X^T (X Omega) = G Omega, an
 // orthonormal basis of the block, and a small decomposition of the projected
 // problem.  On the first power steps only the span of the block matters, and the
 // basis comes from one modified Gram-Schmidt pass.  After those, basis and small
-// decomposition are done together by a one-sided (Hestenes) Jacobi method on the
-// d x L block Z = G Q: rotating column pairs of Z until they are mutually orthogonal
-// diagonalizes Q^T G^2 Q, which is the Rayleigh-Ritz step for G^2 on span(Q), and the
-// normalized columns are the next orthonormal basis.  One-sided Jacobi is insensitive
+// decomposition are done together on the d x L block Z = G Q: making its columns mutually
+// orthogonal diagonalizes Q^T G^2 Q, which is the Rayleigh-Ritz step for G^2 on span(Q), and
+// the normalized columns are the next orthonormal basis.  ritz_rotate does it through the
+// eigenvectors of Z^T Z in double precision; the narrowest blocks and those with coinciding
+// eigenvalues take one-sided (Hestenes) Jacobi sweeps over the columns of Z.  Both are insensitive
 // to the huge dynamic range of the block (G Omega is dominated by the leading
 // eigenvectors) and to rank deficiency (columns that vanish are dropped).  The power
 // step after a Jacobi phase yields the residuals |G q_i - theta_i q_i| of the Ritz
@@ -24,6 +27,7 @@
 // every trip count a compile-time constant.
 #include "common.h"
 #include "kernels.h"
+#include "tridiag.h"
 
 namespace solar {
 
@@ -84,23 +88,36 @@ __device__ __forceinline__ float team_sum(float v) {
     return v;
 }
 
-// Z = G Q with the float 16x16x4 MFMA, block rows of 16 dealt round-robin to the
-// waves.  G is symmetric, so A[i][k] = G[k][i] is read with the 16 lanes of a slot group
-// on consecutive addresses.  Q and Z are stored column by column (column j at j*LD).
-// Gb has row stride GS: the copy of G in LDS (row stride D + 16, which puts the two slot
-// groups of a half wave on disjoint banks) or, when G does not fit there, G itself.
+// Z = G Q with the float 16x16x4 MFMA, block rows of 16 dealt round-robin to the waves.  G is symmetric, and
+// the order of the contraction is free, so lane (i, g) takes entries 16 j + 4 g .. + 3 of row i of G and of
+// column i of Q with one 16-byte read each and feeds them to four products in turn.  The strides D + 4 of
+// Gs and of the columns of Q and Z spread the 16 rows over all banks.  Gb has row stride GS: the copy of G
+// in LDS or, when G does not fit there, G itself: then the whole rows are loaded ahead of the products.
 // With a shift t the result is (G - t I) Q: the accumulators start from -t Q.
 template <int D, int LP, int GS, bool SHIFTED = false>
 __device__ __forceinline__ void gemm_gq(const float* Gb, const float* Qc, float* Zc, float shift = 0.f) {
     constexpr int LD = D + 4;
-    constexpr int NRB = D / 16, NCB = LP / 16;
+    constexpr int NRB = D / 16, NCB = LP / 16, NK = D / 16;
+    constexpr bool AHEAD = D > 128;                     // G comes from memory
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int i16 = lane & 15, g = lane >> 4;
+    const float* qb = Qc + i16 * LD + 4 * g;
+    constexpr int NB = (NRB + kEigWaves - 1) / kEigWaves;
+    v4f ahead[AHEAD ? NB : 1][AHEAD ? NK : 1];
+    if constexpr (AHEAD) {
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+#pragma unroll
+            for (int j = 0; j < NK; ++j)
+                ahead[n][j] = *reinterpret_cast<const v4f*>(Gb + (16 * (wave + n * kEigWaves) + i16) * GS + 16 * j + 4 * g);
+    }
     // a wave takes whole block rows: the operand read from G serves all NCB column blocks, whose
     // accumulators are independent chains for the matrix unit
-    for (int ib = wave; ib < NRB; ib += kEigWaves) {
-        const float* ga = Gb + g * GS + 16 * ib + i16;
-        const float* qb = Qc + i16 * LD + g;
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+        const int ib = wave + n * kEigWaves;
+        if (NRB % kEigWaves != 0 && ib >= NRB) break;
+        const float* ga = Gb + (16 * ib + i16) * GS + 4 * g;
         v4f acc[NCB];
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb) {
@@ -109,17 +126,45 @@ __device__ __forceinline__ void gemm_gq(const float* Gb, const float* Qc, float*
             else
                 acc[cb] = v4f{0.f, 0.f, 0.f, 0.f};
         }
-#pragma unroll 8
-        for (int k0 = 0; k0 < D; k0 += 4) {
-            const float a = ga[k0 * GS];
 #pragma unroll
-            for (int cb = 0; cb < NCB; ++cb) acc[cb] = mfma16x16x4(a, qb[16 * cb * LD + k0], acc[cb]);
+        for (int j = 0; j < NK; ++j) {
+            v4f a, q[NCB];
+            if constexpr (AHEAD) a = ahead[n][j];
+            else a = *reinterpret_cast<const v4f*>(ga + 16 * j);
+#pragma unroll
+            for (int cb = 0; cb < NCB; ++cb) q[cb] = *reinterpret_cast<const v4f*>(qb + 16 * cb * LD + 16 * j);
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int cb = 0; cb < NCB; ++cb) acc[cb] = mfma16x16x4(a[s], q[cb][s], acc[cb]);
         }
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb)
             *reinterpret_cast<v4f*>(&Zc[(16 * cb + i16) * LD + 16 * ib + 4 * g]) = acc[cb];
     }
 }
+
+// Work arrays of one dense solve at `base` (doubles): reflectors, wa, wb, vectors of length N.
+template <int N, int RB>
+struct TriLds {
+    using T = TriCfg<N, RB>;
+    double *U, *wa, *wb, *dd, *ee, *ih, *es, *lam;
+    double2* t;
+    static constexpr size_t kDoublesNoWa = T::USZ + T::WB + T::VEC;
+    static constexpr size_t kDoubles = kDoublesNoWa + T::WA;
+    // wa == nullptr: behind the other arrays
+    __device__ __forceinline__ TriLds(double* base, double* wa_) {
+        U = base;
+        wb = U + T::USZ;
+        dd = wb + T::WB;
+        ee = dd + N;
+        ih = ee + N;
+        es = ih + N;
+        t = reinterpret_cast<double2*>(es + N);
+        lam = reinterpret_cast<double*>(t + N + 8);
+        wa = wa_ ? wa_ : dd + T::VEC;
+    }
+};
 
 template <int D, int L>
 struct EigCfg {
@@ -129,8 +174,23 @@ struct EigCfg {
     static constexpr int TC = min_c(min_c(64, D), pow2floor_c(kEigThreads / L));
     // G is staged in LDS when it fits beside the two iterate blocks
     static constexpr bool GLDS = D <= 128;
-    static constexpr int GS = GLDS ? D + 16 : D;
-    static constexpr size_t lds_floats = (size_t)2 * LP * LD + 3 * LP + 8 + (GLDS ? (size_t)D * GS : 0);
+    static constexpr int GS = GLDS ? D + 4 : D;
+    static constexpr size_t base_floats = (size_t)2 * LP * LD + 3 * LP + 8 + (GLDS ? (size_t)D * GS : 0);
+    // Wide blocks are solved directly: the reduction of the whole matrix is then cheaper than the
+    // power steps, Gram-Schmidt passes and Ritz steps of the iteration, and takes the same time for every
+    // spectrum (16 users, d = 128, r = 64: 214 us per launch, where iterating took 360 for
+    // inputs of rank r, 452 for singular values ~ k^-1/2 and 732 with the last ones in the noise; d = 64, r = 40:
+    // 78 us against 122, 227 and 619; at d = 64, L = 24 and d = 128, L = 48 the two are about even on easy spectra).
+    static constexpr bool direct = (D == 64 && L >= 32) || (D == 128 && L >= 56);
+    // Narrower ones take the Ritz step of the iteration through the same solver instead of Jacobi sweeps
+    // (16 users, inputs of rank r: d = 128, r = 32 from 142 to 113 us, r = 16 from 82 to 67; d = 256,
+    // r = 32 from 253 to 178, of which 55 are the wider reads of the products G Q), except the narrowest,
+    // where it is no faster (d = 64, r = 8: 38 us).
+    static constexpr bool ritz = !direct && (D > 64 || L > 16);
+    static constexpr size_t ritz_floats = ritz ? 2 * TriLds<ritz ? L : 16, ritz ? L : 16>::kDoublesNoWa : 0;
+    static constexpr size_t direct_floats = D <= 128 ? 2 * TriLds<(D <= 128 ? D : 64), (D == 128 ? 32 : 64)>::kDoubles : 0;
+    static constexpr size_t lds_floats =
+        base_floats + ritz_floats > direct_floats ? base_floats + ritz_floats : direct_floats;
 };
 
 // One cyclic sweep of one-sided Jacobi over the L columns of Zc; returns this thread's largest
@@ -409,6 +469,156 @@ __device__ __forceinline__ void mgs_orthonormalize(float* Zc, float* Qc, float* 
     }
 }
 
+// Two wanted eigenvalues closer than this (relative to the norm) leave their vectors, which are computed
+// independently of each other, orthogonal only to about 1e-15 / kTriGap: the caller takes another route.
+constexpr double kTriGap = 1.0e-9;
+// A matrix of zeros comes out of the reduction with a norm of about 1e-89; one of floats, or of their
+// squares, is above this.
+constexpr double kTriZero = 1.0e-80;
+
+// The Rayleigh-Ritz step on the N columns of Zc (LDS, column stride D + 4): with C = Z^T Z = W diag(l) W^T,
+// formed and solved in double precision, the columns of Z W diag(l)^-1/2 are orthonormal and
+// diagonalize the projected problem, which is what one-sided Jacobi sweeps over Z converge to.  They go
+// to Qc (zero where sqrt(l) is below kDeadRel of the largest), in descending order of l; sig[k] receives
+// sqrt(l_k).  Qc may share its memory with wa.  False (and Qc untouched unless it is wa): two of the
+// `wanted` leading eigenvalues are too close for this route.
+template <int D, int N>
+__device__ __forceinline__ bool ritz_rotate(const float* Zc, float* Qc, const TriLds<N, N>& w, double* scal, int* twist,
+                                            float* sig, int wanted) {
+    using T = TriCfg<N, N>;
+    constexpr int LD = D + 4, NT = (N + 15) / 16;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int i16 = lane & 15, g = lane >> 4;
+    double* Cm = w.wa;
+    for (int p = wave; p < NT * (NT + 1) / 2; p += kEigWaves) {
+        int I = 0, rest = p;
+        while (rest >= NT - I) { rest -= NT - I; ++I; }
+        const int J = I + rest;
+        const float* za = Zc + (16 * I + i16) * LD + g;
+        const float* zb = Zc + (16 * J + i16) * LD + g;
+        v4d acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 8
+        for (int k0 = 0; k0 < D; k0 += 4) acc = mfma16x16x4f64((double)za[k0], (double)zb[k0], acc);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int i = 16 * I + g + 4 * t, j = 16 * J + i16;
+            if (i < N && j < N) {
+                Cm[i * N + j] = acc[t];
+                Cm[j * N + i] = acc[t];
+            }
+        }
+    }
+    __syncthreads();
+    TriRows<N> a;
+    if (wave < kTriWaves) {
+#pragma unroll
+        for (int m = 0; m < T::RS; ++m)
+#pragma unroll
+            for (int c = 0; c < T::NC; ++c) {
+                const int i = 16 * (m / 4) + 4 * wave + m % 4, j = (lane ^ (4 * wave)) + 64 * c;
+                a[m][c] = i < N && j < N ? Cm[i * N + j] : 0.0;
+            }
+    }
+    tri_reduce<N>(a, w.wb, w.U, w.dd, w.ee, w.ih);
+    const double bound = tri_values<N, (N <= 32 ? 8 : 4)>(w.dd, w.ee, w.es, w.t, w.lam, scal,
+                                                          reinterpret_cast<int*>(w.wb), N);
+    const double l0 = w.lam[0], dead = (double)kDeadRel * kDeadRel * l0;
+    const bool close = tid + 1 < wanted && w.lam[tid + 1] > dead && w.lam[tid] - w.lam[tid + 1] < kTriGap;
+    if (__syncthreads_or(close) || !(bound > kTriZero) || !(l0 > 0.0)) return false;
+    tri_vectors<N, N>(w.t, w.es, w.lam, w.wa, w.wb, twist, 0, N);
+    constexpr int TB = 8;
+    const int v = tid / TB, u = tid % TB;
+    double y[N / TB];
+    if (v < N) tri_load<N, N, TB>(w.wa, v, u, y);
+    tri_cross<N>(w.U, w.dd);
+    if (v < N) {
+        tri_back<N, TB>(w.U, w.ih, w.dd, u, y);
+        const double l = w.lam[v], rs = l > dead ? rsq64(l * bound) : 0.0;
+        if (u == 0) sig[v] = (float)(l > 0.0 ? l * bound * rsq64(l * bound) : 0.0);
+#pragma unroll
+        for (int q = 0; q < N / TB; ++q) w.wb[v * N + TB * q + u] = l > dead ? y[q] * rs : 0.0;
+    }
+    __syncthreads();
+    for (int J = wave; J < D / 16; J += kEigWaves) {
+#pragma unroll
+        for (int I = 0; I < NT; ++I) {
+            const bool in = 16 * I + i16 < N;
+            const double* wr = w.wb + (in ? 16 * I + i16 : 0) * N + g;
+            const float* zr = Zc + g * LD + 16 * J + i16;
+            v4d acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int k0 = 0; k0 < N; k0 += 4) acc = mfma16x16x4f64(in ? wr[k0] : 0.0, (double)zr[k0 * LD], acc);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) Qc[(16 * I + g + 4 * t) * LD + 16 * J + i16] = (float)acc[t];
+        }
+    }
+    __syncthreads();
+    return true;
+}
+
+// The r leading eigenpairs straight from the D x D matrix in Gs (LDS, row stride GS), written to S and V.
+// Takes all of the dynamic LDS; Gs may lie anywhere in it.  False (nothing written): two wanted
+// eigenvalues are too close.
+template <int D, int RMAX, int GS>
+__device__ __forceinline__ bool eig_direct(const float* Gs, double* sm, double* scal, int* twist, int r, float* S,
+                                           float* V) {
+    constexpr int RB = D == 128 ? 32 : 64;              // vectors per pass
+    constexpr int TB = RMAX <= 32 && D == 128 ? 16 : 8;
+    using T = TriCfg<D, RB>;
+    const TriLds<D, RB> w(sm, nullptr);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    TriRows<D> a;
+    if (wave < kTriWaves) {
+#pragma unroll
+        for (int m = 0; m < T::RS; ++m)
+#pragma unroll
+            for (int c = 0; c < T::NC; ++c)
+                a[m][c] = Gs[(16 * (m / 4) + 4 * wave + m % 4) * GS + (lane ^ (4 * wave)) + 64 * c];
+    }
+    __syncthreads();
+    tri_reduce<D>(a, w.wb, w.U, w.dd, w.ee, w.ih);
+    const double bound = tri_values<D, (RMAX <= 32 ? 8 : 4)>(w.dd, w.ee, w.es, w.t, w.lam, scal,
+                                                             reinterpret_cast<int*>(w.wb), r);
+    const double l0 = w.lam[0], dead = (double)kDeadRel * l0;
+    const bool any = bound > kTriZero && l0 > 0.0;
+    const bool close = tid + 1 < r && w.lam[tid + 1] > dead && w.lam[tid] - w.lam[tid + 1] < kTriGap;
+    if (__syncthreads_or(any && close)) return false;
+    const int v = tid / TB, u = tid % TB;
+    double y[D / TB];
+#pragma unroll 1
+    for (int v0 = 0; v0 < r; v0 += RB) {
+        const int nb = r - v0 < RB ? r - v0 : RB;
+        tri_vectors<D, RB>(w.t, w.es, w.lam, w.wa, w.wb, twist, v0, nb);
+        if (v >= v0 && v < v0 + nb) tri_load<D, RB, TB>(w.wa, v - v0, u, y);
+        __syncthreads();
+    }
+    tri_cross<D>(w.U, w.dd);
+    if (v < r) {
+        tri_back<D, TB>(w.U, w.ih, w.dd, u, y);
+        const double l = w.lam[v];
+        const bool live = any && l > dead;
+        // sign fixed by the largest-magnitude entry
+        float best = -1.f, val = 0.f;
+        int bi = 0;
+#pragma unroll
+        for (int q = 0; q < D / TB; ++q) {
+            const float f = (float)y[q];
+            if (fabsf(f) > best) { best = fabsf(f); bi = TB * q + u; val = f; }
+        }
+#pragma unroll
+        for (int m = 1; m < TB; m <<= 1) {
+            const float ob = __shfl_xor(best, m), ov = __shfl_xor(val, m);
+            const int oi = __shfl_xor(bi, m);
+            if (ob > best || (ob == best && oi < bi)) { best = ob; bi = oi; val = ov; }
+        }
+        const float sgn = val < 0.f ? -1.f : 1.f;
+#pragma unroll
+        for (int q = 0; q < D / TB; ++q) V[(size_t)(TB * q + u) * r + v] = live ? sgn * (float)y[q] : 0.f;
+        if (u == 0) S[v] = live ? (float)(l * bound * rsq64(l * bound)) : 0.f;
+    }
+    return true;
+}
+
 template <int D, int L>
 __global__ __launch_bounds__(kEigThreads) void eig_topr_kernel(
     const float* __restrict__ G, const float* __restrict__ partials, int nsplit,
@@ -426,9 +636,12 @@ __global__ __launch_bounds__(kEigThreads) void eig_topr_kernel(
     __shared__ int sh_bits;
     __shared__ int sh_bits2;
     __shared__ float sh_rate[2];
+    __shared__ double sh_scal[1];
+    __shared__ int sh_twist[64];
     const int tid = threadIdx.x;
     const int b = blockIdx.x;
     const float* Gb = G + (size_t)b * D * D;
+    double* tri = reinterpret_cast<double*>(smem + C::base_floats);
 
     {
         const int raw = lengths ? lengths[b] : N;
@@ -440,6 +653,7 @@ __global__ __launch_bounds__(kEigThreads) void eig_topr_kernel(
         }
     }
     if (tid == 0) { sh_bits = 0; sh_bits2 = 0; }
+    auto stage = [&]() __attribute__((always_inline)) {
     if constexpr (C::GLDS) {
         if (partials) {
             // G from the split-N partial blocks of the Gram kernel: per chunk and fragment pair
@@ -494,6 +708,23 @@ __global__ __launch_bounds__(kEigThreads) void eig_topr_kernel(
                     *reinterpret_cast<const v4f*>(Gb + (size_t)i * D + 4 * c4);
             }
         }
+    }
+    };
+    stage();
+    // wide blocks; a test that caps the power steps wants to see the iteration
+    bool by_ritz = true;
+    if constexpr (C::direct) {
+        if (prm.direct) {
+            __syncthreads();
+            if (eig_direct<D, L - 8, C::GS>(Gs, reinterpret_cast<double*>(smem), sh_scal, sh_twist, r,
+                                            S + (size_t)b * r, V + (size_t)b * D * r)) {
+                if (tid == 0 && info) info[b] = 0;
+                return;
+            }
+            __syncthreads();
+            stage();
+        }
+        by_ritz = false;
     }
     const float* Gop = C::GLDS ? Gs : Gb;
     // start block Omega (columns >= L stay zero so that the padded GEMM columns are zero)
@@ -623,7 +854,17 @@ __global__ __launch_bounds__(kEigThreads) void eig_topr_kernel(
         cycle = cycle < 0 ? 1 : cycle + 1;
         cheap_left = prm.mgs_steps << (cycle < 3 ? cycle : 3);
         have_ritz = true;
-        // orthogonalize the columns of Z (this also rotates them towards Ritz vectors)
+        // orthogonalize the columns of Z (this also rotates them to Ritz vectors)
+        if constexpr (C::ritz) {
+            if (by_ritz) {
+                const TriLds<L, L> w(tri, reinterpret_cast<double*>(Qc));
+                if (ritz_rotate<D, L>(Zc, Qc, w, sh_scal, sh_twist, resid, r)) {
+                    orth_ok = true;
+                    continue;
+                }
+                by_ritz = false;                         // close eigenvalues: sweeps, from here on
+            }
+        }
         orth_ok = false;
         for (int sw = 0; sw < prm.sweeps; ++sw) {
             const float mine = jacobi_sweep<D, L>(Zc, dead2);
@@ -909,6 +1150,7 @@ EigParams eig_default_params() {
     p.max_iter = 40;
     p.sweeps = 12;
     p.mgs_steps = 2;
+    p.direct = true;
     return p;
 }
 
@@ -918,12 +1160,6 @@ int eig_block_columns(int d, int r) {
     if (L < 16) L = 16;
     if (L > d) L = d;
     return L;
-}
-
-size_t eig_lds_bytes(int d, int r) {
-    const int L = eig_block_columns(d, r);
-    const int LP = 16 * ((L + 15) / 16);
-    return sizeof(float) * ((size_t)2 * LP * (d + 4) + 3 * LP + 8 + (d <= 128 ? (size_t)d * (d + 16) : 0));
 }
 
 hipError_t launch_eig(const float* G, const float* partials, int nsplit, const int32_t* lengths, int B, int N,

@@ -1,0 +1,549 @@
+// Eigenpairs of a small dense symmetric matrix in double precision, one workgroup of 512 threads:
+// Householder tridiagonalization, multisection on Sturm counts for the wanted eigenvalues, twisted
+// factorizations for their eigenvectors, and the reflectors applied backwards.
+//
+// The phase is bound by the length of its dependent chain, not by arithmetic: one Householder step is
+// two wave-wide sums, a reciprocal square root, a reciprocal, and one exchange of partial sums between
+// the waves.  Double precision costs nothing against float here (a v_fma_f64 issues like a v_fma_f32,
+// 9 cycles dependent and 5 independent, measured) except in the wave sums, and it is what lets the
+// eigenvectors be computed independently of each other: their mutual orthogonality is about
+// 1e-15 / gap, where gap is the distance of neighbouring eigenvalues relative to the norm.
+//
+// The matrix lives in the registers of four waves, one per SIMD: wave w holds the rows i with
+// (i / 4) % 4 == w, a lane one column, or two of more than 64, so the trailing block stays spread over
+// the waves while it shrinks.  A step needs a single barrier: each of the four forms the reflector and the correction
+// vector for itself, from the four partial products A u and the next pivot row (as it was before the
+// step), which they exchange through a double buffer in LDS.  (Eight waves, two per SIMD, do that
+// redundant part twice on every SIMD: 1880 cycles per step at 40 columns.)
+#pragma once
+
+#include "common.h"
+
+namespace solar {
+
+constexpr int kTriThreads = 512;
+constexpr int kTriWaves = 4;   // waves that hold the matrix
+constexpr double kTriTiny = 1.0e-180;
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_mov64(double v) {
+    union { double d; int i[2]; } x, y;
+    x.d = v;
+    y.i[0] = __builtin_amdgcn_mov_dpp(x.i[0], CTRL, 0xf, 0xf, true);   // every lane has a source
+    y.i[1] = __builtin_amdgcn_mov_dpp(x.i[1], CTRL, 0xf, 0xf, true);
+    return y.d;
+}
+
+__device__ __forceinline__ double readlane64(double v, int lane) {
+    union { double d; int i[2]; } x, y;
+    x.d = v;
+    y.i[0] = __builtin_amdgcn_readlane(x.i[0], lane);
+    y.i[1] = __builtin_amdgcn_readlane(x.i[1], lane);
+    return y.d;
+}
+
+// Sum over the 64 lanes, the same bits in every lane.  Two 4x4x4 products with ones add the lanes that
+// share (l / 4) % 4 (the first over l / 16, the second over l % 4: 20 cycles each, where a DPP stage on
+// a double takes 28), two mirrors the remaining four groups, as (g0 + g1) + (g2 + g3): an exchange of
+// lanes l <-> l ^ 4 w beforehand does not change a bit of the result.
+__device__ __forceinline__ double wave_sum64_begin(double v) {
+    return __builtin_amdgcn_mfma_f64_4x4x4f64(v, 1.0, 0.0, 0, 0, 0);
+}
+__device__ __forceinline__ double wave_sum64_end(double v) {
+    v = __builtin_amdgcn_mfma_f64_4x4x4f64(1.0, v, 0.0, 0, 0, 0);
+    v += dpp_mov64<0x141>(v);   // row_half_mirror
+    v += dpp_mov64<0x140>(v);   // row_mirror
+    return v;
+}
+
+// Sum over teams of T = 8 or 16 consecutive lanes.
+template <int T>
+__device__ __forceinline__ double team_sum64(double v) {
+    static_assert(T == 8 || T == 16, "teams inside a row of 16 lanes");
+    v += dpp_mov64<0xB1>(v);
+    v += dpp_mov64<0x4E>(v);
+    v += dpp_mov64<0x141>(v);
+    if constexpr (T == 16) v += dpp_mov64<0x140>(v);
+    return v;
+}
+
+// 1 / x and 1 / sqrt(x): the hardware's estimate (2^-23 or better) and one Newton step, about 1e-14.
+__device__ __forceinline__ double rcp64(double x) {
+    const double r = __builtin_amdgcn_rcp(x);
+    return fma(fma(-x, r, 1.0), r, r);
+}
+__device__ __forceinline__ double rsq64(double x) {
+    const double r = __builtin_amdgcn_rsq(x);
+    return fma(fma(-x * r, r, 1.0), 0.5 * r, r);
+}
+
+// LDS of one solve, in doubles.  `wa` and `wb` are two work arrays of WA and WB doubles; the exchange
+// buffers of the reduction live in `wb`.
+template <int N, int RB>
+struct TriCfg {
+    static constexpr int NC = (N + 63) / 64;           // columns per lane
+    static constexpr int RS = 4 * ((N + 15) / 16);     // rows per wave, in chunks of four
+    static constexpr int PS = 64 * NC;
+    // reflectors, packed: row k (entries k+1 .. N-1) above row k-1; a whole-wave store of row k runs on into
+    // rows that are stored later, and behind the last one
+    static constexpr int USZ = N * (N - 1) / 2 + PS;
+    // exchange buffers: partial products [2][waves][PS] and the rows that hold the next pivot [2][16][PS]
+    static constexpr int EX = (2 * kTriWaves + 32) * PS;
+    static constexpr int WA = N * RB;
+    static constexpr int WB = (N * RB > EX) ? N * RB : EX;
+    static constexpr int VEC = 6 * N + 16 + 64;        // d, e, 1/h, scaled e, (d, e^2) and a chunk, lambda
+    static_assert(N % 8 == 0 && N >= 16 && N <= 128, "multiples of eight");
+};
+template <int N>
+using TriRows = double[4 * ((N + 15) / 16)][(N + 63) / 64];   // rows per wave x columns per lane
+template <int N>
+using TriCols = double[(N + 63) / 64];
+
+// where entry j of reflector k would be in U if its entries started at 0 (they start at k + 1)
+__device__ __forceinline__ int tri_row(int n, int k) { return k * (n - 1) - (k * (k - 1)) / 2 - (k + 1); }
+
+// State of the reduction that a wave carries from step to step.
+template <int N>
+struct TriState {
+    TriCols<N> x;                        // the pivot row, updated
+    TriCols<N> uo, qo;                   // reflector and correction of the last step, not yet applied to the rows
+    TriCols<N> dr, er, hr;               // column j of the results (diagonal, off-diagonal, 1/h)
+    double ur[4 * ((N + 15) / 16)];      // entries of uo that belong to the wave's own rows, in scalar registers
+};
+
+// Steps of the reduction whose next pivot is in rows 16 A0 .. 16 A0 + 15, then those of A0 + 1 and so on:
+// the chunks of rows that are still in the trailing block are a compile-time set, so a step has no branch.
+// A wave alone on its SIMD issues one instruction, scalar ones included, per five cycles, and every access
+// to LDS delays the exchange (removing both sums changes nothing, removing a store of all waves takes 60 to
+// 100 cycles off a step): entries of u and q that a row needs are lane broadcasts, not reads.
+template <int N, int A0>
+__device__ __forceinline__ void tri_steps(TriRows<N>& a, TriState<N>& st, double* ex, double* U, int wave,
+                                          int col) {
+    using T = TriCfg<N, 8>;
+    constexpr int NC = T::NC, PS = T::PS, W = kTriWaves, NA = (N + 15) / 16;
+    constexpr int C0 = A0 >= 4 ? 1 : 0;                 // columns of earlier registers have left the block
+    constexpr int K0 = A0 ? 16 * A0 - 1 : 0, K1 = 16 * A0 + 15 < N - 2 ? 16 * A0 + 15 : N - 2;
+    double* rows = ex + 2 * W * PS;                     // [2][16][PS]
+    constexpr bool KEEP = NC - C0 == 1;                 // two columns per lane need the scalar registers
+    // one and zero in double precision by their high words
+    auto unit = [](bool on) __attribute__((always_inline)) { return __hiloint2double(on ? 0x3ff00000 : 0, 0); };
+#pragma unroll 1
+    for (int k = K0; k < K1; ++k) {
+        double* pb = ex + (k & 1) * (W * PS) + col;
+        double* rb = rows + (k & 1) * (16 * PS) + col;
+        const int k1 = k + 1;
+        double u[NC], s2 = kTriTiny;                    // a column of zeros still gives a reflector
+#pragma unroll
+        for (int c = C0; c < NC; ++c) {
+            u[c] = st.x[c] * unit(col + 64 * c > k);
+            s2 = fma(u[c], u[c], s2);
+        }
+        double xk1 = st.x[NC - 1];
+        if constexpr (NC - C0 == 2) xk1 = k1 >= 64 ? st.x[1] : st.x[0];
+        s2 = wave_sum64_begin(s2);
+        const double alpha = readlane64(xk1, (k1 ^ (4 * wave)) & 63);
+        s2 = wave_sum64_end(s2);
+        // the reflector I - u u^T / h maps the column to g e_(k+1)
+        const double g = -copysign(s2 * rsq64(s2), alpha);
+        const double inv = rcp64(fma(-alpha, g, s2) - 32.0 * kTriTiny);
+#pragma unroll
+        for (int c = C0; c < NC; ++c) {
+            u[c] = fma(-g, unit(col + 64 * c == k1), u[c]);
+        }
+        // own rows of the trailing block: the last step's update, then the product with u
+        double pp[NC][4];
+#pragma unroll
+        for (int c = C0; c < NC; ++c) pp[c][0] = pp[c][1] = pp[c][2] = pp[c][3] = 0.0;
+#pragma unroll
+        for (int q = A0; q < NA; ++q)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const int m = 4 * q + s, r = (16 * q) >> 6, i = (16 * q + s) & 63;
+                const double qr = readlane64(st.qo[r], i);
+                const double ul = KEEP ? st.ur[m] : readlane64(st.uo[r], i);
+#pragma unroll
+                for (int c = C0; c < NC; ++c) {
+                    a[m][c] = fma(-ul, st.qo[c], fma(-qr, st.uo[c], a[m][c]));
+                    if (q == A0) rb[(4 * wave + s) * PS + 64 * c] = a[m][c];
+                }
+            }
+#pragma unroll
+        for (int q = A0; q < NA; ++q)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const int m = 4 * q + s, r = (16 * q) >> 6, i = (16 * q + s) & 63;
+                const double ui = readlane64(u[r], i);
+#pragma unroll
+                for (int c = C0; c < NC; ++c) pp[c][s] = fma(ui, a[m][c], pp[c][s]);
+                if (KEEP) st.ur[m] = ui;
+            }
+#pragma unroll
+        for (int c = C0; c < NC; ++c) pb[wave * PS + 64 * c] = (pp[c][0] + pp[c][1]) + (pp[c][2] + pp[c][3]);
+        __syncthreads();
+        double r[NC][W], y[NC];
+#pragma unroll
+        for (int c = C0; c < NC; ++c) {
+#pragma unroll
+            for (int w = 0; w < W; ++w) r[c][w] = pb[w * PS + 64 * c];
+            y[c] = rb[(k1 & 15) * PS + 64 * c];
+        }
+        if (wave == (k & (W - 1))) {
+            double* uk = U + tri_row(N, k) + k1;
+#pragma unroll
+            for (int c = C0; c < NC; ++c) uk[(col + 64 * c - k1) & (PS - 1)] = u[c];
+        }
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            st.er[c] = col + 64 * c == k ? g : st.er[c];
+            st.hr[c] = col + 64 * c == k ? inv : st.hr[c];
+        }
+        // with w = u^T A u, the correction is q = p - (w / 2 h^2) u for p = A u / h, and the new pivot row
+        // is row - u_(k+1) q - q_(k+1) u; all of it but the multiple of w is ready before w is
+        double p[NC], t[NC], up = 0.0;
+#pragma unroll
+        for (int c = C0; c < NC; ++c) {
+            const double sum = (r[c][0] + r[c][1]) + (r[c][2] + r[c][3]);
+            up = fma(u[c], sum, up);
+            p[c] = sum * inv;
+        }
+        up = wave_sum64_end(wave_sum64_begin(up));
+        double ps = p[NC - 1];
+        if constexpr (NC - C0 == 2) ps = k1 >= 64 ? p[1] : p[0];
+        const double uk1 = alpha - g, pk1 = readlane64(ps, (k1 ^ (4 * wave)) & 63);
+#pragma unroll
+        for (int c = C0; c < NC; ++c) {
+            y[c] = fma(-uk1, p[c], fma(-pk1, u[c], y[c]));
+            t[c] = inv * uk1 * inv * u[c];
+        }
+        const double w2 = -0.5 * (inv * up) * inv;
+#pragma unroll
+        for (int c = C0; c < NC; ++c) {
+            st.x[c] = fma(up, t[c], y[c]);
+            st.qo[c] = fma(w2, u[c], p[c]);
+            st.uo[c] = u[c];
+            st.dr[c] = col + 64 * c == k1 ? st.x[c] : st.dr[c];
+        }
+    }
+    if constexpr (A0 == 3 && NC == 2) {                 // from here on the broadcasts are kept
+#pragma unroll
+        for (int m = 16; m < T::RS; ++m) st.ur[m] = readlane64(st.uo[1], (16 * (m / 4) + m % 4) & 63);
+    }
+    if constexpr (K1 < N - 2) tri_steps<N, A0 + 1>(a, st, ex, U, wave, col);
+}
+
+// Householder reduction of the matrix in `a` to tridiagonal form: diagonal dd[N], off-diagonal ee[N-1],
+// reflector k in row k of U (entries k+1 .. N-1) with its 1/h in ih[k].  Waves 0 .. 3 hold the matrix:
+// a[4 q + s][c] is entry (16 q + 4 wave + s, (lane ^ 4 wave) + 64 c), zero outside.  With the columns
+// exchanged like that the lane of a wave's own row is a constant, and a lane broadcast from a constant
+// lane takes half the time (5 cycles against 9).
+template <int N>
+__device__ __forceinline__ void tri_reduce(TriRows<N>& a, double* ex, double* U,
+                                           double* dd, double* ee, double* ih) {
+    using T = TriCfg<N, 8>;
+    constexpr int NC = T::NC, PS = T::PS, W = kTriWaves;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (wave >= W) {
+#pragma unroll 1
+        for (int k = 0; k < N; ++k) __syncthreads();    // one for the first row, N - 2 steps, one at the end
+        return;
+    }
+    const int col = (threadIdx.x & 63) ^ (4 * wave);
+    double* row0 = ex + (2 * W + 16) * PS;
+    if (wave == 0) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) row0[col + 64 * c] = a[0][c];
+    }
+    __syncthreads();
+    TriState<N> st;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        st.x[c] = row0[col + 64 * c];
+        st.uo[c] = st.qo[c] = st.er[c] = st.hr[c] = 0.0;
+        st.dr[c] = st.x[c];                             // d_0 in column 0
+    }
+#pragma unroll
+    for (int m = 0; m < T::RS; ++m) st.ur[m] = 0.0;
+    tri_steps<N, 0>(a, st, ex, U, wave, col);
+    // row N-2 is in x; of row N-1 only the last diagonal entry is missing the last update
+    if (wave == (((N - 1) >> 2) & 3)) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const int j = col + 64 * c;
+            if (j == N - 1) st.dr[c] = fma(-2.0 * st.uo[c], st.qo[c], a[4 * ((N - 1) >> 4) + 3][c]);
+            if (j < N) dd[j] = st.dr[c];
+            if (j < N - 2) { ee[j] = st.er[c]; ih[j] = st.hr[c]; }
+            if (j == N - 1) ee[N - 2] = st.x[c];
+        }
+    }
+    __syncthreads();
+}
+
+// Numbers of eigenvalues >= la and >= lb of the tridiagonal matrix (t[i].x = d_i, t[i].y = e_(i-1)^2,
+// t[0].y = 0), from the signs of its leading minors.  Two points per lane share the reads of t, which
+// four waves could not feed to one point each (a 16-byte read occupies the LDS port for 8 cycles per
+// wave, even of one address).  The recurrences are rescaled every 16 steps: a minor shrinks by about
+// |lambda| per step at most, and no wanted eigenvalue is below 1e-10 of the norm.
+template <int N>
+__device__ __forceinline__ void sturm_count_ge(const double2* t, double la, double lb, int& ca, int& cb) {
+    double p = 1.0, pm = 0.0, r = 1.0, rm = 0.0;
+    uint32_t bp = 0, br = 0;
+    int np = 0, nr = 0;
+    auto load = [&](double2 (&v)[8], int i0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) v[s] = t[i0 + s];
+    };
+    auto steps = [&](const double2 (&v)[8]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            const double pn = fma(v[s].x - la, p, -(v[s].y * pm));
+            const double rn = fma(v[s].x - lb, r, -(v[s].y * rm));
+            pm = p; p = pn;
+            rm = r; r = rn;
+            bp = __builtin_amdgcn_alignbit(bp, (uint32_t)__double2hiint(pn), 31);
+            br = __builtin_amdgcn_alignbit(br, (uint32_t)__double2hiint(rn), 31);
+        }
+    };
+    double2 v0[8], v1[8];
+    load(v0, 0);
+    if constexpr (N % 16 == 8) {
+        load(v1, 8);
+        steps(v0);
+        np = __popc((bp ^ (bp >> 1)) & 0xffu);
+        nr = __popc((br ^ (br >> 1)) & 0xffu);
+#pragma unroll
+        for (int s = 0; s < 8; ++s) v0[s] = v1[s];
+    }
+#pragma unroll 1
+    for (int i0 = N % 16; i0 < N; i0 += 16) {
+        load(v1, i0 + 8);
+        steps(v0);
+        load(v0, i0 + 16);                               // the last one reads past the matrix
+        steps(v1);
+        np += __popc((bp ^ (bp >> 1)) & 0xffffu);
+        nr += __popc((br ^ (br >> 1)) & 0xffffu);
+        const int ep = -__builtin_amdgcn_frexp_exp(fmax(fabs(p), fabs(pm)));
+        const int er = -__builtin_amdgcn_frexp_exp(fmax(fabs(r), fabs(rm)));
+        p = __builtin_amdgcn_ldexp(p, ep);
+        pm = __builtin_amdgcn_ldexp(pm, ep);
+        r = __builtin_amdgcn_ldexp(r, er);
+        rm = __builtin_amdgcn_ldexp(rm, er);
+    }
+    ca = N - np;
+    cb = N - nr;
+}
+
+// The R largest eigenvalues of the tridiagonal matrix, scaled by a power of two so that its norm is at
+// most one: lam[0..R-1] descending, to 2^-49 absolute.  256 threads (one wave per SIMD) first count
+// at 512 points for all eigenvalues together; then TP lanes share an eigenvalue and cut its interval
+// into 2 TP + 1 parts per round.  Returns the scale (0: the matrix is zero).
+template <int N, int TP>
+__device__ __forceinline__ double tri_values(const double* dd, const double* ee, double* es, double2* t, double* lam,
+                                             double* scal, int* cnt, int R) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    if (tid < 64) {
+        double bmax = 0.0;
+        for (int i = lane; i < N; i += 64)
+            bmax = fmax(bmax, fabs(dd[i]) + (i ? fabs(ee[i - 1]) : 0.0) + (i < N - 1 ? fabs(ee[i]) : 0.0));
+#pragma unroll
+        for (int m = 1; m < 64; m <<= 1) bmax = fmax(bmax, __shfl_xor(bmax, m));
+        const int ex = __builtin_amdgcn_frexp_exp(bmax);
+        if (lane == 0) scal[0] = bmax > 0.0 ? __builtin_amdgcn_ldexp(1.0, ex) : 0.0;
+        for (int i = lane; i < N; i += 64) {
+            const double e1 = i ? __builtin_amdgcn_ldexp(ee[i - 1], -ex) : 0.0;
+            t[i] = double2{__builtin_amdgcn_ldexp(dd[i], -ex), e1 * e1};
+            if (i) es[i - 1] = e1;
+        }
+    }
+    __syncthreads();
+    const double bound = scal[0];
+    // positive semidefinite up to rounding: [-2^-20, 1] holds every eigenvalue that matters
+    constexpr double kLo = -9.5367431640625e-07, kStep = (1.0 - kLo) / 512;
+    if (tid < 256) {
+        int c0, c1;
+        sturm_count_ge<N>(t, fma(kStep, (double)tid, kLo), fma(kStep, (double)(tid + 256), kLo), c0, c1);
+        cnt[tid] = c0;
+        cnt[tid + 256] = c1;
+    }
+    __syncthreads();
+    if (tid < 256) {
+        const int v = tid / TP, pt = tid % TP;
+        const int k = v < R ? v : R - 1;
+        int at = 0;                                      // last point whose count exceeds k
+#pragma unroll
+        for (int s = 256; s; s >>= 1) at += cnt[at + s] > k ? s : 0;
+        double lo = fma(kStep, (double)at, kLo), w = kStep;
+        constexpr int rounds = TP == 8 ? 10 : 13;        // 17^10 > 2^40, 9^13 > 2^41, after the first 2^9
+#pragma unroll 1
+        for (int it = 0; it < rounds; ++it) {
+            w *= 1.0 / (2 * TP + 1);
+            int c0, c1;
+            sturm_count_ge<N>(t, fma(w, (double)(pt + 1), lo), fma(w, (double)(pt + 1 + TP), lo), c0, c1);
+            const uint64_t m0 = __ballot(c0 > k), m1 = __ballot(c1 > k);
+            constexpr uint32_t kTeam = (1u << TP) - 1u;
+            const int sh = lane & ~(TP - 1);
+            const int above = __popc((uint32_t)(m0 >> sh) & kTeam) + __popc((uint32_t)(m1 >> sh) & kTeam);
+            lo = fma(w, (double)above, lo);
+        }
+        if (pt == 0 && v < R) lam[v] = fma(0.5, w, lo);
+    }
+    __syncthreads();
+    return bound;
+}
+
+// multipliers of the factorization of T - l I from the top (DIR = 1) or the bottom (DIR = -1)
+template <int N, int RB, int DIR>
+__device__ __forceinline__ void tri_factor(const double2* t, const double* es, double l, double* w) {
+    double dn = t[DIR > 0 ? 0 : N - 1].x - l;
+#pragma unroll 8
+    for (int s = 0; s < N - 1; ++s) {
+        const int i = DIR > 0 ? s : N - 1 - s;
+        const double e = es[DIR > 0 ? i : i - 1];
+        const double m = -e * rcp64(dn + 1.0e-300);      // a zero pivot becomes a tiny one
+        w[i * RB] = m;
+        dn = fma(e, m, t[i + DIR].x - l);
+    }
+}
+
+// Eigenvectors v0 .. v0 + nb - 1 of the scaled tridiagonal matrix, from twisted factorizations: the
+// multipliers of the forward and backward factorizations (one wave each) in wa and wb [N][RB], the
+// twist where the pivot is smallest, and the vector grown from it in both directions.  The
+// unnormalized vector replaces wa.
+template <int N, int RB>
+__device__ __forceinline__ void tri_vectors(const double2* t, const double* es, const double* lam, double* wa,
+                                            double* wb, int* twist, int v0, int nb) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (wave == 0) {
+        if (lane < nb) tri_factor<N, RB, 1>(t, es, lam[v0 + lane], wa + lane);
+    } else if (wave == 1) {
+        if (lane < nb) tri_factor<N, RB, -1>(t, es, lam[v0 + lane], wb + lane);
+    }
+    __syncthreads();
+    {
+        const int v = tid >> 3, s = tid & 7;
+        if (v < nb) {
+            const double l = lam[v0 + v];
+            double best = 1.0e300;
+            int bi = 0;
+#pragma unroll 4
+            for (int i = s; i < N; i += 8) {
+                const int ip = i > 0 ? i - 1 : 0, in = i < N - 1 ? i : N - 2;
+                double g = t[i].x - l;
+                g = fma(i > 0 ? es[ip] : 0.0, wa[ip * RB + v], g);
+                g = fma(i < N - 1 ? es[in] : 0.0, wb[(in + 1) * RB + v], g);
+                g = fabs(g);
+                if (g < best) { best = g; bi = i; }
+            }
+#pragma unroll
+            for (int m = 1; m < 8; m <<= 1) {
+                const double ob = __shfl_xor(best, m);
+                const int oi = __shfl_xor(bi, m);
+                if (ob < best || (ob == best && oi < bi)) { best = ob; bi = oi; }
+            }
+            if (s == 0) twist[v] = bi;
+        }
+    }
+    __syncthreads();
+    if (wave < 2 && lane < nb) {
+        const int r = twist[lane];
+        double z = 1.0;
+        if (wave == 0) {
+#pragma unroll 8
+            for (int i = N - 2; i >= 0; --i) {
+                const double m = wa[i * RB + lane];
+                z *= i < r ? m : 1.0;
+                if (i < r) wa[i * RB + lane] = z;
+            }
+            wa[r * RB + lane] = 1.0;
+        } else {
+#pragma unroll 8
+            for (int i = 1; i < N; ++i) {
+                const double m = wb[i * RB + lane];
+                z *= i > r ? m : 1.0;
+                if (i > r) wa[i * RB + lane] = z;
+            }
+        }
+    }
+    __syncthreads();
+}
+
+// Vector v of wa (a column of [N][RB]), normalized, in a team of TB lanes: entry TB*q + u in y[q] of lane u.
+template <int N, int RB, int TB>
+__device__ __forceinline__ void tri_load(const double* wa, int v, int u, double (&y)[N / TB]) {
+    double nn = 0.0;
+#pragma unroll
+    for (int q = 0; q < N / TB; ++q) {
+        y[q] = wa[(TB * q + u) * RB + v];
+        nn = fma(y[q], y[q], nn);
+    }
+    const double sc = rsq64(team_sum64<TB>(nn));
+#pragma unroll
+    for (int q = 0; q < N / TB; ++q) y[q] *= sc;
+}
+
+// cross[k] = u_k . u_(k+1) of the reflectors in U, for k = 0 .. N - 4, one team of eight lanes each.
+template <int N>
+__device__ __forceinline__ void tri_cross(const double* U, double* cross) {
+    const int team = threadIdx.x >> 3, s = threadIdx.x & 7;
+    for (int k = team; k < N - 3; k += kTriThreads / 8) {
+        const double *uk = U + tri_row(N, k), *ul = U + tri_row(N, k + 1);
+        double d = 0.0;
+        for (int j = k + 2 + s; j < N; j += 8) d = fma(uk[j], ul[j], d);
+        d = team_sum64<8>(d);
+        if (s == 0) cross[k] = d;
+    }
+    __syncthreads();
+}
+
+// The reflectors applied to the vector in y, last one first and two at a time: with s1 = u1 . y and
+// s0 = u0 . y taken together, the first one changes the second product by (u0 . u1) s1 / h1.  The block of
+// TB rows that the pivots are in is a compile-time constant, so only one entry per lane needs a mask.
+template <int N, int TB, int QK>
+__device__ __forceinline__ void tri_back_block(const double* U, const double* ih, const double* cross, int u,
+                                               double (&y)[N / TB]) {
+    constexpr int QB = N / TB;
+    constexpr int kTop = TB * QK + TB - 1 < N - 3 ? TB * QK + TB - 1 : N - 3;
+    auto load = [&](int k, double (&w)[QB]) __attribute__((always_inline)) {
+        const double* uk = U + tri_row(N, k) + u;
+        w[QK] = TB * QK + u > k ? uk[TB * QK] : 0.0;
+#pragma unroll
+        for (int q = QK + 1; q < QB; ++q) w[q] = uk[TB * q];
+    };
+    int k = kTop;
+    if constexpr ((kTop - TB * QK) % 2 == 0) {
+        double w[QB], s = 0.0;
+        load(k, w);
+#pragma unroll
+        for (int q = QK; q < QB; ++q) s = fma(w[q], y[q], s);
+        s = team_sum64<TB>(s) * ih[k];
+#pragma unroll
+        for (int q = QK; q < QB; ++q) y[q] = fma(-s, w[q], y[q]);
+        --k;
+    }
+#pragma unroll 1
+    for (; k > TB * QK; k -= 2) {
+        double w1[QB], w0[QB], s1 = 0.0, s0 = 0.0;
+        load(k, w1);
+        load(k - 1, w0);
+        const double h1 = ih[k], h0 = ih[k - 1], cr = cross[k - 1];
+#pragma unroll
+        for (int q = QK; q < QB; ++q) {
+            s1 = fma(w1[q], y[q], s1);
+            s0 = fma(w0[q], y[q], s0);
+        }
+        s1 = team_sum64<TB>(s1) * h1;
+        s0 = team_sum64<TB>(s0);
+        s0 = fma(-cr, s1, s0) * h0;
+#pragma unroll
+        for (int q = QK; q < QB; ++q) y[q] = fma(-s0, w0[q], fma(-s1, w1[q], y[q]));
+    }
+    if constexpr (QK > 0) tri_back_block<N, TB, QK - 1>(U, ih, cross, u, y);
+}
+
+template <int N, int TB>
+__device__ __forceinline__ void tri_back(const double* U, const double* ih, const double* cross, int u,
+                                         double (&y)[N / TB]) {
+    tri_back_block<N, TB, (N - 3) / TB>(U, ih, cross, u, y);
+}
+
+}  // namespace solar

@@ -1,0 +1,76 @@
+"""The routes of the eigensolver at the widths where it changes from one to another: the iteration with
+Jacobi sweeps (narrow blocks), with the dense Ritz step (medium), the direct solution of the whole Gram
+matrix (wide), and the way back to the sweeps when wanted eigenvalues coincide.
+
+Tolerances: the factors come from the float Gram matrix, whose entries carry an absolute error of a few
+2^-24 of the largest eigenvalue; S relative to s_1 and the eigen-residual relative to the largest eigenvalue
+are therefore bounded by 2e-6 (measured 1e-7) and 2e-5, the orthogonality of the float vectors by 2e-5."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lib():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("these tests need the GPU")
+    from paper_2603_02561_amd import binding
+    return binding
+
+
+def factors(lib, X, r):
+    import torch
+    B, N, d = X.shape
+    db = lib.DeviceBatch(X, np.zeros((B, 1, d), dtype=np.float32), None, r, False)
+    db.factorize()
+    torch.cuda.synchronize()
+    return (db.info.cpu().numpy(), db.S.cpu().numpy().astype(np.float64), db.V.cpu().numpy().astype(np.float64))
+
+
+def check(X, info, S, V, r):
+    assert np.all(info == 0), info
+    for b in range(X.shape[0]):
+        G = X[b].astype(np.float64).T @ X[b].astype(np.float64)
+        lam = np.linalg.eigvalsh(G)[::-1][:r]
+        live = lam > 1.2e-5 * lam[0]
+        assert np.all(np.abs(S[b][live] - np.sqrt(lam[live])) < 2e-6 * np.sqrt(lam[0]))
+        Vl = V[b][:, live]
+        assert np.abs(Vl.T @ Vl - np.eye(Vl.shape[1])).max() < 2e-5
+        assert np.abs(G @ Vl - Vl * lam[live]).max() < 2e-5 * lam[0]
+
+
+# r at both sides of every change of route: 8 | 9 and 16 | 17 (d = 64), 40 | 41 (d = 128), and the largest
+@pytest.mark.parametrize("d,r", [(64, 8), (64, 9), (64, 16), (64, 17), (64, 57), (64, 64), (128, 1), (128, 9),
+                                 (128, 33), (128, 40), (128, 41), (128, 64), (256, 8), (256, 32)])
+@pytest.mark.parametrize("noise", [0.0, 0.05])
+def test_routes(lib, d, r, noise):
+    g = np.random.default_rng(100 * d + r)
+    B, N = 3, 700
+    X = np.empty((B, N, d), dtype=np.float32)
+    for b in range(B):
+        U, _ = np.linalg.qr(g.standard_normal((N, r)))
+        W, _ = np.linalg.qr(g.standard_normal((d, r)))
+        X[b] = (U * (30.0 / (1.0 + np.arange(r)) ** 0.7)) @ W.T + noise * g.standard_normal((N, d))
+    print(f"[case] d={d} r={r} noise={noise}", flush=True)
+    check(X, *factors(lib, X, r), r)
+
+
+@pytest.mark.parametrize("d,r", [(64, 12), (64, 40), (128, 24), (128, 64), (256, 16)])
+def test_coinciding_eigenvalues(lib, d, r):
+    """Rows that are unit vectors: G is diagonal with integer entries, several of them equal."""
+    print(f"[case] ties d={d} r={r}", flush=True)
+    counts = np.concatenate([np.repeat(np.arange(40, 40 - (r + 2) // 3, -1), 3)[:r], np.full(d - r, 2)])
+    rows = np.repeat(np.arange(d), counts)
+    X = np.zeros((2, rows.size, d), dtype=np.float32)
+    X[0, np.arange(rows.size), rows] = 1.0
+    perm = np.random.default_rng(d).permutation(d)
+    X[1, np.arange(rows.size), perm[rows]] = 1.0
+    check(X, *factors(lib, X, r), r)
+
+
+def test_zero_matrix(lib):
+    for d, r in ((64, 8), (64, 40), (128, 16), (128, 64)):
+        info, S, V = factors(lib, np.zeros((1, 100, d), dtype=np.float32), r)
+        assert np.all(S == 0.0) and np.all(V == 0.0)
