@@ -3,11 +3,15 @@
 //     O_b = scale * Q_b G_b, G_b = X_b^T X_b from the Gram kernel;
 //   * the learnable projections W_Q, W_K, W_V of the Preliminaries, folded around an operator
 //     that works on H itself: Q' = C (W_Q W_K^T) before it and O' = O W_V after it.
-// Both are Out[rows x d] = scale * In[rows x d] * W[d x d] with a float matrix W (per user or
-// shared) held in LDS and the float 16x16x4 MFMA (G has the dynamic range of squared singular
-// values; the products are tiny next to the attention itself).  A wave owns 16 rows; its A
-// operand is a contiguous quarter of each row per lane group (contraction slot (ks, g) is
-// column g*d/4 + ks, which both operands agree on).
+// Both are Out[rows x d] = scale * In[rows x d] * W[d x d] with a float matrix W, per user or shared.
+//
+// Bound by memory.  W is split once per workgroup into three bf16 matrices that add up to it exactly (24
+// bits) and kept in LDS; the products run on the 32x32x16 bf16 instruction with float accumulation.  A bf16
+// row takes three of them, each product exact; a float row is split the same way and takes the six whose
+// size is above 2^-24 of the leading one, which is the rounding of a float product.  That is a third (or
+// two thirds) of the time of the float instruction for the same precision: 64000 rows of d = 128 take
+// 12.6 us from bf16 to bf16 (2.6 TB/s) and 21.3 from float to float, of d = 256 33.9 and 62.1; with the
+// float instruction, 16 rows per wave and a copy of W per 64 rows 31.5, 38.5, 154.9 and 189.4.
 #include "common.h"
 #include "kernels.h"
 
@@ -15,71 +19,149 @@ namespace solar {
 
 namespace {
 
-constexpr int kRowWaves = 4;
-constexpr int kColChunk = 64;   // output columns per pass over the rows (bounds the LDS image of W)
+constexpr int kRowWaves = 8;
 
+__device__ __forceinline__ v16f mfma32x32x16bf16(v8bf a, v8bf b, v16f c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+
+// x = s[0] + s[1] + s[2] to 24 bits
+__device__ __forceinline__ void split3(const float (&x)[8], v8bf (&s)[3]) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const __bf16 h = (__bf16)x[i];
+        const float r = x[i] - (float)h;
+        const __bf16 m = (__bf16)r;
+        s[0][i] = h;
+        s[1][i] = m;
+        s[2][i] = (__bf16)(r - (float)m);
+    }
+}
+
+template <int D>
+struct RowCfg {
+    static constexpr int NC = D < 128 ? D : (D == 128 ? 128 : 64);   // output columns per workgroup (LDS)
+    static constexpr int LDW = D + 8;                                // bf16 stride of a column: conflict-free
+    static constexpr size_t lds_bytes = (size_t)3 * NC * LDW * 2;
+};
+
+// One wave takes blocks of 32 rows: lane (i, h) holds entries 16 s + 8 h .. + 7 of row i for every step s of
+// the contraction, the next block's rows are loaded while this one is multiplied.
 template <int D, bool IN_BF16, bool OUT_BF16>
 __global__ __launch_bounds__(kRowWaves * 64) void rowgemm_kernel(
     const void* __restrict__ In, const float* __restrict__ W, size_t w_stride, int rows, float scale,
     void* __restrict__ Out) {
-    constexpr int LDW = kColChunk + 1;
-    extern __shared__ __attribute__((aligned(16))) float smem[];   // [D][LDW]
-    const int b = blockIdx.y;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int i16 = lane & 15, g = lane >> 4;
-    const int row0 = (blockIdx.x * kRowWaves + wave) * 16;
-    const int row = row0 + i16;
-    const bool valid = row < rows;
-    const float* Wb = W + (size_t)b * w_stride;
-    // this lane's quarter of its row, as floats
-    float a[D / 4];
+    using C = RowCfg<D>;
+    constexpr int NC = C::NC, LDW = C::LDW, NS = D / 16, NT = NC / 32;
+    constexpr int VS = IN_BF16 ? 1 : 2;                  // 16-byte loads per step
+    constexpr bool AHEAD = NS * VS < 16;                 // two blocks of rows fit the registers
+    extern __shared__ __attribute__((aligned(16))) __bf16 img[];     // [3][NC][LDW]
+    const int b = blockIdx.y, c0 = blockIdx.z * NC;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int i32 = lane & 31, h = lane >> 5;
+    const int nblk = ceil_div(rows, 32), stride = gridDim.x * kRowWaves;
+    const char* in = reinterpret_cast<const char*>(In) + (size_t)b * rows * D * (IN_BF16 ? 2 : 4);
+    v4u raw[AHEAD ? 2 : 1][NS][VS];
+    auto load = [&](int blk, v4u (&r)[NS][VS]) __attribute__((always_inline)) {
+        int row = 32 * blk + i32;
+        row = row < rows ? row : rows - 1;
+        const char* p = in + ((size_t)row * D + 8 * h) * (IN_BF16 ? 2 : 4);
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+            for (int v = 0; v < VS; ++v)
+                r[s][v] = *reinterpret_cast<const v4u*>(p + s * (IN_BF16 ? 32 : 64) + 16 * v);
+    };
+    int blk = blockIdx.x * kRowWaves + wave;
+    if (blk < nblk) load(blk, raw[0]);
     {
-        const size_t off = ((size_t)b * rows + (valid ? row : 0)) * D + (size_t)g * (D / 4);
-        if constexpr (IN_BF16) {
-            const uint16_t* p = reinterpret_cast<const uint16_t*>(In) + off;
+        const float* Wb = W + (size_t)b * w_stride + c0;
+        for (int e = tid; e < NC * (D / 8); e += kRowWaves * 64) {
+            const int c = e % NC, k8 = e / NC;
+            float x[8];
+            v8bf s[3];
 #pragma unroll
-            for (int q = 0; q < D / 16; ++q) {
-                const uint2 v = *reinterpret_cast<const uint2*>(p + 4 * q);
-                a[4 * q + 0] = bf16_lo(v.x); a[4 * q + 1] = bf16_hi(v.x);
-                a[4 * q + 2] = bf16_lo(v.y); a[4 * q + 3] = bf16_hi(v.y);
-            }
-        } else {
-            const float* p = reinterpret_cast<const float*>(In) + off;
+            for (int k = 0; k < 8; ++k) x[k] = Wb[(size_t)(8 * k8 + k) * D + c];
+            split3(x, s);
 #pragma unroll
-            for (int q = 0; q < D / 16; ++q) {
-                const v4f v = *reinterpret_cast<const v4f*>(p + 4 * q);
-                a[4 * q + 0] = v.x; a[4 * q + 1] = v.y; a[4 * q + 2] = v.z; a[4 * q + 3] = v.w;
-            }
-        }
-        if (!valid) {
-#pragma unroll
-            for (int k = 0; k < D / 4; ++k) a[k] = 0.f;
+            for (int p = 0; p < 3; ++p) *reinterpret_cast<v8bf*>(img + (p * NC + c) * LDW + 8 * k8) = s[p];
         }
     }
-    for (int c0 = 0; c0 < D; c0 += kColChunk) {
-        __syncthreads();
-        for (int e = threadIdx.x; e < D * kColChunk; e += kRowWaves * 64) {
-            const int k = e / kColChunk, c = e % kColChunk;
-            smem[k * LDW + c] = Wb[(size_t)k * D + c0 + c];
+    __syncthreads();
+    const __bf16* wb = img + i32 * LDW + 8 * h;
+    auto multiply = [&](int at, const v4u (&r)[NS][VS]) __attribute__((always_inline)) {
+        v16f acc[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
+        // the operands from LDS one step ahead of the products, and no further: left alone, the compiler
+        // reads all steps' at once and spills
+        v8bf w[2][NT][3];
+        auto read = [&](int s, v8bf (&d)[NT][3]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int p = 0; p < 3; ++p)
+                    d[t][p] = *reinterpret_cast<const v8bf*>(wb + (p * NC + 32 * t) * LDW + 16 * s);
+        };
+        read(0, w[0]);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            if (s + 1 < NS) read(s + 1, w[(s + 1) & 1]);
+            v8bf a[3];
+            if constexpr (IN_BF16) {
+                a[0] = __builtin_bit_cast(v8bf, r[s][0]);
+            } else {
+                float x[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) x[k] = __uint_as_float(r[s][k / 4][k % 4]);
+                split3(x, a);
+            }
+            auto product = [&](int i, int j) __attribute__((always_inline)) {
+#pragma unroll
+                for (int t = 0; t < NT; ++t) acc[t] = mfma32x32x16bf16(a[i], w[s & 1][t][j], acc[t]);
+            };
+            // the small products first
+            product(0, 2);
+            if constexpr (!IN_BF16) {
+                product(1, 1);
+                product(2, 0);
+                product(1, 0);
+            }
+            product(0, 1);
+            product(0, 0);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        __syncthreads();
+        // component e is row 8 (e / 4) + 4 h + e % 4 of the block, column i32 of the tile
+        const int row0 = 32 * at + 4 * h;
 #pragma unroll
-        for (int cb = 0; cb < kColChunk / 16; ++cb) {
-            v4f acc = v4f{0.f, 0.f, 0.f, 0.f};
-            const float* wcol = smem + (g * (D / 4)) * LDW + 16 * cb + i16;
+        for (int e = 0; e < 16; ++e) {
+            const int row = row0 + 8 * (e / 4) + e % 4;
+            if (row < rows) {
+                const size_t o = ((size_t)b * rows + row) * D + c0 + i32;
 #pragma unroll
-            for (int ks = 0; ks < D / 4; ++ks) acc = mfma16x16x4(a[ks], wcol[ks * LDW], acc);
-            // element t of the accumulator is row 4*g + t of the wave's block, column i16
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int orow = row0 + 4 * g + t;
-                if (orow < rows) {
-                    const size_t o = ((size_t)b * rows + orow) * D + c0 + 16 * cb + i16;
-                    const float v = scale * acc[t];
-                    if constexpr (OUT_BF16) reinterpret_cast<__bf16*>(Out)[o] = (__bf16)v;
-                    else reinterpret_cast<float*>(Out)[o] = v;
+                for (int t = 0; t < NT; ++t) {
+                    const float v = scale * acc[t][e];
+                    if constexpr (OUT_BF16) reinterpret_cast<__bf16*>(Out)[o + 32 * t] = (__bf16)v;
+                    else reinterpret_cast<float*>(Out)[o + 32 * t] = v;
                 }
             }
+        }
+    };
+    if constexpr (AHEAD) {
+        for (; blk < nblk; blk += 2 * stride) {
+            if (blk + stride < nblk) load(blk + stride, raw[1]);
+            multiply(blk, raw[0]);
+            if (blk + stride >= nblk) break;
+            if (blk + 2 * stride < nblk) load(blk + 2 * stride, raw[0]);
+            multiply(blk + stride, raw[1]);
+        }
+    } else {
+        while (blk < nblk) {
+            multiply(blk, raw[0]);
+            blk += stride;
+            if (blk < nblk) load(blk, raw[0]);
         }
     }
 }
@@ -87,14 +169,18 @@ __global__ __launch_bounds__(kRowWaves * 64) void rowgemm_kernel(
 template <int D>
 hipError_t launch_d(const void* In, const float* W, size_t w_stride, int B, int rows, float scale, bool in_bf16,
                     bool out_bf16, void* Out, hipStream_t stream) {
-    const size_t lds = sizeof(float) * (size_t)D * (kColChunk + 1);
-    dim3 grid(ceil_div(rows, kRowWaves * 16), B), block(kRowWaves * 64);
+    using C = RowCfg<D>;
+    // one workgroup per compute unit (the images of W take more than half of its LDS), none without a block
+    // of rows for every wave
+    constexpr int NZ = D / C::NC;
+    const int want = ceil_div(ceil_div(rows, 32), kRowWaves), room = ceil_div(256, B * NZ);
+    dim3 grid(want < room ? want : room, B, NZ), block(kRowWaves * 64);
 #define SOLAR_ROWGEMM(IB, OB)                                                                        \
     do {                                                                                             \
         auto kern = rowgemm_kernel<D, IB, OB>;                                                       \
-        hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds);    \
+        hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), C::lds_bytes);         \
         if (e != hipSuccess) return e;                                                               \
-        hipLaunchKernelGGL(kern, grid, block, lds, stream, In, W, w_stride, rows, scale, Out);       \
+        hipLaunchKernelGGL(kern, grid, block, C::lds_bytes, stream, In, W, w_stride, rows, scale, Out); \
     } while (0)
     if (in_bf16 && out_bf16) SOLAR_ROWGEMM(true, true);
     else if (in_bf16) SOLAR_ROWGEMM(true, false);

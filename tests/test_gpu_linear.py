@@ -83,3 +83,25 @@ def test_folded_projections(lib, oracle, name, w):
     e2 = rel_err(Of.cpu().numpy().astype(np.float64), want)
     print(f"  output err {e2:.3e}", flush=True)
     assert e2 < (1e-4 if not bf16 else 2e-2)
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("rows", [1, 31, 33, 255, 257, 8225])
+@pytest.mark.parametrize("in_bf16,out_bf16", [(True, True), (True, False), (False, True), (False, False)])
+def test_row_blocks(lib, d, rows, in_bf16, out_bf16):
+    """Rows at the edges of the 32-row blocks, of a workgroup's eight and of the second round of workgroups,
+    against the product in double precision.  Float outputs: the operands are exact sums of bf16 terms, so
+    what is left is the rounding of a float sum of d products, d 2^-24 at worst (1.6e-5 of the norm of a row
+    times that of a column; measured 3e-7); a bf16 output adds 2^-9 of its own size (2^-7 allowed)."""
+    import torch
+    print(f"[case] row blocks d={d} rows={rows} {in_bf16} {out_bf16}", flush=True)
+    g = torch.Generator().manual_seed(1000 * d + rows)
+    In = torch.randn(rows, d, generator=g).to(torch.bfloat16 if in_bf16 else torch.float32).cuda()
+    W = torch.randn(d, d, generator=g).cuda()
+    Out = torch.full((rows, d), 7.0, dtype=torch.bfloat16 if out_bf16 else torch.float32, device="cuda")
+    lib.solar_apply_weights(In, W, Out)
+    torch.cuda.synchronize()
+    want = In.double() @ W.double()
+    size = In.double().norm(dim=1, keepdim=True) * W.double().norm(dim=0, keepdim=True)
+    err = ((Out.double() - want).abs() / (size + (want.abs() * 2.0 ** 8 if out_bf16 else 0))).max().item()
+    assert err < (2.0 ** -16 if not out_bf16 else 2.0 ** -15)
