@@ -117,10 +117,27 @@ __device__ __forceinline__ uint2 lds_read_tr16(const uint16_t* p) {
 // of every 16 ranks are swapped
 __device__ __forceinline__ int quad_pos(int c4) { return (c4 & ~3) | ((c4 & 1) << 1) | ((c4 >> 1) & 1); }
 
+// Dynamic LDS of a variant.
+template <int D, int RP, bool FUSED, bool SPLIT>
+struct X32Lds {
+    static constexpr int LDR = RP + 8;
+    static constexpr bool kShareVt = SPLIT && !FUSED;              // vt lies where the images go
+    static constexpr size_t kTiles = SPLIT ? (size_t)kWaves * 3 * 32 * LDR : (size_t)3 * kNT * LDR;
+    static constexpr size_t kVt = 2 * (size_t)RP * (D + 8), kVimg = 2 * (size_t)D * LDR;
+    static constexpr size_t bytes = 2 * (kTiles + kVimg + (kShareVt ? 0 : kVt)) + 16;
+    // the images of 64 ranks and of V do not fit together when the projection reads V in the loop
+    static constexpr bool fits = bytes <= 160 * 1024;
+    static_assert(!kShareVt || kVt <= kTiles, "vt fits the images it shares memory with");
+};
+
 // FUSED: Pin is the user's X (bf16, [B][N][D]) and the loader forms the rows of P = X V itself
 // (the projection of Section "SVD-Attention" evaluated where it is consumed; every workgroup of
 // a user repeats it); otherwise Pin is P (float, [B][N][r]).
-template <int D, int RP, bool FUSED>
+// SPLIT: for launches that would leave most of the GPU idle.  The eight waves take the same 32 queries and every
+// eighth block of 32 rows each, in tile images of their own (loaded and converted by the wave, no barrier in
+// the loop), and their references, row sums and Z are merged through LDS before the epilogue: eight
+// times the workgroups, an eighth of the blocks per wave.
+template <int D, int RP, bool FUSED, bool SPLIT>
 __global__ __launch_bounds__(kThreads) void attention_seq_x32_kernel(
     const void* __restrict__ Qv, const float* __restrict__ S, const float* __restrict__ V,
     const void* __restrict__ Pin, const int32_t* __restrict__ lengths, int B, int N, int r, int M,
@@ -130,20 +147,27 @@ __global__ __launch_bounds__(kThreads) void attention_seq_x32_kernel(
     constexpr int LDR = RP + 8, kBuf = kNT * LDR;
     constexpr int NC = RP / 16;   // 16-rank chunks of the score product
     constexpr int NH = RP / 32;   // 32-rank halves of Z
+    using Lds = X32Lds<D, RP, FUSED, SPLIT>;
+    constexpr int kBlk = 32 * LDR;   // image of one block
     extern __shared__ __attribute__((aligned(16))) float smem[];
     // V as bf16 head (truncated, so the remainder is exact) and tail, in the two orders the
     // matrix unit wants it: transposed for Qt^T = V^T Q^T (and the fused projection), and row
     // by row with the rank quads in the order of the tile images for O^T = V Z^T
     constexpr int LDVT = D + 8, LDI = RP + 8;                      // bf16 elements
-    uint16_t* tiles = reinterpret_cast<uint16_t*>(smem);           // [3][kBuf]
-    int* redo = reinterpret_cast<int*>(tiles + 3 * kBuf);          // set when a wave's optimistic pass overflowed
-    uint16_t* vt = reinterpret_cast<uint16_t*>(redo + 4);          // [2][RP][LDVT]
-    uint16_t* vimg = vt + 2 * RP * LDVT;                           // [2][D][LDI]
+    uint16_t* tiles = reinterpret_cast<uint16_t*>(smem);           // [3][kBuf]; SPLIT: [waves][3][kBlk]
+    int* redo = reinterpret_cast<int*>(tiles + Lds::kTiles);       // set when a wave's optimistic pass overflowed
+    uint16_t* vimg = reinterpret_cast<uint16_t*>(redo + 4);        // [2][D][LDI]
+    // [2][RP][LDVT]; only the prologue (and the fused projection) reads it
+    uint16_t* vt = Lds::kShareVt ? tiles : vimg + 2 * D * LDI;
     // Workgroups are dealt to the 8 XCDs round-robin by linear id.  All M-tiles of a user
     // get ids that agree modulo 8, so they share one XCD and its L2 holds that user's P once.
-    const int mtiles = ceil_div(M, kWaves * kQW);
-    const int slot_id = blockIdx.x >> 3;
-    const int place = (slot_id / mtiles) * 8 + (blockIdx.x & 7);
+    constexpr int kQT = SPLIT ? kQW : kWaves * kQW;                // queries per workgroup
+    const int mtiles = ceil_div(M, kQT);
+    // Fewer than eight users would leave XCDs idle that way: they take consecutive ids and every XCD reads
+    // its own copy.
+    const bool spread = B < 8;
+    const int slot_id = spread ? (int)blockIdx.x : (int)(blockIdx.x >> 3);
+    const int place = spread ? slot_id / mtiles : (slot_id / mtiles) * 8 + (int)(blockIdx.x & 7);
     if (place >= B) return;   // uniform over the workgroup
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n32 = lane & 31, h = lane >> 5;
@@ -169,7 +193,7 @@ __global__ __launch_bounds__(kThreads) void attention_seq_x32_kernel(
         __syncthreads();
     }
     const int len = user_len(lengths, b, N);
-    const int m_wave = (slot_id % mtiles) * (kWaves * kQW) + wave * kQW;
+    const int m_wave = (slot_id % mtiles) * kQT + (SPLIT ? 0 : wave * kQW);
     // P is scaled into [-1, 1] by the largest singular value before it is rounded to fp16
     // when that value lies outside [1, 2^13]; inside that range fp16 holds P as it is
     float pscale = 1.f, punscale = 1.f;
@@ -201,9 +225,13 @@ __global__ __launch_bounds__(kThreads) void attention_seq_x32_kernel(
         const int e = tid + i * kThreads, k = e / (RP / 4), c4 = e % (RP / 4);
         vreg[i] = 4 * c4 < r ? *reinterpret_cast<const v4f*>(V + ((size_t)b * D + k) * r + 4 * c4) : v4f{0.f, 0.f, 0.f, 0.f};
     }
-    // zero the tile buffers once: padded rank columns stay zero for ever
-    static_assert((3 * kBuf) % 8 == 0, "whole 16-byte stores");
-    for (int e = tid; e < 3 * kBuf / 8; e += kThreads) reinterpret_cast<v4u*>(tiles)[e] = v4u{0u, 0u, 0u, 0u};
+    // zero the tile buffers once: padded rank columns stay zero for ever (images that share memory with vt
+    // are zeroed below)
+    static_assert(Lds::kTiles % 8 == 0, "whole 16-byte stores");
+    auto zero_tiles = [&]() __attribute__((always_inline)) {
+        for (int e = tid; e < (int)Lds::kTiles / 8; e += kThreads) reinterpret_cast<v4u*>(tiles)[e] = v4u{0u, 0u, 0u, 0u};
+    };
+    if constexpr (!Lds::kShareVt) zero_tiles();
     if (tid == 0) *redo = 0;
 #pragma unroll
     for (int i = 0; i < VQ; ++i) {
@@ -254,6 +282,14 @@ __global__ __launch_bounds__(kThreads) void attention_seq_x32_kernel(
             for (int u = 0; u < 8; ++u)
                 q[u] = fminf(fmaxf(qt[c / 2][8 * (c % 2) + u] * (scale * kLog2e * punscale), -6.0e4f), 6.0e4f);
             qB[c] = v4u{pack_f16(q[0], q[1]), pack_f16(q[2], q[3]), pack_f16(q[4], q[5]), pack_f16(q[6], q[7])};
+        }
+    }
+
+    if constexpr (Lds::kShareVt) {   // the images of the blocks take the place of vt
+        __syncthreads();
+        if (r < RP) {
+            zero_tiles();
+            __syncthreads();
         }
     }
 
@@ -346,6 +382,86 @@ __global__ __launch_bounds__(kThreads) void attention_seq_x32_kernel(
                 if (__builtin_expect(rescale, 0)) x *= pscale;   // uniform
                 *reinterpret_cast<uint2*>(dst + i * LDR) = uint2{pack_f16(x[0], x[1]), pack_f16(x[2], x[3])};
             }
+        }
+    };
+
+    // -- SPLIT: the same for the wave's own blocks of 32 rows, block j of the wave being block wave + 8 j of the
+    // sequence.  P given: a load instruction covers 64 / kQuads rows; X given: two halves of 16 rows.
+    constexpr int RI = 32 * kQuads / 64;
+    constexpr int NSB = (FUSED || RP == 64) ? 1 : 2;   // blocks whose loads are in flight
+    v4f bstage[NSB][FUSED ? 1 : RI];
+    v4u bxst[FUSED ? 2 : 1][FUSED ? KS : 1];
+    const int lb_row = lane / kQuads, lb_c4 = lane % kQuads;
+    const bool lb_active = 4 * lb_c4 < r;
+    const uint32_t lb_col = 16u * (uint32_t)min(lb_c4, (r >> 2) - 1);
+    const int lb_dst = lb_row * LDR + 4 * quad_pos(lb_c4);
+    const uint32_t lb_off0 = (uint32_t)(32 * wave + (FUSED ? (lane & 15) : lb_row)) * row_bytes + (FUSED ? 0u : lb_col);
+    const uint32_t lb_step = 32u * kWaves * row_bytes;   // from block to block of the wave
+    uint32_t lb_off = lb_off0;
+    constexpr int LH = FUSED ? 16 : 64 / kQuads;         // rows between two loads
+    auto fetch_block = [&](int j, auto set_tag) __attribute__((always_inline)) {
+        constexpr int set = decltype(set_tag)::value;
+        const int row0 = 32 * (wave + kWaves * j);
+        uint32_t o[FUSED ? 2 : RI];
+#pragma unroll
+        for (int i = 0; i < (FUSED ? 2 : RI); ++i) o[i] = lb_off + i * LH * row_bytes;
+        if (__builtin_expect(row0 + 32 > len, 0)) {      // uniform: ragged or past the end, rows clamped
+#pragma unroll
+            for (int i = 0; i < (FUSED ? 2 : RI); ++i)
+                o[i] = (uint32_t)min(row0 + i * LH + (FUSED ? (lane & 15) : lb_row), last_row) * row_bytes +
+                       (FUSED ? 0u : lb_col);
+        }
+        if constexpr (FUSED) {
+#pragma unroll
+            for (int hf = 0; hf < 2; ++hf) {
+                const v4u* p = reinterpret_cast<const v4u*>(Pbytes + o[hf]);
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) bxst[hf][ks] = p[ks];
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < RI; ++i) bstage[set][i] = *reinterpret_cast<const v4f*>(Pbytes + o[i]);
+        }
+        lb_off += lb_step;
+    };
+    auto commit_block = [&](uint16_t* buf, int j, auto set_tag) __attribute__((always_inline)) {
+        constexpr int set = decltype(set_tag)::value;
+        const int row0 = 32 * (wave + kWaves * j);
+        const bool ragged = row0 + 32 > len;   // uniform
+        if constexpr (FUSED) {
+#pragma unroll
+            for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+                for (int nb = 0; nb < RP / 16; ++nb) {
+                    v4f pa = v4f{0.f, 0.f, 0.f, 0.f};
+                    const uint16_t* va = vt + (16 * nb + (lane & 15)) * LDVT + (D / 4) * fx_g;
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks) {
+                        pa = mfma16x16x32bf16(*reinterpret_cast<const v4u*>(va + 8 * ks), bxst[hf][ks], pa);
+                        pa = mfma16x16x32bf16(*reinterpret_cast<const v4u*>(va + RP * LDVT + 8 * ks), bxst[hf][ks], pa);
+                    }
+                    const int row = 16 * hf + (lane & 15), quad = 4 * nb + fx_g;
+                    if (__builtin_expect(ragged, 0)) {
+                        if (row0 + row >= len) pa = v4f{0.f, 0.f, 0.f, 0.f};
+                    }
+                    if (__builtin_expect(rescale, 0)) pa *= pscale;   // uniform
+                    *reinterpret_cast<uint2*>(buf + row * LDR + 4 * quad_pos(quad)) =
+                        uint2{pack_f16(pa[0], pa[1]), pack_f16(pa[2], pa[3])};   // ranks past r: V is zero there
+                }
+        } else if (lb_active) {
+            if (__builtin_expect(ragged, 0)) {
+#pragma unroll
+                for (int i = 0; i < RI; ++i)
+                    if (row0 + i * LH + lb_row >= len) bstage[set][i] = v4f{0.f, 0.f, 0.f, 0.f};
+            }
+            if (__builtin_expect(rescale, 0)) {   // uniform
+#pragma unroll
+                for (int i = 0; i < RI; ++i) bstage[set][i] *= pscale;
+            }
+#pragma unroll
+            for (int i = 0; i < RI; ++i)
+                *reinterpret_cast<uint2*>(buf + lb_dst + i * LH * LDR) =
+                    uint2{pack_f16(bstage[set][i][0], bstage[set][i][1]), pack_f16(bstage[set][i][2], bstage[set][i][3])};
         }
     };
 
@@ -591,8 +707,63 @@ __global__ __launch_bounds__(kThreads) void attention_seq_x32_kernel(
     const int nblocks = ceil_div(len, 32);
     using tag0 = std::integral_constant<int, 0>;
     using tag1 = std::integral_constant<int, 1>;
+    // SPLIT: blocks of this wave
+    const int nmine = nblocks > wave ? (nblocks - wave - 1) / kWaves + 1 : 0;
+    auto pass_split = [&](auto guard_tag) __attribute__((always_inline)) {
+        constexpr bool guarded = decltype(guard_tag)::value;
+        uint16_t* mine = tiles + wave * (3 * kBlk);
+        reset_state();
+        lb_off = lb_off0;
+        fetch_block(0, tag0{});
+        commit_block(mine, 0, tag0{});
+        fetch_block(1, tag0{});
+        commit_block(mine + kBlk, 1, tag0{});
+        fetch_block(2, tag0{});
+        if constexpr (NSB == 2) fetch_block(3, tag1{});
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            sA[0][c] = *reinterpret_cast<const v4u*>(mine + sa_off + 16 * c);
+            sA[1][c] = *reinterpret_cast<const v4u*>(mine + kBlk + sa_off + 16 * c);
+        }
+        s[0] = mma32(sA[0][0], qB[0], cinit);
+#pragma unroll
+        for (int c = 1; c < NC; ++c) s[0] = mma32(sA[0][c], qB[c], s[0]);
+#pragma unroll
+        for (int t = 0; t < 16; ++t) s[1][t] = 0.f;
+        if (nmine > 0) {
+            mask_block(0, wave);
+            move_reference(0, true, guarded ? 0.f : head);
+        }
+        int o_cur = 0, o_nxt = kBlk, o_wr = 2 * kBlk;
+        // block j: block j + 2 (loaded NSB blocks ago) into the free image, the loads of block j + 2 + NSB, the slot
+        auto run_block = [&](int j, auto par_tag) __attribute__((always_inline)) {
+            using set_tag = std::integral_constant<int, NSB == 2 ? decltype(par_tag)::value : 0>;
+            commit_block(mine + o_wr, j + 2, set_tag{});
+            fetch_block(j + 2 + NSB, set_tag{});
+            slot(wave + kWaves * j, par_tag, guard_tag, mine + o_wr + sa_off, mine + o_cur + za_off);
+            const int o = o_cur; o_cur = o_nxt; o_nxt = o_wr; o_wr = o;
+        };
+        int j = 0;
+        for (; j + 1 < nmine; j += 2) {
+            run_block(j, tag0{});
+            run_block(j + 1, tag1{});
+        }
+        if (j < nmine) run_block(j, tag0{});
+        // Z of the last block trails the loop
+        if (nmine > 0) {
+            const bool odd = (nmine - 1) & 1;
+#pragma unroll
+            for (int hh = 0; hh < NH; ++hh)
+#pragma unroll
+                for (int c = 0; c < 2; ++c)
+                    z[hh] = odd ? mma32(zA[1][hh][c], wp[1][c], z[hh]) : mma32(zA[0][hh][c], wp[0][c], z[hh]);
+        } else {
+            mref = -INFINITY;
+        }
+    };
     auto pass = [&](auto guard_tag) __attribute__((always_inline)) {
     constexpr bool guarded = decltype(guard_tag)::value;
+    if constexpr (SPLIT) { pass_split(guard_tag); return; }
     reset_state();
     if (ntiles > 0) { fetch(0, tag0{}); commit(tiles, 0, tag0{}); }
     if (ntiles > 1) { fetch(1, tag0{}); commit(tiles + kBuf, 1, tag0{}); }
@@ -685,6 +856,42 @@ __global__ __launch_bounds__(kThreads) void attention_seq_x32_kernel(
             const float l0 = __shfl(lacc[0], n32 & 15), l1 = __shfl(lacc[1], n32 & 15);
             l = n32 < 16 ? l0 : l1;
         }
+        if constexpr (SPLIT) {
+            // the waves' sums on the largest of their references, in the order of the waves
+            float* ml = reinterpret_cast<float*>(tiles);                   // [waves][2][32] reference, row sum
+            v4f* zq = reinterpret_cast<v4f*>(ml + kWaves * 64);            // [waves][NH * 4][64]
+            __syncthreads();                                               // the images are done with
+            if (h == 0) { ml[wave * 64 + n32] = mref; ml[wave * 64 + 32 + n32] = l; }
+#pragma unroll
+            for (int hh = 0; hh < NH; ++hh)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    zq[((wave * NH + hh) * 4 + q) * 64 + lane] = v4f{z[hh][4 * q], z[hh][4 * q + 1], z[hh][4 * q + 2], z[hh][4 * q + 3]};
+            __syncthreads();
+            if (wave >= D / 32) return;   // uniform: a wave of the epilogue takes 32 columns
+            float top = -INFINITY;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) top = fmaxf(top, ml[w * 64 + n32]);
+            l = 0.f;
+#pragma unroll
+            for (int hh = 0; hh < NH; ++hh)
+#pragma unroll
+                for (int t = 0; t < 16; ++t) z[hh][t] = 0.f;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {
+                const float mw = ml[w * 64 + n32];
+                const float f = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - top);
+                l += f * ml[w * 64 + 32 + n32];
+#pragma unroll
+                for (int hh = 0; hh < NH; ++hh)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const v4f v = zq[((w * NH + hh) * 4 + q) * 64 + lane];
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) z[hh][4 * q + t] += f * v[t];
+                    }
+            }
+        }
         const float inv = l > 0.f ? punscale / l : 0.f;
         v4u zh[NC], zl[NC];
 #pragma unroll
@@ -702,7 +909,7 @@ __global__ __launch_bounds__(kThreads) void attention_seq_x32_kernel(
             zh[c] = v4u{hw[0], hw[1], hw[2], hw[3]};
             zl[c] = v4u{lw[0], lw[1], lw[2], lw[3]};
         }
-        for (int db = 0; db < D / 32; ++db) {
+        for (int db = SPLIT ? wave : 0; db < D / 32; db += SPLIT ? kWaves : 1) {
             v16f o;
 #pragma unroll
             for (int t = 0; t < 16; ++t) o[t] = 0.f;
@@ -725,24 +932,51 @@ __global__ __launch_bounds__(kThreads) void attention_seq_x32_kernel(
     }
 }
 
+// Which form: rounds of workgroups times the thousands of cycles of one, both measured (one to 24 users, N = 300
+// to 20000).  A block of 32 rows costs a wave 0.6 (0.85 with 64 ranks) in the common form, where eight waves share
+// the conversion of a tile, and 0.95 (1.5) when it converts its own; with the projection in the loop 0.7 to 1.5
+// against 2.1 to 8.5, because every wave then reads all of V from LDS for every block.  The split form pays
+// while its workgroups do not need many more rounds: one user, N = 20000, M = 1000, r = 32 takes 41 us instead of
+// 168 (64 ranks: 58 instead of 223), 24 users 145 instead of 177; 64 users stay in the common form.
+inline int rounds_of(int B, int mtiles) {
+    return B < 8 ? ceil_div(B * mtiles, 256) : ceil_div(ceil_div(B, 8) * mtiles, 32);
+}
 template <int D, int RP, bool FUSED>
-hipError_t launch_d(const void* Q, const float* S, const float* V, const void* P, const int32_t* lengths,
-                    int B, int N, int r, int M, float scale, float* O, hipStream_t stream) {
+bool split_pays(int B, int N, int M) {
+    const double blocks = ceil_div(N, 32);
+    const double block = FUSED ? (RP == 32 ? 0.4 + D / 230.0 : 0.7 + D / 180.0) : (RP == 32 ? 0.6 : 0.85);
+    const double block_split = FUSED ? RP / 32 * (D / 30.5) : (RP == 32 ? 0.95 : 1.5);
+    return rounds_of(B, ceil_div(M, kQW)) * (30.0 + block_split * blocks / kWaves) <
+           rounds_of(B, ceil_div(M, kWaves * kQW)) * (23.0 + block * blocks);
+}
+
+template <int D, int RP, bool FUSED, bool SPLIT>
+hipError_t launch_form(const void* Q, const float* S, const float* V, const void* P, const int32_t* lengths,
+                       int B, int N, int r, int M, float scale, float* O, hipStream_t stream) {
     // debug switch (solar_debug_option): skip the optimistic pass
     const int guarded_only = (debug_force_guarded_pass() || N > kOptimisticMaxN) ? 1 : 0;
     const float head = optimistic_head_room(N);
-    constexpr int kBuf = kNT * (RP + 8);
-    const size_t lds = sizeof(uint16_t) * (3 * (size_t)kBuf + 2 * RP * (size_t)(D + 8) + 2 * D * (size_t)(RP + 8)) + 16;
-    dim3 grid(ceil_div(M, kWaves * kQW) * 8 * ceil_div(B, 8)), block(kThreads);
+    constexpr size_t lds = X32Lds<D, RP, FUSED, SPLIT>::bytes;
+    dim3 grid(ceil_div(M, SPLIT ? kQW : kWaves * kQW) * (B < 8 ? B : 8 * ceil_div(B, 8))), block(kThreads);
     // ranking the users costs every workgroup B^2 / 512 comparisons per thread: worth it only when the
     // launch runs in several rounds of workgroups and the lengths can differ
     const int longest_first = lengths != nullptr && grid.x > 256 && B <= 512;
-    auto kern = attention_seq_x32_kernel<D, RP, FUSED>;
+    auto kern = attention_seq_x32_kernel<D, RP, FUSED, SPLIT>;
     hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, grid, block, lds, stream, Q, S, V, P, lengths, B, N, r, M, scale, guarded_only,
                        head, longest_first, O);
     return hipGetLastError();
+}
+
+template <int D, int RP, bool FUSED>
+hipError_t launch_d(const void* Q, const float* S, const float* V, const void* P, const int32_t* lengths,
+                    int B, int N, int r, int M, float scale, float* O, hipStream_t stream) {
+    if constexpr (X32Lds<D, RP, FUSED, true>::fits) {
+        if (split_pays<D, RP, FUSED>(B, N, M))
+            return launch_form<D, RP, FUSED, true>(Q, S, V, P, lengths, B, N, r, M, scale, O, stream);
+    }
+    return launch_form<D, RP, FUSED, false>(Q, S, V, P, lengths, B, N, r, M, scale, O, stream);
 }
 
 }  // namespace
