@@ -288,25 +288,31 @@ solar_status solar_svd_factorize_rsvd(const void* X, const int32_t* lengths, int
     float* Y = reinterpret_cast<float*>(base);
     base += align256(sizeof(float) * (size_t)B * N * r);
     float* Wb = reinterpret_cast<float*>(base);
-    base += align256(sizeof(float) * (size_t)B * d * r);
-    float* Gy = reinterpret_cast<float*>(base);
-    base += align256(sizeof(float) * (size_t)B * r * r);
+    base += align256(sizeof(float) * (size_t)B * d * r) + align256(sizeof(float) * (size_t)B * r * r);
     float* partials = reinterpret_cast<float*>(base);
     hipStream_t st = (hipStream_t)stream;
     const bool bf16 = t == SOLAR_BF16;
-    hipError_t e = launch_project(X, lengths, Omega, nullptr, B, N, d, r, bf16, Y, st);
-    if (e != hipSuccess) return SOLAR_ERR_HIP;
-    for (int it = 0; it <= n_iter; ++it) {
-        e = launch_xty(X, Y, lengths, B, N, d, r, bf16, partials, Wb, Gy, st);
+    const int nsplit = gram_nsplit(B, N);
+    hipError_t e;
+    const float* block = Omega;
+    for (int it = 0;; ++it) {
+        const bool last = it == n_iter;
+        if (bf16) {
+            // Y = H Omega is formed inside the pass
+            e = launch_power_pass(static_cast<const uint16_t*>(X), block, lengths, B, N, d, r, last, partials, st);
+        } else {
+            e = launch_project(X, lengths, block, nullptr, B, N, d, r, false, Y, st);
+            if (e != hipSuccess) return SOLAR_ERR_HIP;
+            e = launch_xty(static_cast<const float*>(X), Y, lengths, B, N, d, r, partials, st);
+        }
         if (e != hipSuccess) return SOLAR_ERR_HIP;
-        if (it == n_iter) break;
+        if (last) break;
         // Omega <- H^T (H Omega), replaced by an orthonormal basis of the same range
-        e = launch_orthonormalize_block(Wb, B, d, r, st);
+        e = launch_orthonormalize_block(partials, nsplit, !bf16, Wb, B, d, r, st);
         if (e != hipSuccess) return SOLAR_ERR_HIP;
-        e = launch_project(X, lengths, Wb, nullptr, B, N, d, r, bf16, Y, st);
-        if (e != hipSuccess) return SOLAR_ERR_HIP;
+        block = Wb;
     }
-    e = launch_rsvd_small(Wb, Gy, lengths, B, N, d, r, S, V, info, st);
+    e = launch_rsvd_small(partials, nsplit, lengths, B, N, d, r, S, V, info, st);
     if (e != hipSuccess) return SOLAR_ERR_HIP;
     if (P) {
         e = launch_project(X, lengths, V, info, B, N, d, r, bf16, P, st);

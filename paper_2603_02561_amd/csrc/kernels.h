@@ -39,16 +39,23 @@ int eig_block_columns(int d, int r);
 hipError_t launch_eig(const float* G, const float* partials, int nsplit, const int32_t* lengths, int B, int N,
                       int d, int r, float* S, float* V, int32_t* info, const EigParams& prm, hipStream_t stream);
 
-// W [B][d][r] <- an orthonormal basis of the range of each user's block (rsvd shapes only)
-hipError_t launch_orthonormalize_block(float* W, int B, int d, int r, hipStream_t stream);
-hipError_t launch_rsvd_small(const float* W, const float* Gy, const int32_t* lengths, int B, int N, int d,
+// The small problems of Algorithm 1 (rsvd shapes only), from partial blocks of nsplit chunks per user (xty_partials.h):
+// W [B][d][r] <- an orthonormal basis of the range of each user's H^T Y; `gram` says whether a chunk also holds
+// the blocks of Y^T Y, which launch_rsvd_small needs
+hipError_t launch_orthonormalize_block(const float* partials, int nsplit, bool gram, float* W, int B, int d, int r,
+                                       hipStream_t stream);
+hipError_t launch_rsvd_small(const float* partials, int nsplit, const int32_t* lengths, int B, int N, int d,
                              int r, float* S, float* V, int32_t* info, hipStream_t stream);
 
 // rsvd.hip
 bool rsvd_supported(int d, int r);
 size_t xty_partial_floats(int B, int N, int d, int r);
-hipError_t launch_xty(const void* X, const float* Y, const int32_t* lengths, int B, int N, int d, int r,
-                      bool bf16, float* partials, float* W, float* Gy, hipStream_t stream);
+// partial blocks of H^T Y and Y^T Y (float X)
+hipError_t launch_xty(const float* X, const float* Y, const int32_t* lengths, int B, int N, int d, int r,
+                      float* partials, hipStream_t stream);
+// partial blocks of H^T (H Omega) and, with `gram`, of (H Omega)^T (H Omega) in one pass (bf16 X)
+hipError_t launch_power_pass(const uint16_t* X, const float* Omega, const int32_t* lengths, int B, int N, int d, int r,
+                             bool gram, float* partials, hipStream_t stream);
 
 // project.hip
 hipError_t launch_project(const void* X, const int32_t* lengths, const float* V,
