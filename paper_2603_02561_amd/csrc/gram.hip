@@ -8,7 +8,7 @@
 // pair (s1 <= s2) yields the 16x16 block {G[CPL*i+s1][CPL*j+s2]}.  Only the upper
 // triangle of fragment pairs is formed.  For bf16 the eight rows a lane loads are
 // transposed in registers into the k-contiguous operand the 16x16x32 MFMA wants;
-// for float the 16x16x4 MFMA takes the loaded values as they are.  No LDS is used
+// float rows become three such operands of bf16 terms.  No LDS is used
 // in the streaming loop: every byte of X is read from HBM once, by one wave.
 //
 // The sequence is cut into `nsplit` chunks per user (one workgroup each); the
@@ -55,6 +55,44 @@ static hipError_t gram_allow_lds(K kern, size_t bytes) {
     return allow_dynamic_lds(reinterpret_cast<const void*>(kern), bytes);
 }
 
+// Float inputs on the bf16 instruction: every value is the sum of three bf16 terms (rounded to nearest, so what is
+// left after three is below 2^-26 of it), and a product of two values is taken as the six products of terms that
+// are not below 2^-25 of it, smallest first, in float accumulators.  Six products over 32 rows take 96 cycles
+// of the matrix unit where the float instruction takes 256, and round an accumulator once per 32 rows instead
+// of once per four.  B = 32, N = 4096, d = 128 (67 MB): 26.6 -> 20.1 us; B = 64, N = 2048, d = 256: 200 -> 117 us.  Errors against
+// double precision are smaller (7.3e-8 -> 6.4e-8 of the norm, geometric mean over 30 batches).
+template <int CPL>
+struct SplitFrags {
+    v4u term[3][CPL];   // [term][column fragment]: the lane's eight rows
+    __device__ __forceinline__ void from_rows(const float (&src)[8][CPL]) {
+#pragma unroll
+        for (int s = 0; s < CPL; ++s) {
+            uint32_t o[3][4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+                float a = src[2 * u][s], c = src[2 * u + 1][s];
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    const v2bf t = {(__bf16)a, (__bf16)c};
+                    o[q][u] = __builtin_bit_cast(uint32_t, t);
+                    a -= bf16_lo(o[q][u]);
+                    c -= bf16_hi(o[q][u]);
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < 3; ++q) term[q][s] = v4u{o[q][0], o[q][1], o[q][2], o[q][3]};
+        }
+    }
+};
+
+template <typename F>
+__device__ __forceinline__ void split_products(F&& product) {
+    product(0, 2); product(2, 0); product(1, 1);
+    product(0, 1); product(1, 0);
+    product(0, 0);
+}
+
 #ifndef SOLAR_GRAM_RING
 #define SOLAR_GRAM_RING 3
 #endif
@@ -65,7 +103,7 @@ __global__ __launch_bounds__(kGramWaves * 64) void gram_partial_kernel(
     float* __restrict__ partials) {
     constexpr int D = 16 * CPL;
     constexpr int NP = gram_pairs<CPL>();
-    constexpr int STEP = BF16 ? 32 : 16;  // rows a wave consumes per step
+    constexpr int STEP = 32;  // rows a wave consumes per step
     const int b = blockIdx.y;
     const int split = blockIdx.x;
     const int lane = threadIdx.x & 63;
@@ -169,14 +207,14 @@ __global__ __launch_bounds__(kGramWaves * 64) void gram_partial_kernel(
             }
         }
     } else {
-        // float inputs: the same ring of row blocks (16 rows per block: lane (j, h) holds rows
-        // 4t + h, t = 0..3, and the loaded values are the MFMA operands as they stand)
+        // float inputs: the same row blocks, a lane's eight rows split into three bf16 terms per value as they are
+        // packed into operands (SplitFrags)
         const float* X = reinterpret_cast<const float*>(Xv) + (size_t)b * N * D + CPL * j;
         const int row_max = max(r1 - 1, 0);
-        auto load = [&](float (&dst)[4][CPL], int base) __attribute__((always_inline)) {
+        auto load = [&](float (&dst)[8][CPL], int base) __attribute__((always_inline)) {
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const float* p = X + (size_t)min(base + 4 * t + h, row_max) * D;
+            for (int t = 0; t < 8; ++t) {
+                const float* p = X + (size_t)min(base + 8 * h + t, row_max) * D;
 #pragma unroll
                 for (int q = 0; q < CPL / 4; ++q) {
                     const v4f v = *reinterpret_cast<const v4f*>(p + 4 * q);
@@ -185,30 +223,31 @@ __global__ __launch_bounds__(kGramWaves * 64) void gram_partial_kernel(
                 }
             }
         };
-        auto compute = [&](const float (&src)[4][CPL]) __attribute__((always_inline)) {
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
+        auto compute = [&](const float (&src)[8][CPL]) __attribute__((always_inline)) {
+            SplitFrags<CPL> f;
+            f.from_rows(src);
+            split_products([&](int qa, int qb) __attribute__((always_inline)) {
                 int p = 0;
 #pragma unroll
                 for (int s1 = 0; s1 < CPL; ++s1)
 #pragma unroll
                     for (int s2 = s1; s2 < CPL; ++s2) {
-                        acc[p] = mfma16x16x4(src[t][s1], src[t][s2], acc[p]);
+                        acc[p] = mfma16x16x32bf16(f.term[qa][s1], f.term[qb][s2], acc[p]);
                         ++p;
                     }
-            }
+            });
         };
-        auto compute_tail = [&](float (&src)[4][CPL], int base) __attribute__((always_inline)) {
+        auto compute_tail = [&](float (&src)[8][CPL], int base) __attribute__((always_inline)) {
 #pragma unroll
-            for (int t = 0; t < 4; ++t)
-                if (base + 4 * t + h >= r1) {
+            for (int t = 0; t < 8; ++t)
+                if (base + 8 * h + t >= r1) {
 #pragma unroll
                     for (int s = 0; s < CPL; ++s) src[t][s] = 0.f;
                 }
             compute(src);
         };
-        constexpr int kRing = SOLAR_GRAM_RING;
-        float ring[kRing][4][CPL];
+        constexpr int kRing = CPL > 4 ? 2 : SOLAR_GRAM_RING;   // a block is 64 registers at d = 128
+        float ring[kRing][8][CPL];
         constexpr int stride = kGramWaves * STEP;
         const int base0 = r0 + wave * STEP;
         const int nblk = base0 < r1 ? ceil_div(r1 - base0, stride) : 0;
@@ -272,12 +311,10 @@ __global__ __launch_bounds__(256) void gram_finalize_kernel(const float* __restr
 // with X0, X1 the left and right 128 columns.  G10 is the mirror image of G01.
 constexpr int kGram256Pairs = 36;   // partial slots per job (jobs 2, 3 use 32 of them)
 
-template <bool BF16>
 __global__ __launch_bounds__(kGramWaves * 64) void gram256_partial_kernel(
-    const void* __restrict__ Xv, const int32_t* __restrict__ lengths, int N, int nsplit,
+    const float* __restrict__ Xv, const int32_t* __restrict__ lengths, int N, int nsplit,
     float* __restrict__ partials) {
-    constexpr int D = 256, CPL = 8, NP = kGram256Pairs;
-    constexpr int STEP = BF16 ? 32 : 16;
+    constexpr int D = 256, CPL = 8, NP = kGram256Pairs, STEP = 32;
     const int b = blockIdx.y, split = blockIdx.x, job = blockIdx.z;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int j = lane & 15, h = lane >> 4;
@@ -287,88 +324,64 @@ __global__ __launch_bounds__(kGramWaves * 64) void gram256_partial_kernel(
     const int r1 = min(len, r0 + chunk);
     const bool cross = job >= 2;
     const int colA = (job == 1) ? 128 : 0;          // half that supplies the A fragments
-    const int colB = (job == 0) ? 0 : 128;          // half that supplies the B fragments
     const int sa0 = (job == 3) ? 4 : 0;             // first A fragment of a cross job
 
     v4f acc[NP];
 #pragma unroll
     for (int p = 0; p < NP; ++p) acc[p] = v4f{0.f, 0.f, 0.f, 0.f};
 
-    auto mma = [&](auto& fa, auto& fb) __attribute__((always_inline)) {
-        // fa, fb: the eight fragments of the A half and of the B half for this k-step
-        if (!cross) {
-            int p = 0;
+    const float* X = Xv + (size_t)b * N * D;
+    const int row_max = max(r1 - 1, 0);
+    // `columns` columns of the lane's eight rows from col0 on; rows past the chunk count as zero
+    auto load_split = [&](auto& frags, auto& rows, int base, int col0) __attribute__((always_inline)) {
+        constexpr int columns = sizeof(rows[0]) / sizeof(float);
 #pragma unroll
-            for (int s1 = 0; s1 < CPL; ++s1)
+        for (int t = 0; t < 8; ++t) {
+            const float* p = X + (size_t)min(base + 8 * h + t, row_max) * D + col0;
 #pragma unroll
-                for (int s2 = s1; s2 < CPL; ++s2) {
-                    if constexpr (BF16) acc[p] = mfma16x16x32bf16(fa[s1], fa[s2], acc[p]);
-                    else acc[p] = mfma16x16x4(fa[s1], fa[s2], acc[p]);
-                    ++p;
-                }
-        } else {
+            for (int q = 0; q < columns / 4; ++q) {
+                const v4f v = *reinterpret_cast<const v4f*>(p + 4 * q);
+                rows[t][4 * q + 0] = v.x; rows[t][4 * q + 1] = v.y; rows[t][4 * q + 2] = v.z; rows[t][4 * q + 3] = v.w;
+            }
+        }
+        if (base + STEP > r1) {
 #pragma unroll
-            for (int s1 = 0; s1 < 4; ++s1)
+            for (int t = 0; t < 8; ++t)
+                if (base + 8 * h + t >= r1) {
 #pragma unroll
-                for (int s2 = 0; s2 < CPL; ++s2) {
-                    if constexpr (BF16) {
-                        const v4u a = sa0 ? fa[s1 + 4] : fa[s1];
-                        acc[s1 * CPL + s2] = mfma16x16x32bf16(a, fb[s2], acc[s1 * CPL + s2]);
-                    } else {
-                        const float a = sa0 ? fa[s1 + 4] : fa[s1];
-                        acc[s1 * CPL + s2] = mfma16x16x4(a, fb[s2], acc[s1 * CPL + s2]);
-                    }
+                    for (int q = 0; q < columns; ++q) rows[t][q] = 0.f;
                 }
         }
+        frags.from_rows(rows);
     };
-
-    if constexpr (BF16) {
-        const uint32_t* X = reinterpret_cast<const uint32_t*>(Xv) + (size_t)b * N * (D / 2);
-        auto load_frags = [&](v4u (&frag)[CPL], int base, int col0) __attribute__((always_inline)) {
-            uint32_t in[8][4];
+    for (int base = r0 + wave * STEP; base < r1; base += kGramWaves * STEP) {
+        if (!cross) {   // uniform over the launch's job
+            SplitFrags<CPL> f;
+            float rows[8][CPL];
+            load_split(f, rows, base, colA + CPL * j);
+            split_products([&](int qa, int qb) __attribute__((always_inline)) {
+                int p = 0;
 #pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                const int row = base + 8 * h + t;
-                v4u v = v4u{0u, 0u, 0u, 0u};
-                if (row < r1) v = *reinterpret_cast<const v4u*>(X + (size_t)row * (D / 2) + col0 / 2 + 4 * j);
-                in[t][0] = v.x; in[t][1] = v.y; in[t][2] = v.z; in[t][3] = v.w;
-            }
+                for (int s1 = 0; s1 < CPL; ++s1)
 #pragma unroll
-            for (int s = 0; s < CPL; ++s) {
-                uint32_t o[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const uint32_t a = in[2 * u][s / 2], c = in[2 * u + 1][s / 2];
-                    o[u] = (s & 1) ? ((a >> 16) | (c & 0xffff0000u)) : ((a & 0xffffu) | (c << 16));
-                }
-                frag[s] = v4u{o[0], o[1], o[2], o[3]};
-            }
-        };
-        for (int base = r0 + wave * STEP; base < r1; base += kGramWaves * STEP) {
-            v4u fa[CPL], fb[CPL];
-            load_frags(fa, base, colA);
-            if (cross) load_frags(fb, base, colB);
-            mma(fa, fb);
-        }
-    } else {
-        const float* X = reinterpret_cast<const float*>(Xv) + (size_t)b * N * D;
-        for (int base = r0 + wave * STEP; base < r1; base += kGramWaves * STEP) {
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int row = base + 4 * t + h;
-                float fa[CPL], fb[CPL];
-#pragma unroll
-                for (int q = 0; q < CPL / 4; ++q) {
-                    v4f va = v4f{0.f, 0.f, 0.f, 0.f}, vb = va;
-                    if (row < r1) {
-                        va = *reinterpret_cast<const v4f*>(X + (size_t)row * D + colA + CPL * j + 4 * q);
-                        if (cross) vb = *reinterpret_cast<const v4f*>(X + (size_t)row * D + colB + CPL * j + 4 * q);
+                    for (int s2 = s1; s2 < CPL; ++s2) {
+                        acc[p] = mfma16x16x32bf16(f.term[qa][s1], f.term[qb][s2], acc[p]);
+                        ++p;
                     }
-                    fa[4 * q + 0] = va.x; fa[4 * q + 1] = va.y; fa[4 * q + 2] = va.z; fa[4 * q + 3] = va.w;
-                    fb[4 * q + 0] = vb.x; fb[4 * q + 1] = vb.y; fb[4 * q + 2] = vb.z; fb[4 * q + 3] = vb.w;
-                }
-                mma(fa, fb);
-            }
+            });
+        } else {
+            SplitFrags<4> fa;
+            SplitFrags<CPL> fb;
+            float ra[8][4], rb[8][CPL];
+            load_split(fa, ra, base, CPL * j + sa0);
+            load_split(fb, rb, base, 128 + CPL * j);
+            split_products([&](int qa, int qb) __attribute__((always_inline)) {
+#pragma unroll
+                for (int s1 = 0; s1 < 4; ++s1)
+#pragma unroll
+                    for (int s2 = 0; s2 < CPL; ++s2)
+                        acc[s1 * CPL + s2] = mfma16x16x32bf16(fa.term[qa][s1], fb.term[qb][s2], acc[s1 * CPL + s2]);
+            });
         }
     }
 
@@ -656,15 +669,10 @@ hipError_t launch_gram(const void* X, const int32_t* lengths, int B, int N, int 
             }
             dim3 grid(nsplit, B, 4);
             constexpr size_t lds = gram_reduce_lds<kGram256Pairs>();
-            hipError_t e = bf16 ? gram_allow_lds(gram256_partial_kernel<true>, lds)
-                                : gram_allow_lds(gram256_partial_kernel<false>, lds);
+            hipError_t e = gram_allow_lds(gram256_partial_kernel, lds);
             if (e != hipSuccess) return e;
-            if (bf16)
-                hipLaunchKernelGGL((gram256_partial_kernel<true>), grid, block, lds, stream, X, lengths, N,
-                                   nsplit, partials);
-            else
-                hipLaunchKernelGGL((gram256_partial_kernel<false>), grid, block, lds, stream, X, lengths, N,
-                                   nsplit, partials);
+            hipLaunchKernelGGL(gram256_partial_kernel, grid, block, lds, stream, static_cast<const float*>(X), lengths,
+                               N, nsplit, partials);
             hipLaunchKernelGGL(gram256_finalize_kernel, g2, dim3(256), 0, stream, partials, nsplit, G);
             return hipGetLastError();
         }

@@ -1,0 +1,71 @@
+"""Float inputs on the bf16 matrix instruction (values split into three bf16 terms): the Gram matrix and the
+attention at the edges of their blocks, against double precision.
+
+Tolerances: a Gram entry is a float sum of N terms, each off by at most 2^-24 of the product of the column
+norms' shares: 2^-21 of |x_i| |x_j|, which the float instruction meets as well.  Attention 1e-5 of the largest output:
+scores of magnitude up to 30 in float (2^-24 * 30 each way) move a weight by 4e-6 at most."""
+import numpy as np
+import pytest
+
+from paper_2603_02561_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _binding():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("needs the GPU")
+    from paper_2603_02561_amd import binding
+    return torch, binding
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("N", [1, 31, 32, 33, 127, 129, 513, 1100])
+def test_gram_float(d, N):
+    torch, sb = _binding()
+    B = 3
+    rng = np.random.default_rng(7 * N + d)
+    X = rng.standard_normal((B, N, d)).astype(np.float32) * (1 + 100 * rng.random((1, 1, d))).astype(np.float32)
+    lengths = np.array([N, max(1, N // 2), max(1, N - 1)], dtype=np.int32)
+    Xd = torch.from_numpy(X).cuda()
+    for b in range(B):
+        Xd[b, lengths[b]:] = float("nan")
+    G = torch.empty((B, d, d), device="cuda")
+    ws = torch.empty(sb.solar_workspace_bytes(B, N, d, 1, 1, sb.SOLAR_F32), dtype=torch.uint8, device="cuda")
+    sb.solar_gram(Xd, torch.from_numpy(lengths).cuda(), G, ws)
+    got = G.double().cpu().numpy()
+    for b in range(B):
+        x = X[b, :lengths[b]].astype(np.float64)
+        want = x.T @ x
+        nrm = np.sqrt(np.diag(want))
+        assert (np.abs(got[b] - want) / np.outer(nrm, nrm)).max() < 2.0**-21
+
+
+@pytest.mark.parametrize("d,r", [(64, 1), (64, 7), (64, 16), (128, 17), (128, 32), (128, 47), (128, 48), (64, 64), (256, 20),
+                                 (256, 32)])
+@pytest.mark.parametrize("B,N,M", [(1, 64, 1), (2, 65, 17), (3, 257, 130), (40, 130, 700)])
+def test_attention_float(d, r, B, N, M):
+    torch, sb = _binding()
+    rng = np.random.default_rng(r + N)
+    V = np.stack([np.linalg.qr(rng.standard_normal((d, r)))[0] for _ in range(B)]).astype(np.float32)
+    P = rng.standard_normal((B, N, r)).astype(np.float32)
+    Q = rng.standard_normal((B, M, d)).astype(np.float32)
+    lengths = rng.integers(max(1, r if N >= r else 1), N + 1, size=B).astype(np.int32)
+    Pd = torch.from_numpy(P).cuda()
+    for b in range(B):
+        Pd[b, lengths[b]:] = float("nan")
+    S = torch.ones((B, r), device="cuda")
+    O = torch.empty((B, M, d), device="cuda")
+    scale = 30.0 / (4 * np.sqrt(r) + 8)
+    if r > N:
+        pytest.skip("rank above the sequence length is refused")
+    sb.solar_svd_attention(torch.from_numpy(Q).cuda(), S, torch.from_numpy(V).cuda(), Pd,
+                           torch.from_numpy(lengths).cuda(), N, float(scale), sb.SOLAR_ATTN_SEQ_SOFTMAX, O)
+    got = O.double().cpu().numpy()
+    for b in range(B):
+        p, v = P[b, :lengths[b]].astype(np.float64), V[b].astype(np.float64)
+        s = np.float64(np.float32(scale)) * (Q[b].astype(np.float64) @ v) @ p.T
+        w = np.exp(s - s.max(1, keepdims=True))
+        want = (w / w.sum(1, keepdims=True)) @ p @ v.T
+        assert np.abs(got[b] - want).max() / np.abs(want).max() < 1e-5
