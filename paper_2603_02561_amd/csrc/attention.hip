@@ -7,12 +7,21 @@
 // online softmax (running row maximum and row sum), keeps Z = sum_n w_n P_n in the
 // matrix-unit accumulators and only at the end maps Z / l back to d columns with
 // V^T.  Key and value are the same tile of P, so one LDS tile feeds both products.
-// All three products use the float 16x16x4 MFMA, whose operands are single values
-// per lane; the transposed forms S^T = P Qt^T and Z^T = P^T W^T are used so that a
+// The transposed forms S^T = P Qt^T and Z^T = P^T W^T are used so that a
 // query is a lane (column l%16 of every accumulator): the softmax statistics of a
 // query are then combined over 4 lane groups only, and the accumulator of one
 // product is directly the B operand of the next with no data movement (the
 // contraction index may be enumerated in any order as long as A and B agree).
+//
+// Both products over the sequence keep float accuracy on the bf16 instruction: P, Qt and the weights W are each
+// the sum of three bf16 terms (rounded to nearest: what is left is below 2^-26), and a product is
+// taken as the six products of terms that are not below 2^-25 of it, with float accumulators.  Per 16 queries,
+// 64 rows and 16 ranks that is 384 cycles of the matrix unit where the float 16x16x4 instruction takes 1024; the
+// tile of P is split once, when it is stored to LDS, the weights by the wave that formed them (about a
+// hundred vector instructions per 64 rows).  B = 32, N = 4096, M = 512,
+// d = 128, r = 16: 64.8 -> 61.2 us; B = 64, N = 1500, M = 1200, r = 64: 422 -> 289 us; errors against double precision fall
+// from 7.7e-7 to 5.8e-7 (geometric mean over twelve shapes).
+// The products with V in the prologue and the epilogue stay on the float instruction.
 //
 // attention_tokens_kernel -- the literal r-token form, with or without softmax:
 //   O = softmax_k(scale * Q T^T) T   or   O = scale * (Q T^T) T,   T = diag(S) V^T.
@@ -28,12 +37,43 @@ namespace {
 constexpr int kAttnThreads = 256;
 constexpr int kNT = 64;   // rows of P per tile
 constexpr float kLog2e = 1.4426950408889634f;
+// the six products of terms that count, smallest first
+__device__ constexpr int kTermA[6] = {0, 2, 1, 0, 1, 0}, kTermB[6] = {2, 0, 1, 1, 0, 0};
 
-// Accumulator component (lane group g, register t) of a 16-row output block is
-// bound to rank index g + 4*t of the block instead of 4*g + t: with this choice the
-// four lane groups read four consecutive floats of an LDS row when the accumulator
-// is reused as a B operand, which keeps those reads free of bank conflicts.
-__device__ __forceinline__ int rank_perm(int i) { return (i >> 2) + 4 * (i & 3); }
+// Ranks of a row in a tile image.  Lane group g holds ranks 16*ib + 4*g + t of Qt in component t of block ib, and
+// these are its contraction slots: an instruction takes 32 ranks (blocks 2c and 2c+1, eight slots per lane), so
+// the image of such a chunk lists the quads of four ranks as 0 4 1 5 2 6 3 7 and a lane's eight are one 16-byte
+// read.  An odd last block fills an instruction with two terms of its 16 ranks; it is stored as it is.
+template <int RB>
+__device__ __forceinline__ constexpr int quad_at(int q) {   // where quad q (ranks 4q .. 4q+3) is, in quads
+    return q < 8 * (RB / 2) ? (q & ~7) + 2 * (q & 3) + ((q >> 2) & 1) : q;
+}
+
+// a, b as three bf16 terms each, packed in t[0..2]
+__device__ __forceinline__ void split3_pair(float a, float b, uint32_t (&t)[3]) {
+    typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const v2bf v = {(__bf16)a, (__bf16)b};
+        t[q] = __builtin_bit_cast(uint32_t, v);
+        a -= bf16_lo(t[q]);
+        b -= bf16_hi(t[q]);
+    }
+}
+
+// four rows of one rank out of a row-major image: within 16 lanes, lane i passes the address of row i/4, quad i%4
+// and receives element i of the 16 for rows 0..3
+__device__ __forceinline__ uint2 read_transposed(const uint16_t* p) {
+    typedef short v4s __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) v4s* lds_v4s_ptr;
+    const v4s v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s_ptr)(p));
+    return __builtin_bit_cast(uint2, v);
+}
+
+// V, and two buffers of NS tiles of three images
+constexpr size_t seq_lds(int D, int RB, int NS) {
+    return sizeof(float) * (size_t)D * (16 * RB + 4) + sizeof(uint16_t) * (size_t)2 * NS * 3 * kNT * (16 * RB + 8);
+}
 
 // NS > 1: the workgroup has NS groups of four waves; group sp takes every NS-th tile of the
 // sequence for the same queries and the groups' partial results (reference, row sum, Z) are
@@ -45,10 +85,13 @@ __global__ __launch_bounds__(kAttnThreads * NS) void attention_seq_kernel(
     const int32_t* __restrict__ lengths, int B, int N, int r, int M, float scale, float* __restrict__ O) {
     constexpr int RP = 16 * RB;
     constexpr int LDV = RP + 4;
-    constexpr int LDP = RP + 4;
+    constexpr int LDP = RP + 8;             // bf16 elements per row of an image; reads are free of bank conflicts
+    constexpr int kImg = kNT * LDP;         // one term of a tile
+    constexpr int FC = RB / 2;              // chunks of 32 ranks, then possibly one of 16
+    constexpr bool HALF = RB % 2 != 0;
     extern __shared__ __attribute__((aligned(16))) float smem[];
-    float* Vs = smem;                       // [D][LDV]
-    float* Ps = Vs + D * LDV;               // [2][NS][kNT][LDP]
+    float* Vs = smem;                                               // [D][LDV]
+    uint16_t* Ps = reinterpret_cast<uint16_t*>(Vs + D * LDV);       // [2][NS][3 terms][kNT][LDP]
     constexpr int NTHR = kAttnThreads * NS;
     // Workgroups are dealt to the 8 XCDs round-robin by linear id.  All M-tiles of a user
     // get ids that agree modulo 8, so they share one XCD and its L2 holds that user's P once.
@@ -69,7 +112,7 @@ __global__ __launch_bounds__(kAttnThreads * NS) void attention_seq_kernel(
         Vs[k * LDV + c] = (c < r) ? V[((size_t)b * D + k) * r + c] : 0.f;
     }
     // zero both P tiles once so that the padded rank columns stay zero
-    for (int e = tid; e < 2 * NS * kNT * LDP; e += NTHR) Ps[e] = 0.f;
+    for (int e = tid; e < 2 * NS * 3 * kImg / 8; e += NTHR) reinterpret_cast<v4u*>(Ps)[e] = v4u{0u, 0u, 0u, 0u};
     __syncthreads();
 
     // ---- prologue: Qt^T = V^T Q^T, scaled by scale*log2(e) -------------------------
@@ -95,11 +138,34 @@ __global__ __launch_bounds__(kAttnThreads * NS) void attention_seq_kernel(
                 const float* vrow = Vs + (16 * kk + 4 * g + t) * LDV;
 #pragma unroll
                 for (int ib = 0; ib < RB; ++ib)
-                    qt[qb][ib] = mfma16x16x4(vrow[16 * ib + rank_perm(i16)], q4[t], qt[qb][ib]);
+                    qt[qb][ib] = mfma16x16x4(vrow[16 * ib + i16], q4[t], qt[qb][ib]);
             }
         }
 #pragma unroll
         for (int ib = 0; ib < RB; ++ib) qt[qb][ib] *= scale * kLog2e;
+    }
+
+    // B operands of the score product: three terms of every chunk of 32 ranks; of an odd last block the pairs of terms
+    // that the pairs of P (0, 1), (0, 1) and (0, 2) are multiplied with
+    v4u qf[QB][FC > 0 ? FC : 1][3], qh[QB][3];
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+        uint32_t w[RB][2][3];
+#pragma unroll
+        for (int ib = 0; ib < RB; ++ib)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) split3_pair(qt[qb][ib][2 * e], qt[qb][ib][2 * e + 1], w[ib][e]);
+#pragma unroll
+        for (int c = 0; c < FC; ++c)
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+                qf[qb][c][q] = v4u{w[2 * c][0][q], w[2 * c][1][q], w[2 * c + 1][0][q], w[2 * c + 1][1][q]};
+        if constexpr (HALF) {
+            constexpr int first[3] = {0, 1, 2}, second[3] = {1, 0, 0};
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                qh[qb][k] = v4u{w[RB - 1][0][first[k]], w[RB - 1][1][first[k]], w[RB - 1][0][second[k]], w[RB - 1][1][second[k]]};
+        }
     }
 
     // ---- main loop over tiles of P -------------------------------------------------
@@ -117,7 +183,7 @@ __global__ __launch_bounds__(kAttnThreads * NS) void attention_seq_kernel(
     constexpr int kRows = NS * kNT;                        // rows loaded per step
     // A step is kRows*r consecutive floats of P; a thread moves float4 (r % 4 == 0) or falls
     // back to scalars.
-    auto load_tile = [&](int tile, float* dst) {
+    auto load_tile = [&](int tile, uint16_t* dst) {
         const int n0 = tile * kRows;
         if ((r & 3) == 0) {
             const int quads_per_row = r >> 2;
@@ -125,12 +191,21 @@ __global__ __launch_bounds__(kAttnThreads * NS) void attention_seq_kernel(
                 const int nn = e / quads_per_row, c4 = e % quads_per_row;
                 v4f v = v4f{0.f, 0.f, 0.f, 0.f};
                 if (n0 + nn < len) v = *reinterpret_cast<const v4f*>(Pb + (size_t)(n0 + nn) * r + 4 * c4);
-                *reinterpret_cast<v4f*>(dst + nn * LDP + 4 * c4) = v;
+                uint32_t lo[3], hi[3];
+                split3_pair(v[0], v[1], lo);
+                split3_pair(v[2], v[3], hi);
+                uint16_t* row = dst + (nn / kNT) * (3 * kImg) + (nn % kNT) * LDP + 4 * quad_at<RB>(c4);
+#pragma unroll
+                for (int q = 0; q < 3; ++q) *reinterpret_cast<uint2*>(row + q * kImg) = uint2{lo[q], hi[q]};
             }
         } else {
             for (int e = tid; e < kRows * r; e += NTHR) {
                 const int nn = e / r, c = e % r;
-                dst[nn * LDP + c] = (n0 + nn < len) ? Pb[(size_t)(n0 + nn) * r + c] : 0.f;
+                uint32_t t[3];
+                split3_pair((n0 + nn < len) ? Pb[(size_t)(n0 + nn) * r + c] : 0.f, 0.f, t);
+                uint16_t* at = dst + (nn / kNT) * (3 * kImg) + (nn % kNT) * LDP + 4 * quad_at<RB>(c >> 2) + (c & 3);
+#pragma unroll
+                for (int q = 0; q < 3; ++q) at[q * kImg] = (uint16_t)t[q];
             }
         }
     };
@@ -138,8 +213,8 @@ __global__ __launch_bounds__(kAttnThreads * NS) void attention_seq_kernel(
     __syncthreads();
 
     for (int tile = 0; tile < ntiles; ++tile) {
-        const float* pt = Ps + ((tile & 1) * NS + sp) * (kNT * LDP);
-        if (tile + 1 < ntiles) load_tile(tile + 1, Ps + ((tile + 1) & 1) * (kRows * LDP));
+        const uint16_t* pt = Ps + ((tile & 1) * NS + sp) * (3 * kImg);
+        if (tile + 1 < ntiles) load_tile(tile + 1, Ps + ((tile + 1) & 1) * (NS * 3 * kImg));
         const int n0 = (tile * NS + sp) * kNT;
         if (n0 < len) {   // uniform over the wave: only the last step can leave a group without rows
 
@@ -149,16 +224,30 @@ __global__ __launch_bounds__(kAttnThreads * NS) void attention_seq_kernel(
         for (int nb = 0; nb < kNT / 16; ++nb) {
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) s[qb][nb] = v4f{0.f, 0.f, 0.f, 0.f};
-            const float* prow = pt + (16 * nb + i16) * LDP;
+            const uint16_t* prow = pt + (16 * nb + i16) * LDP;
 #pragma unroll
-            for (int ib = 0; ib < RB; ++ib)
+            for (int c = 0; c < FC; ++c) {
+                v4u a[3];
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const float a = prow[16 * ib + 4 * t + g];
+                for (int q = 0; q < 3; ++q) a[q] = *reinterpret_cast<const v4u*>(prow + q * kImg + 32 * c + 8 * g);
+#pragma unroll
+                for (int k = 0; k < 6; ++k)
 #pragma unroll
                     for (int qb = 0; qb < QB; ++qb)
-                        s[qb][nb] = mfma16x16x4(a, qt[qb][ib][t], s[qb][nb]);
+                        s[qb][nb] = mfma16x16x32bf16(a[kTermA[k]], qf[qb][c][kTermB[k]], s[qb][nb]);
+            }
+            if constexpr (HALF) {
+                uint2 a[3];
+#pragma unroll
+                for (int q = 0; q < 3; ++q) a[q] = *reinterpret_cast<const uint2*>(prow + q * kImg + 32 * FC + 4 * g);
+                const v4u a01 = v4u{a[0].x, a[0].y, a[1].x, a[1].y}, a02 = v4u{a[0].x, a[0].y, a[2].x, a[2].y};
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb) {
+                    s[qb][nb] = mfma16x16x32bf16(a02, qh[qb][2], s[qb][nb]);
+                    s[qb][nb] = mfma16x16x32bf16(a01, qh[qb][1], s[qb][nb]);
+                    s[qb][nb] = mfma16x16x32bf16(a01, qh[qb][0], s[qb][nb]);
                 }
+            }
         }
         // mask rows past the valid length (component t of block nb is row 16*nb + 4*g + t)
         if (n0 + kNT > len) {
@@ -197,20 +286,38 @@ __global__ __launch_bounds__(kAttnThreads * NS) void attention_seq_kernel(
 #pragma unroll
             for (int ib = 0; ib < RB; ++ib) z[qb][ib] *= alpha;
         }
-        // Z^T += P^T W^T : contraction slot g of step (nb, t) is row 16*nb + 4*g + t
+        // Z^T += P^T W^T, 32 rows at a time: slots 0..3 of lane group g are rows 4*g .. +3 of block 2c, slots 4..7
+        // those of block 2c + 1
 #pragma unroll
-        for (int nb = 0; nb < kNT / 16; ++nb)
+        for (int c = 0; c < kNT / 32; ++c) {
+            v4u w[QB][3];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const float* prow = pt + (16 * nb + 4 * g + t) * LDP;
+            for (int qb = 0; qb < QB; ++qb) {
+                uint32_t t[4][3];
 #pragma unroll
-                for (int ib = 0; ib < RB; ++ib) {
-                    const float a = prow[16 * ib + rank_perm(i16)];
+                for (int e = 0; e < 4; ++e)
+                    split3_pair(s[qb][2 * c + e / 2][2 * (e % 2)], s[qb][2 * c + e / 2][2 * (e % 2) + 1], t[e]);
+#pragma unroll
+                for (int q = 0; q < 3; ++q) w[qb][q] = v4u{t[0][q], t[1][q], t[2][q], t[3][q]};
+            }
+            const uint16_t* zrow = pt + (32 * c + 4 * g + (i16 >> 2)) * LDP;
+#pragma unroll
+            for (int ib = 0; ib < RB; ++ib) {
+                v4u a[3];
+                const int col = 4 * quad_at<RB>(4 * ib + (i16 & 3));
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    const uint2 lo = read_transposed(zrow + q * kImg + col);
+                    const uint2 hi = read_transposed(zrow + q * kImg + 16 * LDP + col);
+                    a[q] = v4u{lo.x, lo.y, hi.x, hi.y};
+                }
+#pragma unroll
+                for (int k = 0; k < 6; ++k)
 #pragma unroll
                     for (int qb = 0; qb < QB; ++qb)
-                        z[qb][ib] = mfma16x16x4(a, s[qb][nb][t], z[qb][ib]);
-                }
+                        z[qb][ib] = mfma16x16x32bf16(a[kTermA[k]], w[qb][kTermB[k]], z[qb][ib]);
             }
+        }
         }
         __syncthreads();
     }
@@ -218,7 +325,7 @@ __global__ __launch_bounds__(kAttnThreads * NS) void attention_seq_kernel(
     // ---- merge of the sequence shares (group 0 takes the others in order) -----------------
     if constexpr (NS > 1) {
         constexpr int kState = QB * (4 * RB + 2);   // floats per lane
-        float* st = Ps;                              // [NS-1][4 waves][kState][64 lanes]
+        float* st = reinterpret_cast<float*>(Ps);    // [NS-1][4 waves][kState][64 lanes]
         if (sp > 0) {
             float* mine = st + ((sp - 1) * 4 + wave) * (kState * 64) + lane;
 #pragma unroll
@@ -271,7 +378,7 @@ __global__ __launch_bounds__(kAttnThreads * NS) void attention_seq_kernel(
             for (int ib = 0; ib < RB; ++ib)
 #pragma unroll
                 for (int t = 0; t < 4; ++t)
-                    o = mfma16x16x4(vrow[16 * ib + 4 * t + g], z[qb][ib][t], o);
+                    o = mfma16x16x4(vrow[16 * ib + 4 * g + t], z[qb][ib][t], o);
             if (m < M) *reinterpret_cast<v4f*>(O + ((size_t)b * M + m) * D + 16 * cb + 4 * g) = o;
         }
     }
@@ -340,8 +447,7 @@ template <int D, int RB, int QB, int NS>
 static hipError_t launch_seq_q(const void* Q, const float* V, const float* P,
                                const int32_t* lengths, int B, int N, int r, int M, float scale,
                                bool bf16, float* O, hipStream_t stream) {
-    constexpr int RP = 16 * RB;
-    const size_t lds = sizeof(float) * ((size_t)D * (RP + 4) + 2 * NS * kNT * (RP + 4));
+    constexpr size_t lds = seq_lds(D, RB, NS);
     dim3 grid(ceil_div(M, 4 * QB * 16) * 8 * ceil_div(B, 8)), block(kAttnThreads * NS);
     if (bf16) {
         auto kern = attention_seq_kernel<D, RB, true, QB, NS>;
@@ -371,8 +477,7 @@ static hipError_t launch_seq_n(const void* Q, const float* V, const float* P,
     // registers each, which that variant does not fit; nor does it fit 256 at d = 256, r > 48)
     constexpr int kMaxNs = QB == 1 ? 4 : ((D == 256 && RB == 4) ? 1 : 2);
     if (ns > kMaxNs) ns = kMaxNs;
-    constexpr size_t row = sizeof(float) * (16 * RB + 4);
-    while (ns > 1 && D * row + 2 * ns * kNT * row > 150 * 1024) ns /= 2;
+    while (ns > 1 && seq_lds(D, RB, ns) > 160 * 1024) ns /= 2;
     while (ns > 1 && N <= (ns / 2) * kNT) ns /= 2;   // no more groups than tiles
     if constexpr (kMaxNs >= 4) {
         if (ns == 4) return launch_seq_q<D, RB, QB, 4>(Q, V, P, lengths, B, N, r, M, scale, bf16, O, stream);
