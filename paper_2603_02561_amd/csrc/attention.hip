@@ -19,7 +19,7 @@
 // 64 rows and 16 ranks that is 384 cycles of the matrix unit where the float 16x16x4 instruction takes 1024; the
 // tile of P is split once, when it is stored to LDS, the weights by the wave that formed them (about a
 // hundred vector instructions per 64 rows).  B = 32, N = 4096, M = 512,
-// d = 128, r = 16: 64.8 -> 61.2 us; B = 64, N = 1500, M = 1200, r = 64: 422 -> 289 us; errors against double precision fall
+// d = 128, r = 16: 64.8 -> 61.2 us, 58.2 with the loads two steps ahead; B = 64, N = 1500, M = 1200, r = 64: 422 -> 289 -> 274; errors against double precision fall
 // from 7.7e-7 to 5.8e-7 (geometric mean over twelve shapes).
 // The products with V in the prologue and the epilogue stay on the float instruction.
 //
@@ -34,8 +34,6 @@ namespace solar {
 
 namespace {
 
-constexpr int kAttnThreads = 256;
-constexpr int kNT = 64;   // rows of P per tile
 constexpr float kLog2e = 1.4426950408889634f;
 // the six products of terms that count, smallest first
 __device__ constexpr int kTermA[6] = {0, 2, 1, 0, 1, 0}, kTermB[6] = {2, 0, 1, 1, 0, 0};
@@ -70,49 +68,49 @@ __device__ __forceinline__ uint2 read_transposed(const uint16_t* p) {
     return __builtin_bit_cast(uint2, v);
 }
 
-// V, and two buffers of NS tiles of three images
-constexpr size_t seq_lds(int D, int RB, int NS) {
-    return sizeof(float) * (size_t)D * (16 * RB + 4) + sizeof(uint16_t) * (size_t)2 * NS * 3 * kNT * (16 * RB + 8);
+// V, and two buffers of NS tiles of three images of NT rows
+constexpr size_t seq_lds(int D, int RB, int NS, int NT) {
+    return sizeof(float) * (size_t)D * (16 * RB + 4) + sizeof(uint16_t) * (size_t)2 * NS * 3 * NT * (16 * RB + 8);
 }
 
-// NS > 1: the workgroup has NS groups of four waves; group sp takes every NS-th tile of the
-// sequence for the same queries and the groups' partial results (reference, row sum, Z) are
-// merged in a fixed order at the end.  It gives a small batch, whose workgroups do not fill the
-// GPU's wave slots, NS independent chains of products and exponentials per SIMD.
-template <int D, int RB, bool BF16, int QB, int NS>
-__global__ __launch_bounds__(kAttnThreads * NS) void attention_seq_kernel(
+// The waves of a workgroup are NS groups of QG.  The waves of a group have queries of their own (QB blocks of 16 each);
+// group sp takes every NS-th tile of NT rows of the sequence for the same queries, and the groups'
+// partial results (reference, row sum, Z) are merged in a fixed order at the end.  NS > 1 gives a small
+// batch, whose workgroups do not fill the GPU's wave slots, NS independent chains of products and
+// exponentials per SIMD; QG = 1 gives a single request four times the workgroups.
+template <int D, int RB, bool BF16, int QB, int NS, int QG, int NT>
+__global__ __launch_bounds__(64 * QG * NS) void attention_seq_kernel(
     const void* __restrict__ Qv, const float* __restrict__ V, const float* __restrict__ P,
     const int32_t* __restrict__ lengths, int B, int N, int r, int M, float scale, float* __restrict__ O) {
     constexpr int RP = 16 * RB;
     constexpr int LDV = RP + 4;
     constexpr int LDP = RP + 8;             // bf16 elements per row of an image; reads are free of bank conflicts
-    constexpr int kImg = kNT * LDP;         // one term of a tile
+    constexpr int kImg = NT * LDP;         // one term of a tile
     constexpr int FC = RB / 2;              // chunks of 32 ranks, then possibly one of 16
     constexpr bool HALF = RB % 2 != 0;
     extern __shared__ __attribute__((aligned(16))) float smem[];
     float* Vs = smem;                                               // [D][LDV]
-    uint16_t* Ps = reinterpret_cast<uint16_t*>(Vs + D * LDV);       // [2][NS][3 terms][kNT][LDP]
-    constexpr int NTHR = kAttnThreads * NS;
+    uint16_t* Ps = reinterpret_cast<uint16_t*>(Vs + D * LDV);       // [2][NS][3 terms][NT][LDP]
+    constexpr int NTHR = 64 * QG * NS;
     // Workgroups are dealt to the 8 XCDs round-robin by linear id.  All M-tiles of a user
     // get ids that agree modulo 8, so they share one XCD and its L2 holds that user's P once.
-    const int mtiles = ceil_div(M, 4 * QB * 16);
-    const int slot = blockIdx.x >> 3;
-    const int b = (slot / mtiles) * 8 + (blockIdx.x & 7);
+    const int mtiles = ceil_div(M, QG * QB * 16);
+    // Fewer than eight users take consecutive ids, so that no XCD idles, and every XCD reads its own copy.
+    const int slot = B < 8 ? (int)blockIdx.x : (int)(blockIdx.x >> 3);
+    const int b = B < 8 ? slot / mtiles : (slot / mtiles) * 8 + (int)(blockIdx.x & 7);
     if (b >= B) return;   // uniform over the workgroup
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = (tid >> 6) & 3;        // query group of the wave
-    const int sp = tid >> 8;                // its share of the sequence (0 when NS == 1)
+    const int wave = (tid >> 6) % QG;       // queries of the wave
+    const int sp = (tid >> 6) / QG;         // its share of the sequence (0 when NS == 1)
     const int i16 = lane & 15, g = lane >> 4;
     const int len = user_len(lengths, b, N);
-    const int m_wave = (slot % mtiles) * (4 * QB * 16) + wave * (QB * 16);
+    const int m_wave = (slot % mtiles) * (QG * QB * 16) + wave * (QB * 16);
     const float* Pb = P + (size_t)b * N * r;
 
     for (int e = tid; e < D * RP; e += NTHR) {
         const int k = e / RP, c = e % RP;
         Vs[k * LDV + c] = (c < r) ? V[((size_t)b * D + k) * r + c] : 0.f;
     }
-    // zero both P tiles once so that the padded rank columns stay zero
-    for (int e = tid; e < 2 * NS * 3 * kImg / 8; e += NTHR) reinterpret_cast<v4u*>(Ps)[e] = v4u{0u, 0u, 0u, 0u};
     __syncthreads();
 
     // ---- prologue: Qt^T = V^T Q^T, scaled by scale*log2(e) -------------------------
@@ -179,49 +177,59 @@ __global__ __launch_bounds__(kAttnThreads * NS) void attention_seq_kernel(
         for (int ib = 0; ib < RB; ++ib) z[qb][ib] = v4f{0.f, 0.f, 0.f, 0.f};
     }
 
-    const int ntiles = ceil_div(ceil_div(len, kNT), NS);   // steps of NS tiles
-    constexpr int kRows = NS * kNT;                        // rows loaded per step
-    // A step is kRows*r consecutive floats of P; a thread moves float4 (r % 4 == 0) or falls
-    // back to scalars.
-    auto load_tile = [&](int tile, uint16_t* dst) {
-        const int n0 = tile * kRows;
-        if ((r & 3) == 0) {
-            const int quads_per_row = r >> 2;
-            for (int e = tid; e < kRows * quads_per_row; e += NTHR) {
-                const int nn = e / quads_per_row, c4 = e % quads_per_row;
-                v4f v = v4f{0.f, 0.f, 0.f, 0.f};
-                if (n0 + nn < len) v = *reinterpret_cast<const v4f*>(Pb + (size_t)(n0 + nn) * r + 4 * c4);
-                uint32_t lo[3], hi[3];
-                split3_pair(v[0], v[1], lo);
-                split3_pair(v[2], v[3], hi);
-                uint16_t* row = dst + (nn / kNT) * (3 * kImg) + (nn % kNT) * LDP + 4 * quad_at<RB>(c4);
+    const int ntiles = ceil_div(ceil_div(len, NT), NS);   // steps of NS tiles
+    constexpr int kRows = NS * NT;                        // rows loaded per step
+    // A thread moves kItems quads of ranks per step; row and quad follow from compile-time divisors.  The loads of a
+    // step are issued two steps ahead and stay in registers while a tile is multiplied: rows are clamped to the last
+    // valid one instead of being predicated, and count as zero when they are split and stored.
+    constexpr int kQuads = 4 * RB, kItems = kRows * kQuads / NTHR;
+    static_assert(kItems * NTHR == kRows * kQuads, "whole items per thread");
+    v4f st[kItems];
+    auto fetch = [&](int tile) __attribute__((always_inline)) {
 #pragma unroll
-                for (int q = 0; q < 3; ++q) *reinterpret_cast<uint2*>(row + q * kImg) = uint2{lo[q], hi[q]};
-            }
-        } else {
-            for (int e = tid; e < kRows * r; e += NTHR) {
-                const int nn = e / r, c = e % r;
-                uint32_t t[3];
-                split3_pair((n0 + nn < len) ? Pb[(size_t)(n0 + nn) * r + c] : 0.f, 0.f, t);
-                uint16_t* at = dst + (nn / kNT) * (3 * kImg) + (nn % kNT) * LDP + 4 * quad_at<RB>(c >> 2) + (c & 3);
+        for (int i = 0; i < kItems; ++i) {
+            const int e = tid + i * NTHR, nn = e / kQuads, c0 = 4 * (e % kQuads);
+            const float* row = Pb + (size_t)min(tile * kRows + nn, len - 1) * r;
+            if ((r & 3) == 0) {   // uniform: rows of 16-byte multiples
+                st[i] = *reinterpret_cast<const v4f*>(row + min(c0, r - 4));
+            } else {
 #pragma unroll
-                for (int q = 0; q < 3; ++q) at[q * kImg] = (uint16_t)t[q];
+                for (int t = 0; t < 4; ++t) st[i][t] = row[min(c0 + t, r - 1)];
             }
         }
     };
-    if (ntiles > 0) load_tile(0, Ps);
+    auto commit = [&](int tile, uint16_t* dst) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < kItems; ++i) {
+            const int e = tid + i * NTHR, nn = e / kQuads, c4 = e % kQuads;
+            const bool on = tile * kRows + nn < len;
+            v4f v;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) v[t] = on && 4 * c4 + t < r ? st[i][t] : 0.f;
+            uint32_t lo[3], hi[3];
+            split3_pair(v[0], v[1], lo);
+            split3_pair(v[2], v[3], hi);
+            uint16_t* at = dst + (nn / NT) * (3 * kImg) + (nn % NT) * LDP + 4 * quad_at<RB>(c4);
+#pragma unroll
+            for (int q = 0; q < 3; ++q) *reinterpret_cast<uint2*>(at + q * kImg) = uint2{lo[q], hi[q]};
+        }
+    };
+    if (ntiles > 0) {
+        fetch(0);
+        commit(0, Ps);
+        fetch(1);
+    }
     __syncthreads();
 
     for (int tile = 0; tile < ntiles; ++tile) {
         const uint16_t* pt = Ps + ((tile & 1) * NS + sp) * (3 * kImg);
-        if (tile + 1 < ntiles) load_tile(tile + 1, Ps + ((tile + 1) & 1) * (NS * 3 * kImg));
-        const int n0 = (tile * NS + sp) * kNT;
+        const int n0 = (tile * NS + sp) * NT;
         if (n0 < len) {   // uniform over the wave: only the last step can leave a group without rows
 
-        // scores S^T[n][m] for the 4 blocks of 16 rows
-        v4f s[QB][kNT / 16];
+        // scores S^T[n][m] for the blocks of 16 rows
+        v4f s[QB][NT / 16];
 #pragma unroll
-        for (int nb = 0; nb < kNT / 16; ++nb) {
+        for (int nb = 0; nb < NT / 16; ++nb) {
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) s[qb][nb] = v4f{0.f, 0.f, 0.f, 0.f};
             const uint16_t* prow = pt + (16 * nb + i16) * LDP;
@@ -250,9 +258,9 @@ __global__ __launch_bounds__(kAttnThreads * NS) void attention_seq_kernel(
             }
         }
         // mask rows past the valid length (component t of block nb is row 16*nb + 4*g + t)
-        if (n0 + kNT > len) {
+        if (n0 + NT > len) {
 #pragma unroll
-            for (int nb = 0; nb < kNT / 16; ++nb)
+            for (int nb = 0; nb < NT / 16; ++nb)
 #pragma unroll
                 for (int t = 0; t < 4; ++t)
                     if (n0 + 16 * nb + 4 * g + t >= len) {
@@ -265,7 +273,7 @@ __global__ __launch_bounds__(kAttnThreads * NS) void attention_seq_kernel(
         for (int qb = 0; qb < QB; ++qb) {
             float mt = -INFINITY;
 #pragma unroll
-            for (int nb = 0; nb < kNT / 16; ++nb)
+            for (int nb = 0; nb < NT / 16; ++nb)
 #pragma unroll
                 for (int t = 0; t < 4; ++t) mt = fmaxf(mt, s[qb][nb][t]);
             mt = wave_xor_max(mt, 16);
@@ -275,7 +283,7 @@ __global__ __launch_bounds__(kAttnThreads * NS) void attention_seq_kernel(
             mrun[qb] = mnew;
             float lsum = 0.f;
 #pragma unroll
-            for (int nb = 0; nb < kNT / 16; ++nb)
+            for (int nb = 0; nb < NT / 16; ++nb)
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
                     const float w = __builtin_amdgcn_exp2f(s[qb][nb][t] - mnew);
@@ -289,7 +297,7 @@ __global__ __launch_bounds__(kAttnThreads * NS) void attention_seq_kernel(
         // Z^T += P^T W^T, 32 rows at a time: slots 0..3 of lane group g are rows 4*g .. +3 of block 2c, slots 4..7
         // those of block 2c + 1
 #pragma unroll
-        for (int c = 0; c < kNT / 32; ++c) {
+        for (int c = 0; c < NT / 32; ++c) {
             v4u w[QB][3];
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) {
@@ -319,15 +327,17 @@ __global__ __launch_bounds__(kAttnThreads * NS) void attention_seq_kernel(
             }
         }
         }
+        commit(tile + 1, Ps + ((tile + 1) & 1) * (NS * 3 * kImg));
+        fetch(tile + 2);
         __syncthreads();
     }
 
     // ---- merge of the sequence shares (group 0 takes the others in order) -----------------
     if constexpr (NS > 1) {
         constexpr int kState = QB * (4 * RB + 2);   // floats per lane
-        float* st = reinterpret_cast<float*>(Ps);    // [NS-1][4 waves][kState][64 lanes]
+        float* st = reinterpret_cast<float*>(Ps);    // [NS-1][QG waves][kState][64 lanes]
         if (sp > 0) {
-            float* mine = st + ((sp - 1) * 4 + wave) * (kState * 64) + lane;
+            float* mine = st + ((sp - 1) * QG + wave) * (kState * 64) + lane;
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) {
                 mine[(qb * (4 * RB + 2) + 0) * 64] = mrun[qb];
@@ -341,7 +351,7 @@ __global__ __launch_bounds__(kAttnThreads * NS) void attention_seq_kernel(
         __syncthreads();
         if (sp > 0) return;
         for (int o = 0; o < NS - 1; ++o) {
-            const float* other = st + (o * 4 + wave) * (kState * 64) + lane;
+            const float* other = st + (o * QG + wave) * (kState * 64) + lane;
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) {
                 const float mo = other[(qb * (4 * RB + 2) + 0) * 64];
@@ -443,23 +453,16 @@ __global__ __launch_bounds__(256) void attention_tokens_kernel(
 
 }  // namespace
 
-template <int D, int RB, int QB, int NS>
+template <int D, int RB, int QB, int NS, int QG = 4, int NT = 64>
 static hipError_t launch_seq_q(const void* Q, const float* V, const float* P,
                                const int32_t* lengths, int B, int N, int r, int M, float scale,
                                bool bf16, float* O, hipStream_t stream) {
-    constexpr size_t lds = seq_lds(D, RB, NS);
-    dim3 grid(ceil_div(M, 4 * QB * 16) * 8 * ceil_div(B, 8)), block(kAttnThreads * NS);
-    if (bf16) {
-        auto kern = attention_seq_kernel<D, RB, true, QB, NS>;
-        hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, grid, block, lds, stream, Q, V, P, lengths, B, N, r, M, scale, O);
-    } else {
-        auto kern = attention_seq_kernel<D, RB, false, QB, NS>;
-        hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, grid, block, lds, stream, Q, V, P, lengths, B, N, r, M, scale, O);
-    }
+    constexpr size_t lds = seq_lds(D, RB, NS, NT);
+    dim3 grid(ceil_div(M, QG * QB * 16) * (B < 8 ? B : 8 * ceil_div(B, 8))), block(64 * QG * NS);
+    auto kern = bf16 ? attention_seq_kernel<D, RB, true, QB, NS, QG, NT> : attention_seq_kernel<D, RB, false, QB, NS, QG, NT>;
+    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, grid, block, lds, stream, Q, V, P, lengths, B, N, r, M, scale, O);
     return hipGetLastError();
 }
 
@@ -477,21 +480,28 @@ static hipError_t launch_seq_n(const void* Q, const float* V, const float* P,
     // registers each, which that variant does not fit; nor does it fit 256 at d = 256, r > 48)
     constexpr int kMaxNs = QB == 1 ? 4 : ((D == 256 && RB == 4) ? 1 : 2);
     if (ns > kMaxNs) ns = kMaxNs;
-    while (ns > 1 && seq_lds(D, RB, ns) > 160 * 1024) ns /= 2;
-    while (ns > 1 && N <= (ns / 2) * kNT) ns /= 2;   // no more groups than tiles
-    if constexpr (kMaxNs >= 4) {
+    while (ns > 1 && seq_lds(D, RB, ns, 64) > 160 * 1024) ns /= 2;
+    while (ns > 1 && N <= (ns / 2) * 64) ns /= 2;   // no more groups than tiles
+    if constexpr (kMaxNs >= 4 && seq_lds(D, RB, 4, 64) <= 160 * 1024) {
         if (ns == 4) return launch_seq_q<D, RB, QB, 4>(Q, V, P, lengths, B, N, r, M, scale, bf16, O, stream);
     }
-    if constexpr (kMaxNs >= 2) {
+    if constexpr (kMaxNs >= 2 && seq_lds(D, RB, 2, 64) <= 160 * 1024) {
         if (ns == 2) return launch_seq_q<D, RB, QB, 2>(Q, V, P, lengths, B, N, r, M, scale, bf16, O, stream);
     }
     return launch_seq_q<D, RB, QB, 1>(Q, V, P, lengths, B, N, r, M, scale, bf16, O, stream);
 }
 
+// Up to 64 workgroups of 64 queries leave three compute units of four idle: sixteen queries to a workgroup then, and
+// its eight waves (four where the images of eight do not fit LDS) share out the sequence in tiles of 32 rows.
+// One user, N = 10000, M = 1000, d = 128, r = 21: 189 -> 85 us (with the loads two steps ahead); two users, N = 20000,
+// M = 200, d = 64, r = 30: 419 -> 158; one user, N = 1024, M = 64, d = 64, r = 8: 16 -> 10.
 template <int D, int RB>
 static hipError_t launch_seq_t(const void* Q, const float* V, const float* P,
                                const int32_t* lengths, int B, int N, int r, int M, float scale,
                                bool bf16, float* O, hipStream_t stream) {
+    constexpr int kShares = seq_lds(D, RB, 8, 32) <= 160 * 1024 ? 8 : 4;
+    if ((long long)B * ceil_div(M, 64) <= 64 && N > 32 * kShares)
+        return launch_seq_q<D, RB, 1, kShares, 1, 32>(Q, V, P, lengths, B, N, r, M, scale, bf16, O, stream);
     if ((long long)B * ceil_div(M, 128) < 256)
         return launch_seq_n<D, RB, 1>(Q, V, P, lengths, B, N, r, M, scale, bf16, O, stream);
     return launch_seq_n<D, RB, 2>(Q, V, P, lengths, B, N, r, M, scale, bf16, O, stream);
