@@ -272,8 +272,9 @@ solar_status solar_gram(const void* X, const int32_t* lengths, int B, int N, int
  * through that range, so the result is the printed algorithm's; in float arithmetic the
  * printed form loses the trailing directions (cond(X Omega) grows by (s_1/s_r)^2 per power
  * step), this one does not.  The QR step is carried by the Cholesky factor of Y^T Y (Q is
- * never formed: Q^T X = R^-T (X^T Y)^T), the small SVD by a one-sided Jacobi.  X is read
- * 2*n_iter + 2 times (plus once for P).
+ * never formed: Q^T X = R^-T (X^T Y)^T), the small SVD by the eigenpairs of its Gram matrix in
+ * double precision (one-sided Jacobi where those are too close).  X is read n_iter + 1 times in bf16,
+ * 2*n_iter + 2 times in float (plus once for P).
  *   Omega    in  [B,d,r] float   the Gaussian start blocks (the caller draws them)
  *   n_iter   power iterations, >= 0
  *   S, V, P, info   as for solar_svd_factorize; info[b] = -2 when Y^T Y is not numerically
