@@ -73,8 +73,8 @@ const char* solar_status_string(solar_status s);
  * Verdict over the per-user `info` array of a factorization, after the caller has waited for
  * the stream and copied `info` to HOST memory: SOLAR_OK if every entry is 0,
  * SOLAR_ERR_INVALID_ARG if any entry is negative (a bad length), else
- * SOLAR_ERR_NOT_CONVERGED (some user's eigen-iteration reached its cap; that user's factors
- * are the best available and finite).
+ * SOLAR_ERR_NOT_CONVERGED (some user's eigen-iteration reached its cap, and that user's factors
+ * are the best available and finite; or X^T X of a user is not finite, and its factors are NaN).
  */
 solar_status solar_info_status(const int32_t* info_host, int B);
 
@@ -124,8 +124,10 @@ size_t solar_workspace_bytes(int B, int N, int d, int r, int M, solar_dtype t);
  *                        NULL if only modes 1 and 2 or solar_svd_attention_from_x
  *                        will be used
  *   info     out [B] or NULL: 0 converged; k > 0 iteration cap reached after k
- *                        steps (results are the best available); -1 bad length
- *                        (not in [r, N]; that user's outputs are zero)
+ *                        steps (results are the best available), or S and V are NaN
+ *                        because X^T X over that user's valid rows is not finite (NaN or
+ *                        Inf in a valid row, or squares that overflow a float); -1 bad
+ *                        length (not in [r, N]; that user's outputs are zero)
  */
 solar_status solar_svd_factorize(const void* X, const int32_t* lengths, int B, int N, int d,
                                  int r, solar_dtype t, float* S, float* V, float* P,

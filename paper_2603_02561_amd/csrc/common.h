@@ -16,6 +16,9 @@ constexpr int kWave = 64;
 
 __host__ __device__ inline int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
+// neither infinite nor NaN
+__device__ __forceinline__ bool finite32(float v) { return fabsf(v) <= 3.402823466e+38f; }
+
 // bf16 bit pattern -> float (exact).
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }

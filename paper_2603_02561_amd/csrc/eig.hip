@@ -663,7 +663,10 @@ __global__ __launch_bounds__(kEigThreads) void eig_topr_kernel(
         }
     }
     if (tid == 0) { sh_bits = 0; sh_bits2 = 0; }
+    // G to LDS where it fits; true if this thread met an entry that is not finite.  One that is not finite shows on
+    // the diagonal too (|G_ij|^2 <= G_ii G_jj), which is what is looked at where G stays in memory.
     auto stage = [&]() __attribute__((always_inline)) {
+    bool bad = false;
     if constexpr (C::GLDS) {
         if (partials) {
             // G from the split-N partial blocks of the Gram kernel: per chunk and fragment pair
@@ -706,6 +709,7 @@ __global__ __launch_bounds__(kEigThreads) void eig_topr_kernel(
 #pragma unroll
                     for (int t = 0; t < 4; ++t) {
                         const int a = CPL * (4 * (ln >> 4) + t) + s1;
+                        bad |= !finite32(acc[i][t]);
                         Gs[a * C::GS + c] = acc[i][t];
                         if (s1 < s2) Gs[c * C::GS + a] = acc[i][t];
                     }
@@ -714,18 +718,31 @@ __global__ __launch_bounds__(kEigThreads) void eig_topr_kernel(
         } else {
             for (int e = tid; e < D * D / 4; e += kEigThreads) {
                 const int i = e / (D / 4), c4 = e % (D / 4);
-                *reinterpret_cast<v4f*>(Gs + i * C::GS + 4 * c4) =
-                    *reinterpret_cast<const v4f*>(Gb + (size_t)i * D + 4 * c4);
+                const v4f v = *reinterpret_cast<const v4f*>(Gb + (size_t)i * D + 4 * c4);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) bad |= !finite32(v[t]);
+                *reinterpret_cast<v4f*>(Gs + i * C::GS + 4 * c4) = v;
             }
         }
+    } else {
+        for (int e = tid; e < D; e += kEigThreads) bad |= !finite32(Gb[(size_t)e * D + e]);
     }
+    return bad;
     };
-    stage();
+    // A G with entries that are not finite has no factors.  Neither solver would say so: norms and maxima drop NaN,
+    // so one takes G for zero and the other for converged.
+    auto not_finite = [&]() __attribute__((always_inline)) {
+        const float nan = __int_as_float(0x7fc00000);
+        for (int e = tid; e < D * r; e += kEigThreads) V[(size_t)b * D * r + e] = nan;
+        for (int e = tid; e < r; e += kEigThreads) S[(size_t)b * r + e] = nan;
+        if (tid == 0 && info) info[b] = prm.max_iter;
+    };
+    const bool bad = stage();
     // wide blocks; a test that caps the power steps wants to see the iteration
     bool by_ritz = true;
     if constexpr (C::direct) {
         if (prm.direct) {
-            __syncthreads();
+            if (__syncthreads_or(bad)) { not_finite(); return; }
             if (eig_direct<D, L - 8, C::GS>(Gs, reinterpret_cast<double*>(smem), sh_scal, sh_twist, r,
                                             S + (size_t)b * r, V + (size_t)b * D * r)) {
                 if (tid == 0 && info) info[b] = 0;
@@ -743,7 +760,7 @@ __global__ __launch_bounds__(kEigThreads) void eig_topr_kernel(
         Qc[j * LD + i] = (j < L) ? omega_entry(b, j, i) : 0.f;
         Zc[j * LD + i] = 0.f;
     }
-    __syncthreads();
+    if (__syncthreads_or(bad)) { not_finite(); return; }   // uniform
 
     const int col = tid / TC, cu = tid % TC;
     // The iteration alternates cheap and full steps.  After a power step Z = G Q the block is

@@ -74,3 +74,39 @@ def test_zero_matrix(lib):
     for d, r in ((64, 8), (64, 40), (128, 16), (128, 64)):
         info, S, V = factors(lib, np.zeros((1, 100, d), dtype=np.float32), r)
         assert np.all(S == 0.0) and np.all(V == 0.0)
+
+
+@pytest.mark.parametrize("d,r", [(64, 8), (64, 12), (64, 20), (64, 64), (128, 16), (128, 40), (128, 41), (128, 64),
+                                 (256, 16)])
+@pytest.mark.parametrize("what", ["nan", "-nan", "inf", "overflow", "one-column"])
+def test_not_finite(lib, d, r, what):
+    """A user whose Gram matrix is not finite (a NaN or an infinity in a valid row, or finite values whose squares
+    overflow) has no factors: info says so and S, V and what follows from them are NaN, on every route.
+    The users beside it are not touched."""
+    import torch
+    print(f"[case] not finite d={d} r={r} {what}", flush=True)
+    g = np.random.default_rng(d + r)
+    X = np.matmul(g.standard_normal((3, 300, r)), g.standard_normal((3, r, d))).astype(np.float32)
+    if what == "overflow":
+        X[1] *= 1e20
+    else:
+        X[1, 77, d - 1] = {"nan": np.nan, "-nan": -np.float32(np.nan), "inf": np.inf, "one-column": 1e20}[what]
+    Q = g.standard_normal((3, 20, d)).astype(np.float32)
+    db = lib.DeviceBatch(X, Q, None, r, False)
+    db.S.fill_(7.0)
+    db.V.fill_(7.0)
+    db.factorize()
+    db.attention(1.0, 0)
+    torch.cuda.synchronize()
+    info, S, V, O = (t.cpu().numpy() for t in (db.info, db.S, db.V, db.O))
+    assert info[1] > 0 and lib.solar_info_status(db.info) == lib.SOLAR_ERR_NOT_CONVERGED
+    assert np.all(np.isnan(S[1])) and np.all(np.isnan(V[1])) and np.all(np.isnan(O[1]))
+    for b in (0, 2):
+        assert info[b] == 0
+        assert np.all(np.isfinite(S[b])) and np.all(np.isfinite(V[b])) and np.all(np.isfinite(O[b]))
+
+
+def test_zero_matrix_converges(lib):
+    for d, r in ((64, 8), (64, 40), (128, 16), (128, 64), (256, 16)):
+        info, S, V = factors(lib, np.zeros((1, 100, d), dtype=np.float32), r)
+        assert info[0] == 0 and np.all(S == 0.0) and np.all(V == 0.0), (d, r, info)
