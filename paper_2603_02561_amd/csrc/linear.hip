@@ -25,6 +25,10 @@ __device__ __forceinline__ v16f mfma32x32x16bf16(v8bf a, v8bf b, v16f c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+__device__ __forceinline__ v16f mfma32x32x2(float a, float b, v16f c) {
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+
 // x = s[0] + s[1] + s[2] to 24 bits
 __device__ __forceinline__ void split3(const float (&x)[8], v8bf (&s)[3]) {
 #pragma unroll
@@ -74,8 +78,8 @@ __global__ __launch_bounds__(kRowWaves * 64) void rowgemm_kernel(
     };
     int blk = blockIdx.x * kRowWaves + wave;
     if (blk < nblk) load(blk, raw[0]);
+    const float* Wb = W + (size_t)b * w_stride + c0;
     {
-        const float* Wb = W + (size_t)b * w_stride + c0;
         for (int e = tid; e < NC * (D / 8); e += kRowWaves * 64) {
             const int c = e % NC, k8 = e / NC;
             float x[8];
@@ -134,19 +138,59 @@ __global__ __launch_bounds__(kRowWaves * 64) void rowgemm_kernel(
             __builtin_amdgcn_sched_barrier(0);
         }
         // component e is row 8 (e / 4) + 4 h + e % 4 of the block, column i32 of the tile
-        const int row0 = 32 * at + 4 * h;
+        auto store = [&]() __attribute__((always_inline)) {
+            const int row0 = 32 * at + 4 * h;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const int row = row0 + 8 * (e / 4) + e % 4;
-            if (row < rows) {
-                const size_t o = ((size_t)b * rows + row) * D + c0 + i32;
+            for (int e = 0; e < 16; ++e) {
+                const int row = row0 + 8 * (e / 4) + e % 4;
+                if (row < rows) {
+                    const size_t o = ((size_t)b * rows + row) * D + c0 + i32;
 #pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    const float v = scale * acc[t][e];
-                    if constexpr (OUT_BF16) reinterpret_cast<__bf16*>(Out)[o + 32 * t] = (__bf16)v;
-                    else reinterpret_cast<float*>(Out)[o + 32 * t] = v;
+                    for (int t = 0; t < NT; ++t) {
+                        const float v = scale * acc[t][e];
+                        if constexpr (OUT_BF16) reinterpret_cast<__bf16*>(Out)[o + 32 * t] = (__bf16)v;
+                        else reinterpret_cast<float*>(Out)[o + 32 * t] = v;
+                    }
                 }
             }
+        };
+        store();
+        // An infinity, or a value that rounds to one as a bf16 (above 3.39e38), has terms inf, inf - inf and NaN, and
+        // the terms of a product that overflows can cancel to NaN: a block with a sum that is not finite is taken
+        // again on the float instruction.  The look at the sums costs 0.1 us a launch, 1 to 2 % of 64000 rows.
+        constexpr int kChains = 8;   // a zero each, NaN if any sum is not finite
+        float probe[kChains];
+#pragma unroll
+        for (int i = 0; i < kChains; ++i) probe[i] = 0.f;
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) probe[e % kChains] = fmaf(acc[t][e], 0.f, probe[e % kChains]);
+#pragma unroll
+        for (int i = kChains / 2; i; i /= 2)
+#pragma unroll
+            for (int k = 0; k < i; ++k) probe[k] += probe[k + i];
+        if (__builtin_expect(__any(probe[0] != 0.f), 0)) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                uint32_t at_w = (16 * s + 8 * h) * D + i32;
+                asm volatile("" : "+v"(at_w));   // or these loads are taken ahead of the loop over the blocks
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    float a;
+                    if constexpr (IN_BF16) a = (k & 1) ? bf16_hi(r[s][0][k / 2]) : bf16_lo(r[s][0][k / 2]);
+                    else a = __uint_as_float(r[s][k / 4][k % 4]);
+#pragma unroll
+                    for (int t = 0; t < NT; ++t)
+                        acc[t] = mfma32x32x2(a, Wb[at_w + k * D + 32 * t], acc[t]);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            store();
         }
     };
     if constexpr (AHEAD) {

@@ -105,3 +105,53 @@ def test_row_blocks(lib, d, rows, in_bf16, out_bf16):
     size = In.double().norm(dim=1, keepdim=True) * W.double().norm(dim=0, keepdim=True)
     err = ((Out.double() - want).abs() / (size + (want.abs() * 2.0 ** 8 if out_bf16 else 0))).max().item()
     assert err < (2.0 ** -16 if not out_bf16 else 2.0 ** -15)
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("in_bf16", [False, True])
+def test_extreme_rows(lib, d, in_bf16):
+    """Rows with a value at the end of the float range (a mask value), an infinity or a NaN, and a matrix with such
+    values: what comes out is what the sum of float products is, finite where that is finite, and rows
+    beside them are not touched.  Finite outputs to d 2^-24 of the sum of the absolute products."""
+    import torch
+    print(f"[case] extreme rows d={d} {in_bf16}", flush=True)
+    big = torch.finfo(torch.float32).max
+    g = torch.Generator().manual_seed(d)
+    In = torch.randn(70, d, generator=g)
+    W = torch.randn(d, d, generator=g) / (4 * d)
+    W[5] = torch.where(torch.arange(d) % 3 == 0, torch.full((d,), 2.0 ** -9), W[5])   # fewer than three terms
+    In[:, 6] /= 16
+    In[3, 5], In[8, 5], In[9, 5], In[40, 5] = -big, float("inf"), -float("inf"), float("nan")
+    In[41, 5], In[41, 6] = float("inf"), -float("inf")
+    In[69, 5] = 3.4e38
+    In = In.to(torch.bfloat16 if in_bf16 else torch.float32).cuda()
+    W = W.cuda()
+    for matrix in (W, W.clone().index_fill_(0, torch.tensor([6], device="cuda"), -big)):
+        Out = torch.full((70, d), 7.0, device="cuda")
+        lib.solar_apply_weights(In, matrix, Out)
+        torch.cuda.synchronize()
+        want = In.double() @ matrix.double()
+        size = In.double().abs() @ matrix.double().abs()
+        finite = size < 0.5 * big                       # no partial sum overflows
+        assert torch.equal(torch.isnan(want), torch.isnan(Out))
+        assert torch.equal(want[torch.isinf(want)].float(), Out[torch.isinf(want)])
+        assert finite.sum() > 60 * d
+        assert ((Out.double() - want).abs()[finite] <= d * 2.0 ** -24 * size[finite]).all()
+
+
+def test_linear_attention_extreme_query(lib):
+    """A query row with a mask value in linear attention: finite where the float products are."""
+    import torch
+    g = torch.Generator().manual_seed(5)
+    for d in (64, 128, 256):
+        X = torch.randn(2, 50, d, generator=g).cuda() / 64
+        Q = torch.randn(2, 40, d, generator=g).cuda()
+        Q[0, 7, 3] = -torch.finfo(torch.float32).max
+        O = torch.empty(2, 40, d, device="cuda")
+        ws = torch.empty(lib.solar_workspace_bytes(2, 50, d, 1, 40, 0), dtype=torch.uint8, device="cuda")
+        lib.solar_linear_attention(Q, X, None, 1.0, O, ws)
+        torch.cuda.synchronize()
+        G = X.double().transpose(1, 2).contiguous() @ X.double()
+        want, size = Q.double() @ G, Q.double().abs() @ G.abs()
+        assert torch.isfinite(O).all()
+        assert ((O.double() - want).abs() <= (50 + d) * 2.0 ** -24 * size).all()
