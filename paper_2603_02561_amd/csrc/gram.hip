@@ -93,6 +93,34 @@ __device__ __forceinline__ void split_products(F&& product) {
     product(0, 0);
 }
 
+// An infinity, or a value that rounds to one as a bf16 (above 3.39e38), has terms inf, inf - inf and NaN, and the terms of
+// a square that overflows can cancel to NaN.  A wave whose sums are not all finite forms them again on the float
+// instruction (sum_exactly).  Such a value shows on the diagonal: its own square is not finite.
+struct FiniteProbe {
+    v4f zero = v4f{0.f, 0.f, 0.f, 0.f};   // NaN where a value was not finite
+    __device__ __forceinline__ void add(v4f a) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) zero[t] = fmaf(a[t], 0.f, zero[t]);
+    }
+    // some lane's; uniform over the wave
+    __device__ __forceinline__ bool hit() const { return __any((zero[0] + zero[1]) + (zero[2] + zero[3]) != 0.f); }
+};
+
+// rows(row, ok): loads the lane's columns of a row, zeros unless ok; products(): adds the products of a step, which
+// lane group h takes row 4 q + h of.
+template <int STEP, typename Rows, typename Products>
+__device__ __forceinline__ void sum_exactly(int r0, int r1, int wave, int h, Rows&& rows, Products&& products) {
+#pragma unroll 1
+    for (int base = r0 + wave * STEP; base < r1; base += kGramWaves * STEP) {
+#pragma unroll 1
+        for (int q = 0; q < STEP / 4; ++q) {
+            const int row = base + 4 * q + h;
+            rows(min(row, r1 - 1), row < r1);
+            products();
+        }
+    }
+}
+
 #ifndef SOLAR_GRAM_RING
 #define SOLAR_GRAM_RING 3
 #endif
@@ -271,6 +299,27 @@ __global__ __launch_bounds__(kGramWaves * 64) void gram_partial_kernel(
                 compute_tail(ring[k], base0 + (i + k) * stride);
             }
         }
+        FiniteProbe probe;
+#pragma unroll
+        for (int s = 0; s < CPL; ++s) probe.add(acc[s * CPL - (s * (s - 1)) / 2]);
+        if (__builtin_expect(probe.hit(), 0)) {
+#pragma unroll
+            for (int p = 0; p < NP; ++p) acc[p] = v4f{0.f, 0.f, 0.f, 0.f};
+            float x[CPL];
+            sum_exactly<STEP>(r0, r1, wave, h, [&](int row, bool ok) __attribute__((always_inline)) {
+#pragma unroll
+                for (int s = 0; s < CPL; ++s) x[s] = ok ? X[(size_t)row * D + s] : 0.f;
+            }, [&]() __attribute__((always_inline)) {
+                int p = 0;
+#pragma unroll
+                for (int s1 = 0; s1 < CPL; ++s1)
+#pragma unroll
+                    for (int s2 = s1; s2 < CPL; ++s2) {
+                        acc[p] = mfma16x16x4(x[s1], x[s2], acc[p]);
+                        ++p;
+                    }
+            });
+        }
     }
 
     v4f* out = reinterpret_cast<v4f*>(partials) + ((size_t)b * nsplit + split) * (NP * 64);
@@ -383,6 +432,38 @@ __global__ __launch_bounds__(kGramWaves * 64) void gram256_partial_kernel(
                         acc[s1 * CPL + s2] = mfma16x16x32bf16(fa.term[qa][s1], fb.term[qb][s2], acc[s1 * CPL + s2]);
             });
         }
+    }
+    FiniteProbe probe;   // a cross job has no diagonal: all its sums
+#pragma unroll
+    for (int p = 0; p < NP; ++p) probe.add(acc[p]);
+    if (__builtin_expect(probe.hit(), 0)) {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) acc[p] = v4f{0.f, 0.f, 0.f, 0.f};
+        float xa[CPL], xb[CPL];   // a cross job uses four of xa
+        sum_exactly<STEP>(r0, r1, wave, h, [&](int row, bool ok) __attribute__((always_inline)) {
+#pragma unroll
+            for (int s = 0; s < CPL; ++s) {
+                xa[s] = ok && (!cross || s < 4) ? X[(size_t)row * D + colA + sa0 + CPL * j + s] : 0.f;
+                xb[s] = ok && cross ? X[(size_t)row * D + 128 + CPL * j + s] : 0.f;
+            }
+        }, [&]() __attribute__((always_inline)) {
+            if (!cross) {
+                int p = 0;
+#pragma unroll
+                for (int s1 = 0; s1 < CPL; ++s1)
+#pragma unroll
+                    for (int s2 = s1; s2 < CPL; ++s2) {
+                        acc[p] = mfma16x16x4(xa[s1], xa[s2], acc[p]);
+                        ++p;
+                    }
+            } else {
+#pragma unroll
+                for (int s1 = 0; s1 < 4; ++s1)
+#pragma unroll
+                    for (int s2 = 0; s2 < CPL; ++s2)
+                        acc[s1 * CPL + s2] = mfma16x16x4(xa[s1], xb[s2], acc[s1 * CPL + s2]);
+            }
+        });
     }
 
     v4f* out = reinterpret_cast<v4f*>(partials) + (((size_t)b * nsplit + split) * 4 + job) * (NP * 64);

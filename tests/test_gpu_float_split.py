@@ -42,6 +42,36 @@ def test_gram_float(d, N):
         assert (np.abs(got[b] - want) / np.outer(nrm, nrm)).max() < 2.0**-21
 
 
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("N", [40, 700])
+@pytest.mark.parametrize("value", [-3.4028235e38, 3.4e38, float("inf"), -float("inf"), 1e25, float("nan")])
+def test_gram_float_extreme(d, N, value):
+    """One entry of a user at the end of the float range, infinite or NaN, in the first and the last valid row: entries of
+    G are what the sum of float products is (N 2^-24 of the sum of their sizes where that is finite, an infinity of the
+    right sign where it overflows), and the columns and users beside it are not touched."""
+    torch, sb = _binding()
+    print(f"[case] extreme Gram d={d} N={N} {value}", flush=True)
+    rng = np.random.default_rng(N + d)
+    X = (rng.standard_normal((3, N, d)) / 16).astype(np.float32)
+    X[0, 0, d - 3] = value
+    X[1, N - 1, 5] = value
+    G = torch.empty((3, d, d), device="cuda")
+    ws = torch.empty(sb.solar_workspace_bytes(3, N, d, 1, 1, sb.SOLAR_F32), dtype=torch.uint8, device="cuda")
+    sb.solar_gram(torch.from_numpy(X).cuda(), None, G, ws)
+    got = G.double().cpu().numpy()
+    x = X.astype(np.float64)
+    big = float(np.finfo(np.float32).max)
+    for b in range(3):
+        with np.errstate(invalid="ignore"):
+            want, size = x[b].T @ x[b], np.abs(x[b]).T @ np.abs(x[b])
+        assert np.array_equal(np.isnan(got[b]), np.isnan(want))
+        small = size < 0.5 * big
+        assert small.sum() >= (d - 1) ** 2
+        assert (np.abs(got[b] - want)[small] <= N * 2.0**-24 * size[small]).all()
+        over = np.abs(want) > 1.01 * big
+        assert np.array_equal(got[b][over], np.sign(want[over]) * np.inf)
+
+
 @pytest.mark.parametrize("d,r", [(64, 1), (64, 7), (64, 16), (128, 17), (128, 32), (128, 47), (128, 48), (64, 64), (256, 20),
                                  (256, 32)])
 @pytest.mark.parametrize("B,N,M", [(1, 64, 1), (2, 65, 17), (3, 257, 130), (40, 130, 700)])
