@@ -47,12 +47,17 @@ __device__ __forceinline__ constexpr int quad_at(int q) {   // where quad q (ran
     return q < 8 * (RB / 2) ? (q & ~7) + 2 * (q & 3) + ((q >> 2) & 1) : q;
 }
 
-// a, b as three bf16 terms each, packed in t[0..2]
+// a, b as three bf16 terms each, packed in t[0..2].  A value above 3.39e38 rounds to infinity as a bf16 and leaves
+// inf - inf and NaN for the other terms; with CLAMP its leading term is the largest bf16, and every finite
+// value is the sum of its terms.
+template <bool CLAMP = false>
 __device__ __forceinline__ void split3_pair(float a, float b, uint32_t (&t)[3]) {
     typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+    constexpr float kTop = 3.38953139e38f;   // the largest bf16
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
-        const v2bf v = {(__bf16)a, (__bf16)b};
+        const v2bf v = CLAMP && q == 0 ? v2bf{(__bf16)fminf(fmaxf(a, -kTop), kTop), (__bf16)fminf(fmaxf(b, -kTop), kTop)}
+                                       : v2bf{(__bf16)a, (__bf16)b};
         t[q] = __builtin_bit_cast(uint32_t, v);
         a -= bf16_lo(t[q]);
         b -= bf16_hi(t[q]);
@@ -152,7 +157,7 @@ __global__ __launch_bounds__(64 * QG * NS) void attention_seq_kernel(
 #pragma unroll
         for (int ib = 0; ib < RB; ++ib)
 #pragma unroll
-            for (int e = 0; e < 2; ++e) split3_pair(qt[qb][ib][2 * e], qt[qb][ib][2 * e + 1], w[ib][e]);
+            for (int e = 0; e < 2; ++e) split3_pair<true>(qt[qb][ib][2 * e], qt[qb][ib][2 * e + 1], w[ib][e]);
 #pragma unroll
         for (int c = 0; c < FC; ++c)
 #pragma unroll
@@ -330,6 +335,90 @@ __global__ __launch_bounds__(64 * QG * NS) void attention_seq_kernel(
         commit(tile + 1, Ps + ((tile + 1) & 1) * (NS * 3 * kImg));
         fetch(tile + 2);
         __syncthreads();
+    }
+
+    // A value of P above 3.39e38 makes its scores NaN, and so can a product that overflows (its terms have different signs)
+    // where the float product is an infinity and its weight zero.  A wave whose sums are not finite
+    // walks its share again on the float instruction, P read from memory and Qt put together again.  The loop above is
+    // the same instruction for instruction (72 shapes: 0.998 of the time on average, 0.86 to 1.04 by register count).
+    bool finite = true;
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+        finite &= finite32(lrun[qb]);
+#pragma unroll
+        for (int ib = 0; ib < RB; ++ib)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) finite &= finite32(z[qb][ib][t]);
+    }
+    if (__builtin_expect(__any(!finite), 0)) {
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+            mrun[qb] = -INFINITY;
+            lrun[qb] = 0.f;
+#pragma unroll
+            for (int ib = 0; ib < RB; ++ib) z[qb][ib] = v4f{0.f, 0.f, 0.f, 0.f};
+        }
+        auto query = [&](int qb, int ib, int t) __attribute__((always_inline)) {
+            float v = 0.f;
+#pragma unroll
+            for (int q = 2; q >= 0; --q) {
+                uint32_t word = HALF && ib == RB - 1 ? qh[qb][q][t / 2] : qf[qb][ib / 2][q][2 * (ib % 2) + t / 2];
+                asm volatile("" : "+v"(word));   // or all of Qt is put together ahead of the loop, and kept
+                v += t % 2 ? bf16_hi(word) : bf16_lo(word);
+            }
+            return v;
+        };
+        auto p_at = [&](int n, int c) __attribute__((always_inline)) {
+            return n < len && c < r ? Pb[(size_t)n * r + c] : 0.f;
+        };
+#pragma unroll 1
+        for (int step = 0; step < ntiles * (NT / 16); ++step) {
+            const int n0 = ((step / (NT / 16)) * NS + sp) * NT + 16 * (step % (NT / 16));
+            if (n0 >= len) break;   // uniform; later steps are further on
+            v4f s[QB];
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) s[qb] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ib = 0; ib < RB; ++ib)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const float a = p_at(n0 + i16, 16 * ib + 4 * g + t);
+#pragma unroll
+                    for (int qb = 0; qb < QB; ++qb) s[qb] = mfma16x16x4(a, query(qb, ib, t), s[qb]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) {
+                float mt = -INFINITY;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    if (n0 + 4 * g + t >= len) s[qb][t] = -INFINITY;
+                    mt = fmaxf(mt, s[qb][t]);
+                }
+                mt = wave_xor_max(mt, 16);
+                mt = wave_xor_max(mt, 32);
+                const float mnew = fmaxf(mrun[qb], mt);
+                const float alpha = __builtin_amdgcn_exp2f(mrun[qb] - mnew);
+                mrun[qb] = mnew;
+                lrun[qb] *= alpha;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    s[qb][t] = __builtin_amdgcn_exp2f(s[qb][t] - mnew);
+                    lrun[qb] += s[qb][t];
+                }
+#pragma unroll
+                for (int ib = 0; ib < RB; ++ib) z[qb][ib] *= alpha;
+            }
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int ib = 0; ib < RB; ++ib) {
+                    const float a = p_at(n0 + 4 * g + t, 16 * ib + i16);
+#pragma unroll
+                    for (int qb = 0; qb < QB; ++qb) z[qb][ib] = mfma16x16x4(a, s[qb][t], z[qb][ib]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+        }
     }
 
     // ---- merge of the sequence shares (group 0 takes the others in order) -----------------

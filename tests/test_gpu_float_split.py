@@ -99,3 +99,34 @@ def test_attention_float(d, r, B, N, M):
         w = np.exp(s - s.max(1, keepdims=True))
         want = (w / w.sum(1, keepdims=True)) @ p @ v.T
         assert np.abs(got[b] - want).max() / np.abs(want).max() < 1e-5
+
+
+@pytest.mark.parametrize("d,r", [(64, 16), (128, 30), (128, 48), (64, 64), (256, 32)])
+@pytest.mark.parametrize("B,N,M", [(1, 300, 20), (9, 700, 130), (44, 300, 700), (8, 300, 8200)])
+@pytest.mark.parametrize("value,query", [(-3.4028235e38, 1.0), (-1e30, 1e12)])
+def test_attention_float_extreme(d, r, B, N, M, value, query):
+    """A row of P with a value that has no bf16 terms, or with a score that overflows, far below the other scores of
+    its user: its weight is zero and the rest of the softmax is not disturbed.  In the first user early in
+    the sequence, in the last in its last valid row.  The shapes reach every form of the kernel."""
+    torch, sb = _binding()
+    print(f"[case] extreme attention d={d} r={r} B={B} N={N} M={M} {value}", flush=True)
+    rng = np.random.default_rng(r + N + M)
+    V = np.stack([np.abs(np.linalg.qr(rng.standard_normal((d, r)))[0]) for _ in range(B)]).astype(np.float32)
+    P = rng.standard_normal((B, N, r)).astype(np.float32)
+    Q = (np.abs(rng.standard_normal((B, M, d))) * query / 4).astype(np.float32)
+    lengths = rng.integers(N - 40, N + 1, size=B).astype(np.int32)
+    P[0, 11, r // 2] = value
+    P[B - 1, lengths[B - 1] - 1, r - 1] = value
+    O = torch.full((B, M, d), 7.0, device="cuda")
+    sb.solar_svd_attention(torch.from_numpy(Q).cuda(), torch.ones((B, r), device="cuda"), torch.from_numpy(V).cuda(),
+                           torch.from_numpy(P).cuda(), torch.from_numpy(lengths).cuda(), N, 0.5,
+                           sb.SOLAR_ATTN_SEQ_SOFTMAX, O)
+    got = O.cpu().numpy()
+    assert np.isfinite(got).all()
+    for b in sorted({0, B // 2, B - 1}):
+        p, v = P[b, :lengths[b]].astype(np.float64), V[b].astype(np.float64)
+        s = 0.5 * (Q[b].astype(np.float64) @ v) @ p.T
+        w = np.exp(s - s.max(1, keepdims=True))
+        want = (w / w.sum(1, keepdims=True)) @ p @ v.T
+        # scores of magnitude up to 60 in float move a weight by 2^-24 * 60 each way
+        assert np.abs(got[b] - want).max() / np.abs(want).max() < 1e-5
