@@ -218,7 +218,7 @@ solar_status solar_dense_attention_ref(const void* Q, const void* X, const int32
  * O_b = scale * Q_b (X_b^T X_b) over the valid rows of X_b, no softmax.  It is the operator the
  * paper compares against in its forward-latency figure, and what the literal r-token mode
  * (SOLAR_ATTN_LINEAR) truncates to rank r.  Workspace: solar_workspace_bytes(...).
- *   O        out [B,M,d] float
+ *   O        out [B,M,d] float; may be Q itself if that is float
  */
 solar_status solar_linear_attention(const void* Q, const void* X, const int32_t* lengths, int B, int N,
                                     int d, int M, float scale, solar_dtype t, float* O,
@@ -232,7 +232,8 @@ solar_status solar_linear_attention(const void* Q, const void* X, const int32_t*
  * projections inside, because Key and Value share H.
  *   In       [rows, d]   element type t_in
  *   W        [d, d] float, row-major
- *   Out      [rows, d]   element type t_out (bf16 output is rounded to nearest even)
+ *   Out      [rows, d]   element type t_out (bf16 output is rounded to nearest even); may be In
+ *            itself if the two types are the same, and overlaps neither In nor W otherwise
  */
 solar_status solar_apply_weights(const void* In, const float* W, int rows, int d, solar_dtype t_in,
                                  solar_dtype t_out, void* Out, void* stream);

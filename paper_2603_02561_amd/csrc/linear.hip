@@ -51,16 +51,17 @@ struct RowCfg {
 
 // One wave takes blocks of 32 rows: lane (i, h) holds entries 16 s + 8 h .. + 7 of row i for every step s of
 // the contraction, the next block's rows are loaded while this one is multiplied.
-template <int D, bool IN_BF16, bool OUT_BF16>
+// IN_PLACE: Out is In, and the columns of a row are spread over workgroups otherwise (d = 256): a workgroup then keeps
+// its rows in registers and takes the column chunks one after another.
+template <int D, bool IN_BF16, bool OUT_BF16, bool IN_PLACE>
 __global__ __launch_bounds__(kRowWaves * 64) void rowgemm_kernel(
-    const void* __restrict__ In, const float* __restrict__ W, size_t w_stride, int rows, float scale,
-    void* __restrict__ Out) {
+    const void* In, const float* __restrict__ W, size_t w_stride, int rows, float scale, void* Out) {
     using C = RowCfg<D>;
     constexpr int NC = C::NC, LDW = C::LDW, NS = D / 16, NT = NC / 32;
     constexpr int VS = IN_BF16 ? 1 : 2;                  // 16-byte loads per step
     constexpr bool AHEAD = NS * VS < 16;                 // two blocks of rows fit the registers
     extern __shared__ __attribute__((aligned(16))) __bf16 img[];     // [3][NC][LDW]
-    const int b = blockIdx.y, c0 = blockIdx.z * NC;
+    const int b = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int i32 = lane & 31, h = lane >> 5;
     const int nblk = ceil_div(rows, 32), stride = gridDim.x * kRowWaves;
@@ -78,22 +79,26 @@ __global__ __launch_bounds__(kRowWaves * 64) void rowgemm_kernel(
     };
     int blk = blockIdx.x * kRowWaves + wave;
     if (blk < nblk) load(blk, raw[0]);
-    const float* Wb = W + (size_t)b * w_stride + c0;
-    {
+    const float* Wb = W + (size_t)b * w_stride;
+    // the images of the NC columns from c0 on
+    auto stage = [&](int c0) __attribute__((always_inline)) {
         for (int e = tid; e < NC * (D / 8); e += kRowWaves * 64) {
             const int c = e % NC, k8 = e / NC;
             float x[8];
             v8bf s[3];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) x[k] = Wb[(size_t)(8 * k8 + k) * D + c];
+            for (int k = 0; k < 8; ++k) x[k] = Wb[(size_t)(8 * k8 + k) * D + c0 + c];
             split3(x, s);
 #pragma unroll
             for (int p = 0; p < 3; ++p) *reinterpret_cast<v8bf*>(img + (p * NC + c) * LDW + 8 * k8) = s[p];
         }
+    };
+    if constexpr (!IN_PLACE) {
+        stage(blockIdx.z * NC);
+        __syncthreads();
     }
-    __syncthreads();
     const __bf16* wb = img + i32 * LDW + 8 * h;
-    auto multiply = [&](int at, const v4u (&r)[NS][VS]) __attribute__((always_inline)) {
+    auto multiply = [&](int at, const v4u (&r)[NS][VS], int c0) __attribute__((always_inline)) {
         v16f acc[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t)
@@ -120,6 +125,10 @@ __global__ __launch_bounds__(kRowWaves * 64) void rowgemm_kernel(
                 float x[8];
 #pragma unroll
                 for (int k = 0; k < 8; ++k) x[k] = __uint_as_float(r[s][k / 4][k % 4]);
+                if constexpr (IN_PLACE) {                // or the terms of all steps are formed once and kept
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) asm volatile("" : "+v"(x[k]));
+                }
                 split3(x, a);
             }
             auto product = [&](int i, int j) __attribute__((always_inline)) {
@@ -186,24 +195,35 @@ __global__ __launch_bounds__(kRowWaves * 64) void rowgemm_kernel(
                     else a = __uint_as_float(r[s][k / 4][k % 4]);
 #pragma unroll
                     for (int t = 0; t < NT; ++t)
-                        acc[t] = mfma32x32x2(a, Wb[at_w + k * D + 32 * t], acc[t]);
+                        acc[t] = mfma32x32x2(a, (Wb + c0)[at_w + k * D + 32 * t], acc[t]);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
             store();
         }
     };
-    if constexpr (AHEAD) {
+    if constexpr (IN_PLACE) {
+        for (int first = blockIdx.x * kRowWaves; first < nblk; first += stride, blk += stride) {   // uniform
+            if (first > (int)blockIdx.x * kRowWaves && blk < nblk) load(blk, raw[0]);
+#pragma unroll 1
+            for (int c0 = 0; c0 < D; c0 += NC) {
+                __syncthreads();                         // the image of the last chunk is done with
+                stage(c0);
+                __syncthreads();
+                if (blk < nblk) multiply(blk, raw[0], c0);
+            }
+        }
+    } else if constexpr (AHEAD) {
         for (; blk < nblk; blk += 2 * stride) {
             if (blk + stride < nblk) load(blk + stride, raw[1]);
-            multiply(blk, raw[0]);
+            multiply(blk, raw[0], blockIdx.z * NC);
             if (blk + stride >= nblk) break;
             if (blk + 2 * stride < nblk) load(blk + 2 * stride, raw[0]);
-            multiply(blk + stride, raw[1]);
+            multiply(blk + stride, raw[1], blockIdx.z * NC);
         }
     } else {
         while (blk < nblk) {
-            multiply(blk, raw[0]);
+            multiply(blk, raw[0], blockIdx.z * NC);
             blk += stride;
             if (blk < nblk) load(blk, raw[0]);
         }
@@ -219,9 +239,13 @@ hipError_t launch_d(const void* In, const float* W, size_t w_stride, int B, int 
     constexpr int NZ = D / C::NC;
     const int want = ceil_div(ceil_div(rows, 32), kRowWaves), room = ceil_div(256, B * NZ);
     dim3 grid(want < room ? want : room, B, NZ), block(kRowWaves * 64);
+    const bool in_place = NZ > 1 && In == Out && in_bf16 == out_bf16;
 #define SOLAR_ROWGEMM(IB, OB)                                                                        \
     do {                                                                                             \
-        auto kern = rowgemm_kernel<D, IB, OB>;                                                       \
+        auto kern = rowgemm_kernel<D, IB, OB, false>;                                                \
+        if constexpr (NZ > 1 && IB == OB) {                                                          \
+            if (in_place) { kern = rowgemm_kernel<D, IB, OB, true>; grid.z = 1; }                    \
+        }                                                                                            \
         hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), C::lds_bytes);         \
         if (e != hipSuccess) return e;                                                               \
         hipLaunchKernelGGL(kern, grid, block, C::lds_bytes, stream, In, W, w_stride, rows, scale, Out); \

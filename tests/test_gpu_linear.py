@@ -155,3 +155,37 @@ def test_linear_attention_extreme_query(lib):
         want, size = Q.double() @ G, Q.double().abs() @ G.abs()
         assert torch.isfinite(O).all()
         assert ((O.double() - want).abs() <= (50 + d) * 2.0 ** -24 * size).all()
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("rows", [1, 40, 257, 20011, 70000])
+@pytest.mark.parametrize("bf16", [True, False])
+def test_in_place(lib, d, rows, bf16):
+    """Out is In: the same bits as with an output of its own, at one and at several rounds of rows per workgroup, with a
+    row that is taken a second time on the float instruction."""
+    import torch
+    print(f"[case] in place d={d} rows={rows} {bf16}", flush=True)
+    g = torch.Generator().manual_seed(d + rows)
+    In = torch.randn(rows, d, generator=g).to(torch.bfloat16 if bf16 else torch.float32).cuda()
+    In[rows // 2, 3] = float("inf")
+    W = torch.randn(d, d, generator=g).cuda()
+    want = torch.empty_like(In)
+    lib.solar_apply_weights(In, W, want)
+    lib.solar_apply_weights(In, W, In)
+    torch.cuda.synchronize()
+    assert torch.equal(In.isnan(), want.isnan())
+    assert torch.equal(In.nan_to_num(nan=0.0), want.nan_to_num(nan=0.0))
+
+
+def test_linear_attention_in_place(lib):
+    """O is Q (float), several users."""
+    import torch
+    g = torch.Generator().manual_seed(9)
+    for d in (64, 128, 256):
+        X, Q = torch.randn(3, 200, d, generator=g).cuda(), torch.randn(3, 333, d, generator=g).cuda()
+        O = torch.empty_like(Q)
+        ws = torch.empty(lib.solar_workspace_bytes(3, 200, d, 1, 333, 0), dtype=torch.uint8, device="cuda")
+        lib.solar_linear_attention(Q, X, None, 0.5, O, ws)
+        lib.solar_linear_attention(Q, X, None, 0.5, Q, ws)
+        torch.cuda.synchronize()
+        assert torch.equal(O, Q)
