@@ -715,9 +715,11 @@ __global__ __launch_bounds__(kThreads) void attention_seq_x32_kernel(
         reset_state();
         lb_off = lb_off0;
         fetch_block(0, tag0{});
+        wave_order();                           // a pass that is walked again: the last reads of the images
         commit_block(mine, 0, tag0{});
         fetch_block(1, tag0{});
         commit_block(mine + kBlk, 1, tag0{});
+        wave_order();                           // the images are read by other lanes than wrote them
         fetch_block(2, tag0{});
         if constexpr (NSB == 2) fetch_block(3, tag1{});
 #pragma unroll
@@ -738,7 +740,9 @@ __global__ __launch_bounds__(kThreads) void attention_seq_x32_kernel(
         // block j: block j + 2 (loaded NSB blocks ago) into the free image, the loads of block j + 2 + NSB, the slot
         auto run_block = [&](int j, auto par_tag) __attribute__((always_inline)) {
             using set_tag = std::integral_constant<int, NSB == 2 ? decltype(par_tag)::value : 0>;
+            wave_order();                       // the last reads of the image that this takes the place of
             commit_block(mine + o_wr, j + 2, set_tag{});
+            wave_order();
             fetch_block(j + 2 + NSB, set_tag{});
             slot(wave + kWaves * j, par_tag, guard_tag, mine + o_wr + sa_off, mine + o_cur + za_off);
             const int o = o_cur; o_cur = o_nxt; o_nxt = o_wr; o_wr = o;

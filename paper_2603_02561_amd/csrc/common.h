@@ -42,6 +42,13 @@ __device__ __forceinline__ v4f mfma16x16x32bf16(v4u a, v4u b, v4f c) {
                                                    __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
 }
 
+// Between stores to LDS and reads of the same words by other lanes of the wave, or the other way round: the LDS
+// instructions of a wave are in order, and this keeps the compiler to it.  No instruction, and no barrier for other waves.
+__device__ __forceinline__ void wave_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 __device__ __forceinline__ float wave_xor_max(float v, int mask) {
     return fmaxf(v, __shfl_xor(v, mask));
 }

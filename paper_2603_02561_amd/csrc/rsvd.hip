@@ -272,10 +272,6 @@ __global__ __launch_bounds__((PassCfg<CPL, CY>::waves * 64)) void power_pass_ker
     for (int p = 0; p < NB; ++p) acc[p] = v4f{0.f, 0.f, 0.f, 0.f};
     __syncthreads();
 
-    auto wave_order = [&]() __attribute__((always_inline)) {   // LDS of a wave is in order; so must the compiler be
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-    };
     auto compute = [&](const uint32_t (&src)[8][W]) __attribute__((always_inline)) {
         wave_order();
 #pragma unroll
