@@ -156,9 +156,9 @@ __global__ __launch_bounds__(kThreads) void attention_seq_x32_kernel(
     constexpr int LDVT = D + 8, LDI = RP + 8;                      // bf16 elements
     uint16_t* tiles = reinterpret_cast<uint16_t*>(smem);           // [3][kBuf]; SPLIT: [waves][3][kBlk]
     int* redo = reinterpret_cast<int*>(tiles + Lds::kTiles);       // set when a wave's optimistic pass overflowed
-    uint16_t* vimg = reinterpret_cast<uint16_t*>(redo + 4);        // [2][D][LDI]
     // [2][RP][LDVT]; only the prologue (and the fused projection) reads it
-    uint16_t* vt = Lds::kShareVt ? tiles : vimg + 2 * D * LDI;
+    uint16_t* vt = Lds::kShareVt ? tiles : reinterpret_cast<uint16_t*>(redo + 4);
+    uint16_t* vimg = reinterpret_cast<uint16_t*>(redo + 4) + (Lds::kShareVt ? 0 : 2 * RP * LDVT);   // [2][D][LDI]
     // Workgroups are dealt to the 8 XCDs round-robin by linear id.  All M-tiles of a user
     // get ids that agree modulo 8, so they share one XCD and its L2 holds that user's P once.
     constexpr int kQT = SPLIT ? kQW : kWaves * kQW;                // queries per workgroup
