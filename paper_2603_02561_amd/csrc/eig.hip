@@ -167,7 +167,8 @@ struct TriLds {
     }
 };
 
-template <int D, int L>
+// MANY: for batches of more users than compute units
+template <int D, int L, bool MANY = false>
 struct EigCfg {
     static constexpr int LP = 16 * ((L + 15) / 16);
     static constexpr int LD = D + 4;
@@ -186,12 +187,22 @@ struct EigCfg {
     // Narrower ones take the Ritz step of the iteration through the same solver instead of Jacobi sweeps
     // (16 users, inputs of rank r: d = 128, r = 32 from 142 to 113 us, r = 16 from 82 to 67; d = 256,
     // r = 32 from 253 to 178, of which 55 are the wider reads of the products G Q), except the narrowest,
-    // where it is no faster (d = 64, r = 8: 38 us).
-    static constexpr bool ritz = !direct && (D > 64 || L > 16);
+    // where it is no faster (d = 64, r = 8: 38 us).  It takes the whole register file for one workgroup: at d = 64 the
+    // sweeps, of which three fit a compute unit, are faster for more users than compute units (r = 16, 256 users 52
+    // us against 58, 1024 users 196 against 128).
+    static constexpr bool ritz = !direct && (D > 64 || L > 16) && !MANY;
     static constexpr size_t ritz_floats = ritz ? 2 * TriLds<ritz ? L : 16, ritz ? L : 16>::kDoublesNoWa : 0;
-    static constexpr size_t direct_floats = D <= 128 ? 2 * TriLds<(D <= 128 ? D : 64), (D == 128 ? 32 : 64)>::kDoubles : 0;
+    static constexpr int RB = D == 128 || L <= 40 ? 32 : 64;   // eigenvectors per pass of the direct solution
+    static constexpr size_t direct_floats = direct ? 2 * TriLds<direct ? D : 16, RB>::kDoubles : 0;
     static constexpr size_t lds_floats =
         base_floats + ritz_floats > direct_floats ? base_floats + ritz_floats : direct_floats;
+    // Workgroups that registers and LDS let share a compute unit, which is what counts with more users than compute
+    // units: the waves of one fill the gaps in the chains of the others.  1024 users at d = 64: r = 8 137 us with one, 84 with
+    // six; r = 24, direct, 279 and 197 with two (where iterating takes 168 for inputs of rank r, 215 to 290 for
+    // singular values ~ k^-1/2 and k^-1).  r > 32 takes the eigenvectors in one pass and 86 KB for it: alone
+    // on its compute unit it is as fast for many users (r = 40: 309) as iterating is at best.
+    static constexpr int groups = D == 64 && !ritz && L <= 40 ? 2 : 1;
+    static_assert(groups * (sizeof(float) * lds_floats + 1024) <= 160 * 1024, "LDS");
 };
 
 // One cyclic sweep of one-sided Jacobi over the L columns of Zc; returns this thread's largest
@@ -569,10 +580,9 @@ __device__ __forceinline__ bool ritz_rotate(const float* Zc, float* Qc, const Tr
 // The r leading eigenpairs straight from the D x D matrix in Gs (LDS, row stride GS), written to S and V.
 // Takes all of the dynamic LDS; Gs may lie anywhere in it.  False (nothing written): two wanted
 // eigenvalues are too close.
-template <int D, int RMAX, int GS>
+template <int D, int RMAX, int RB, int GS>
 __device__ __forceinline__ bool eig_direct(const float* Gs, double* sm, double* scal, int* twist, int r, float* S,
                                            float* V) {
-    constexpr int RB = D == 128 ? 32 : 64;              // vectors per pass
     constexpr int TB = RMAX <= 32 && D == 128 ? 16 : 8;
     using T = TriCfg<D, RB>;
     const TriLds<D, RB> w(sm, nullptr);
@@ -629,12 +639,12 @@ __device__ __forceinline__ bool eig_direct(const float* Gs, double* sm, double* 
     return true;
 }
 
-template <int D, int L>
-__global__ __launch_bounds__(kEigThreads) void eig_topr_kernel(
+template <int D, int L, bool MANY>
+__global__ __launch_bounds__(kEigThreads, (EigCfg<D, L, MANY>::groups * kEigWaves / 4)) void eig_topr_kernel(
     const float* __restrict__ G, const float* __restrict__ partials, int nsplit,
     const int32_t* __restrict__ lengths, int N, int r,
     float* __restrict__ S, float* __restrict__ V, int32_t* __restrict__ info, EigParams prm) {
-    using C = EigCfg<D, L>;
+    using C = EigCfg<D, L, MANY>;
     constexpr int LP = C::LP, LD = C::LD, TC = C::TC;
     extern __shared__ __attribute__((aligned(16))) float smem[];
     float* Zc = smem;
@@ -666,7 +676,11 @@ __global__ __launch_bounds__(kEigThreads) void eig_topr_kernel(
     // G to LDS where it fits; true if this thread met an entry that is not finite.  One that is not finite shows on
     // the diagonal too (|G_ij|^2 <= G_ii G_jj), which is what is looked at where G stays in memory.
     auto stage = [&]() __attribute__((always_inline)) {
-    bool bad = false;
+    v4f probe = v4f{0.f, 0.f, 0.f, 0.f};                // NaN where an entry was not finite
+    auto look = [&](v4f v) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) probe[t] = fmaf(v[t], 0.f, probe[t]);
+    };
     if constexpr (C::GLDS) {
         if (partials) {
             // G from the split-N partial blocks of the Gram kernel: per chunk and fragment pair
@@ -705,11 +719,11 @@ __global__ __launch_bounds__(kEigThreads) void eig_topr_kernel(
                     int s1 = 0, rest = pair;
                     while (rest >= CPL - s1) { rest -= CPL - s1; ++s1; }
                     const int s2 = s1 + rest;
+                    look(acc[i]);
                     const int c = CPL * (ln & 15) + s2;
 #pragma unroll
                     for (int t = 0; t < 4; ++t) {
                         const int a = CPL * (4 * (ln >> 4) + t) + s1;
-                        bad |= !finite32(acc[i][t]);
                         Gs[a * C::GS + c] = acc[i][t];
                         if (s1 < s2) Gs[c * C::GS + a] = acc[i][t];
                     }
@@ -719,15 +733,14 @@ __global__ __launch_bounds__(kEigThreads) void eig_topr_kernel(
             for (int e = tid; e < D * D / 4; e += kEigThreads) {
                 const int i = e / (D / 4), c4 = e % (D / 4);
                 const v4f v = *reinterpret_cast<const v4f*>(Gb + (size_t)i * D + 4 * c4);
-#pragma unroll
-                for (int t = 0; t < 4; ++t) bad |= !finite32(v[t]);
+                look(v);
                 *reinterpret_cast<v4f*>(Gs + i * C::GS + 4 * c4) = v;
             }
         }
     } else {
-        for (int e = tid; e < D; e += kEigThreads) bad |= !finite32(Gb[(size_t)e * D + e]);
+        for (int e = tid; e < D; e += kEigThreads) probe[0] = fmaf(Gb[(size_t)e * D + e], 0.f, probe[0]);
     }
-    return bad;
+    return (probe[0] + probe[1]) + (probe[2] + probe[3]) != 0.f;
     };
     // A G with entries that are not finite has no factors.  Neither solver would say so: norms and maxima drop NaN,
     // so one takes G for zero and the other for converged.
@@ -743,7 +756,7 @@ __global__ __launch_bounds__(kEigThreads) void eig_topr_kernel(
     if constexpr (C::direct) {
         if (prm.direct) {
             if (__syncthreads_or(bad)) { not_finite(); return; }
-            if (eig_direct<D, L - 8, C::GS>(Gs, reinterpret_cast<double*>(smem), sh_scal, sh_twist, r,
+            if (eig_direct<D, L - 8, C::RB, C::GS>(Gs, reinterpret_cast<double*>(smem), sh_scal, sh_twist, r,
                                             S + (size_t)b * r, V + (size_t)b * D * r)) {
                 if (tid == 0 && info) info[b] = 0;
                 return;
@@ -1191,12 +1204,16 @@ hipError_t launch_rsvd_small_t(const float* partials, int nsplit, const int32_t*
     return hipGetLastError();
 }
 
-template <int D, int L>
+template <int D, int L, bool MANY = false>
 hipError_t launch_eig_t(const float* G, const float* partials, int nsplit, const int32_t* lengths, int B, int N,
                         int r, float* S, float* V, int32_t* info, const EigParams& prm, hipStream_t stream) {
-    if (partials && !EigCfg<D, L>::GLDS) return hipErrorInvalidValue;
-    const size_t lds = sizeof(float) * EigCfg<D, L>::lds_floats;
-    auto kern = eig_topr_kernel<D, L>;
+    using C = EigCfg<D, L, MANY>;
+    if constexpr (D == 64 && C::ritz) {
+        if (B > 256) return launch_eig_t<D, L, true>(G, partials, nsplit, lengths, B, N, r, S, V, info, prm, stream);
+    }
+    if (partials && !C::GLDS) return hipErrorInvalidValue;
+    const size_t lds = sizeof(float) * C::lds_floats;
+    auto kern = eig_topr_kernel<D, L, MANY>;
     hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(B), dim3(kEigThreads), lds, stream, G, partials, nsplit, lengths, N, r, S, V,

@@ -110,3 +110,15 @@ def test_zero_matrix_converges(lib):
     for d, r in ((64, 8), (64, 40), (128, 16), (128, 64), (256, 16)):
         info, S, V = factors(lib, np.zeros((1, 100, d), dtype=np.float32), r)
         assert info[0] == 0 and np.all(S == 0.0) and np.all(V == 0.0), (d, r, info)
+
+
+@pytest.mark.parametrize("d,r", [(64, 8), (64, 9), (64, 16), (64, 24), (64, 40), (128, 16)])
+@pytest.mark.parametrize("B", [256, 257, 700])
+def test_more_users_than_compute_units(lib, d, r, B):
+    """Batches at and beyond one user per compute unit, where the route depends on the number of users (d = 64,
+    r = 9 .. 16) and several workgroups share a compute unit."""
+    print(f"[case] many users d={d} r={r} B={B}", flush=True)
+    g = np.random.default_rng(B + d + r)
+    X = np.matmul(g.standard_normal((B, 90, r)) / np.sqrt(1 + np.arange(r)), g.standard_normal((B, r, d)))
+    X = (X + 0.01 * g.standard_normal(X.shape)).astype(np.float32)
+    check(X, *factors(lib, X, r), r)
