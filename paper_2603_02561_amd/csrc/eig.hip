@@ -25,36 +25,13 @@
 // kernel runs eight waves (two per SIMD), gives every column pair a team of up to 16
 // lanes whose partial dot products are combined with DPP lane permutations, and keeps
 // every trip count a compile-time constant.
+#include "column_block.h"
 #include "common.h"
 #include "kernels.h"
-#include "tridiag.h"
-#include "xty_partials.h"
 
 namespace solar {
 
 namespace {
-
-constexpr int kEigThreads = 512;
-constexpr int kEigWaves = kEigThreads / 64;
-// A column of the iterate whose norm falls below this fraction of the largest column norm
-// is rounding noise of the float Gram matrix (about sqrt(d) * 2^-24 relative) and is dropped.
-constexpr float kDeadRel = 1.0e-5f;
-// Rotations are skipped below kSkipCos.  The Jacobi phase converges quadratically: a sweep whose
-// largest |cos| was c leaves about c^2 behind (L * c^2 at worst), so the phase ends after the
-// first sweep that met no |cos| above kSweepDone = 5e-4, with a few 1e-6 left; the residual
-// check of the following power step is what accepts the result.  (1e-3 leaves V^T V up to 1.3e-5
-// off the identity at 72 columns and 3e-3 up to 4e-5; 3e-2 makes the check fail and the iteration
-// longer.  In a batch some user nearly always needs the sweep that a looser limit would save
-// the others, so the launch is no shorter with 1e-3.)
-constexpr float kSkipCos = 1.0e-7f;
-constexpr float kSweepDone = 5.0e-4f;
-
-__host__ __device__ constexpr int pow2floor_c(int x) {
-    int p = 1;
-    while (2 * p <= x) p *= 2;
-    return p;
-}
-__host__ __device__ constexpr int min_c(int a, int b) { return a < b ? a : b; }
 
 __device__ __forceinline__ uint32_t mix32(uint32_t x) {
     x ^= x >> 16; x *= 0x7feb352du; x ^= x >> 15; x *= 0x846ca68bu; x ^= x >> 16;
@@ -68,25 +45,6 @@ __device__ __forceinline__ float omega_entry(int b, int j, int i) {
     float u1 = ((c >> 8) + 1u) * (1.0f / 16777217.0f);
     float u2 = (c2 >> 8) * (1.0f / 16777216.0f);
     return sqrtf(-2.0f * __logf(u1)) * __cosf(6.28318530718f * u2);
-}
-
-template <int CTRL>
-__device__ __forceinline__ float dpp_mov(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
-}
-
-// Sum over a team of T consecutive lanes (T a power of two, team aligned to T); every
-// lane of the team receives the same bits.  Up to 16 lanes the exchange is a DPP operand
-// (quad permutes, then mirror within 8 and within 16 lanes).
-template <int T>
-__device__ __forceinline__ float team_sum(float v) {
-    if constexpr (T >= 2) v += dpp_mov<0xB1>(v);    // quad_perm [1,0,3,2]
-    if constexpr (T >= 4) v += dpp_mov<0x4E>(v);    // quad_perm [2,3,0,1]
-    if constexpr (T >= 8) v += dpp_mov<0x141>(v);   // row_half_mirror
-    if constexpr (T >= 16) v += dpp_mov<0x140>(v);  // row_mirror
-    if constexpr (T >= 32) v += __shfl_xor(v, 16);
-    if constexpr (T >= 64) v += __shfl_xor(v, 32);
-    return v;
 }
 
 // Z = G Q with the float 16x16x4 MFMA, block rows of 16 dealt round-robin to the waves.  G is symmetric, and
@@ -145,246 +103,8 @@ __device__ __forceinline__ void gemm_gq(const float* Gb, const float* Qc, float*
     }
 }
 
-// Work arrays of one dense solve at `base` (doubles): reflectors, wa, wb, vectors of length N.
-template <int N, int RB>
-struct TriLds {
-    using T = TriCfg<N, RB>;
-    double *U, *wa, *wb, *dd, *ee, *ih, *es, *lam;
-    double2* t;
-    static constexpr size_t kDoublesNoWa = T::USZ + T::WB + T::VEC;
-    static constexpr size_t kDoubles = kDoublesNoWa + T::WA;
-    // wa == nullptr: behind the other arrays
-    __device__ __forceinline__ TriLds(double* base, double* wa_) {
-        U = base;
-        wb = U + T::USZ;
-        dd = wb + T::WB;
-        ee = dd + N;
-        ih = ee + N;
-        es = ih + N;
-        t = reinterpret_cast<double2*>(es + N);
-        lam = reinterpret_cast<double*>(t + N + 8);
-        wa = wa_ ? wa_ : dd + T::VEC;
-    }
-};
-
-// MANY: for batches of more users than compute units
-template <int D, int L, bool MANY = false>
-struct EigCfg {
-    static constexpr int LP = 16 * ((L + 15) / 16);
-    static constexpr int LD = D + 4;
-    // lanes per column outside the Jacobi rounds
-    static constexpr int TC = min_c(min_c(64, D), pow2floor_c(kEigThreads / L));
-    // G is staged in LDS when it fits beside the two iterate blocks
-    static constexpr bool GLDS = D <= 128;
-    static constexpr int GS = GLDS ? D + 4 : D;
-    static constexpr size_t base_floats = (size_t)2 * LP * LD + 3 * LP + 8 + (GLDS ? (size_t)D * GS : 0);
-    // Wide blocks are solved directly: the reduction of the whole matrix is then cheaper than the
-    // power steps, Gram-Schmidt passes and Ritz steps of the iteration, and takes the same time for every
-    // spectrum (16 users, d = 128, r = 64: 214 us per launch, where iterating took 360 for
-    // inputs of rank r, 452 for singular values ~ k^-1/2 and 732 with the last ones in the noise; d = 64, r = 40:
-    // 78 us against 122, 227 and 619; at d = 64, L = 24 and d = 128, L = 48 the two are about even on easy spectra).
-    static constexpr bool direct = (D == 64 && L >= 32) || (D == 128 && L >= 56);
-    // Narrower ones take the Ritz step of the iteration through the same solver instead of Jacobi sweeps
-    // (16 users, inputs of rank r: d = 128, r = 32 from 142 to 113 us, r = 16 from 82 to 67; d = 256,
-    // r = 32 from 253 to 178, of which 55 are the wider reads of the products G Q), except the narrowest,
-    // where it is no faster (d = 64, r = 8: 38 us).  It takes the whole register file for one workgroup: at d = 64 the
-    // sweeps, of which three fit a compute unit, are faster for more users than compute units (r = 16, 256 users 52
-    // us against 58, 1024 users 196 against 128).
-    static constexpr bool ritz = !direct && (D > 64 || L > 16) && !MANY;
-    static constexpr size_t ritz_floats = ritz ? 2 * TriLds<ritz ? L : 16, ritz ? L : 16>::kDoublesNoWa : 0;
-    static constexpr int RB = D == 128 || L <= 40 ? 32 : 64;   // eigenvectors per pass of the direct solution
-    static constexpr size_t direct_floats = direct ? 2 * TriLds<direct ? D : 16, RB>::kDoubles : 0;
-    static constexpr size_t lds_floats =
-        base_floats + ritz_floats > direct_floats ? base_floats + ritz_floats : direct_floats;
-    // Workgroups that registers and LDS let share a compute unit, which is what counts with more users than compute
-    // units: the waves of one fill the gaps in the chains of the others.  1024 users at d = 64: r = 8 137 us with one, 84 with
-    // six; r = 24, direct, 279 and 197 with two (where iterating takes 168 for inputs of rank r, 215 to 290 for
-    // singular values ~ k^-1/2 and k^-1).  r > 32 takes the eigenvectors in one pass and 86 KB for it: alone
-    // on its compute unit it is as fast for many users (r = 40: 309) as iterating is at best.
-    static constexpr int groups = D == 64 && !ritz && L <= 40 ? 2 : 1;
-    static_assert(groups * (sizeof(float) * lds_floats + 1024) <= 160 * 1024, "LDS");
-};
-
-// One cyclic sweep of one-sided Jacobi over the L columns of Zc; returns this thread's largest
-// |cos| met in the sweep.
-//
-// A rotation needs two columns and a round of disjoint rotations touches every column, so a
-// sweep that keeps the columns in LDS between rounds moves the whole block through LDS and meets
-// a workgroup barrier once per round: 39 times per sweep at 40 columns, about 640 of a round's
-// 1280 cycles.  Here the columns are dealt to the waves in half-groups of G = 64 / T columns (T
-// lanes per column pair) and a wave keeps two half-groups A, B in registers for G rounds:
-// team i of the wave holds A[i] and, in round j, B[(i + j) mod G], which the teams pass on with
-// lane permutations; after G rounds every column of A has met every column of B.  The half-groups
-// meet each other in a round-robin tournament of H - 1 such super-rounds, with LDS and the
-// workgroup barrier only between them, and the pairs inside a half-group are taken first, G - 1
-// rounds through LDS.  The number of rotations per sweep is that of any cyclic ordering; the
-// barriers drop from L - 1 to (H - 1) + (G - 1).
 // most power steps that a slow convergence rate may add before the first Jacobi phase
 constexpr int kExtraStepsCap = 4;
-// the widest team (at most 16 lanes, a float4 per lane at least) whose waves fit the workgroup
-__host__ __device__ constexpr int jacobi_team_lanes(int d, int l) {
-    for (int t = 16; t > 8; t /= 2) {
-        const int g = 64 / t;
-        if (4 * t <= d && (l + 2 * g - 1) / (2 * g) <= kEigWaves) return t;
-    }
-    return 8;
-}
-
-template <int D, int L>
-struct JacobiCfg {
-    static constexpr int T = jacobi_team_lanes(D, L);   // lanes per column pair
-    static constexpr int G = 64 / T;                    // column pairs per wave = columns per half-group
-    static constexpr int NW = (L + 2 * G - 1) / (2 * G);  // waves that hold columns
-    static constexpr int H = 2 * NW;                    // half-groups
-    static constexpr int LPAD = H * G;                  // columns including the (zero) padding
-    static constexpr int CH = D / (4 * T);              // float4 per lane and column
-    static_assert(NW <= kEigWaves, "one wave per pair of half-groups");
-    static_assert(LPAD <= EigCfg<D, L>::LP, "the padding columns exist in LDS");
-    static_assert(LPAD / 2 * T <= kEigThreads, "one team per pair in the rounds through LDS");
-    static_assert(D % (4 * T) == 0 && CH >= 1, "whole float4 per lane");
-};
-
-// The rotation that makes the columns a, c of a pair orthogonal, from their squared norms al, be
-// and inner product ga; the norms follow in closed form (al' = al - t ga, be' = be + t ga with
-// t the tangent).  With d = be - al and g = ga, both divided by |a||c| so that squares cannot
-// overflow, the rotation has cos^2 = x = 1/2 + |d| / (2 sqrt(d^2 + 4 g^2)) and
-// sin = sign(d) g / (sqrt(d^2 + 4 g^2) cos): two dependent reciprocal square roots, where the
-// route over zeta = d / 2g and the tangent takes four dependent transcendental steps.  Columns
-// that have collapsed to rounding noise are left alone (dropped later), and so are pairs whose
-// cosine is below kSkipCos.  With BRANCHLESS the rotation is always applied and a pair that is
-// left alone gets the identity: no lane branches in the chain of dependent instructions, which
-// pays while a lane holds up to eight elements per column.
-template <int T, int CH, bool BRANCHLESS>
-__device__ __forceinline__ void rotate_columns(v4f (&a)[CH], v4f (&c)[CH], float& al, float& be, float ga,
-                                               float dead2, float& offmax) {
-    const float ra = __builtin_amdgcn_rsqf(al), rb = __builtin_amdgcn_rsqf(be);
-    const float gn = ga * ra * rb;   // cosine of the angle between the columns
-    const float dn = (be - al) * ra * rb;
-    const float cosv = fabsf(gn);
-    const bool live = al > dead2 && be > dead2;
-    const bool rot = live && cosv > kSkipCos;
-    const float ih = __builtin_amdgcn_rsqf(dn * dn + 4.f * gn * gn);
-    const float x = 0.5f + 0.5f * fabsf(dn) * ih;
-    const float r = __builtin_amdgcn_rsqf(x);
-    float cs = x * r;
-    float sn = (dn >= 0.f ? gn : -gn) * ih * r;
-    float tg = sn * r * ga;
-    if constexpr (BRANCHLESS) {
-        offmax = live ? fmaxf(offmax, cosv) : offmax;
-        cs = rot ? cs : 1.f;
-        sn = rot ? sn : 0.f;
-        tg = rot ? tg : 0.f;
-#pragma unroll
-        for (int k = 0; k < CH; ++k) {
-            const v4f x4 = a[k], y4 = c[k];
-            a[k] = cs * x4 - sn * y4;
-            c[k] = sn * x4 + cs * y4;
-        }
-        al -= tg;
-        be += tg;
-    } else {
-        if (live) offmax = fmaxf(offmax, cosv);
-        if (rot) {
-#pragma unroll
-            for (int k = 0; k < CH; ++k) {
-                const v4f x4 = a[k], y4 = c[k];
-                a[k] = cs * x4 - sn * y4;
-                c[k] = sn * x4 + cs * y4;
-            }
-            al -= tg;
-            be += tg;
-        }
-    }
-}
-
-template <int CH>
-__device__ __forceinline__ float dot_ch(const v4f (&a)[CH], const v4f (&c)[CH]) {
-    float s = 0.f;
-#pragma unroll
-    for (int k = 0; k < CH; ++k) s += a[k].x * c[k].x + a[k].y * c[k].y + a[k].z * c[k].z + a[k].w * c[k].w;
-    return s;
-}
-
-// pair number k of round rho of a round-robin tournament of n players (n even): player n - 1
-// stays, the others go round
-__device__ __forceinline__ void tournament_pair(int n, int rho, int k, int& p, int& q) {
-    p = rho + k;
-    q = rho - k;
-    if (p >= n - 1) p -= n - 1;
-    if (q < 0) q += n - 1;
-    if (k == 0) p = n - 1;
-}
-
-template <int D, int L>
-__device__ __forceinline__ float jacobi_sweep(float* Zc, float dead2) {
-    using J = JacobiCfg<D, L>;
-    constexpr int T = J::T, G = J::G, CH = J::CH, LD = EigCfg<D, L>::LD;
-    constexpr bool NB = T == 16;   // measured: teams of 16 lanes gain from it, teams of 8 lose
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int u = tid % T;
-    float offmax = 0.f;
-    v4f a[CH], c[CH];
-    auto load = [&](v4f (&dst)[CH], int col) __attribute__((always_inline)) {
-#pragma unroll
-        for (int k = 0; k < CH; ++k) dst[k] = *reinterpret_cast<const v4f*>(Zc + col * LD + 4 * u + 4 * T * k);
-    };
-    auto store = [&](const v4f (&src)[CH], int col) __attribute__((always_inline)) {
-#pragma unroll
-        for (int k = 0; k < CH; ++k) *reinterpret_cast<v4f*>(Zc + col * LD + 4 * u + 4 * T * k) = src[k];
-    };
-    // the pairs inside every half-group: G - 1 rounds through LDS, one team per pair
-    if constexpr (G > 1) {
-        const int team = tid / T;
-        const int hg = team / (G / 2), k = team % (G / 2);
-#pragma unroll 1
-        for (int rho = 0; rho < G - 1; ++rho) {
-            if (team < J::LPAD / 2) {
-                int p, q;
-                tournament_pair(G, rho, k, p, q);
-                load(a, hg * G + p);
-                load(c, hg * G + q);
-                float al = team_sum<T>(dot_ch<CH>(a, a)), be = team_sum<T>(dot_ch<CH>(c, c));
-                rotate_columns<T, CH, NB>(a, c, al, be, team_sum<T>(dot_ch<CH>(a, c)), dead2, offmax);
-                store(a, hg * G + p);
-                store(c, hg * G + q);
-            }
-            __syncthreads();
-        }
-    }
-    // the pairs between half-groups: wave w holds the half-groups of pair w of the super-round
-    const int i = lane / T;
-#pragma unroll 1
-    for (int s = 0; s < J::H - 1; ++s) {
-        if (wave < J::NW) {
-            int ha, hb;
-            tournament_pair(J::H, s, wave, ha, hb);
-            load(a, ha * G + i);
-            load(c, hb * G + i);
-            // squared norms once per super-round; they follow the rotations in closed form, and
-            // that of a B column travels with the column
-            float al = team_sum<T>(dot_ch<CH>(a, a)), be = team_sum<T>(dot_ch<CH>(c, c));
-#pragma unroll
-            for (int j = 0; j < G; ++j) {
-                rotate_columns<T, CH, NB>(a, c, al, be, team_sum<T>(dot_ch<CH>(a, c)), dead2, offmax);
-                if (j + 1 < G) {
-                    // team i takes over the B column of team i + 1
-                    be = __shfl(be, (lane + T) & 63);
-#pragma unroll
-                    for (int k = 0; k < CH; ++k) {
-                        c[k].x = __shfl(c[k].x, (lane + T) & 63);
-                        c[k].y = __shfl(c[k].y, (lane + T) & 63);
-                        c[k].z = __shfl(c[k].z, (lane + T) & 63);
-                        c[k].w = __shfl(c[k].w, (lane + T) & 63);
-                    }
-                }
-            }
-            store(a, ha * G + i);
-            store(c, hb * G + (i + G - 1) % G);
-        }
-        __syncthreads();
-    }
-    return offmax;
-}
 
 // One pass of modified Gram-Schmidt over the L columns of Zc, normalized into Qc: a cheap
 // orthonormal basis of span(Z) for the early power steps, where only the span matters.  The
@@ -479,102 +199,6 @@ __device__ __forceinline__ void mgs_orthonormalize(float* Zc, float* Qc, float* 
         }
         __syncthreads();
     }
-}
-
-// Two wanted eigenvalues closer than this (relative to the norm) leave their vectors, which are computed
-// independently of each other, orthogonal only to about 1e-15 / kTriGap: the caller takes another route.
-constexpr double kTriGap = 1.0e-9;
-// A matrix of zeros comes out of the reduction with a norm of about 1e-89; one of floats, or of their
-// squares, is above this.
-constexpr double kTriZero = 1.0e-80;
-
-// Gm[i][j] = z_i . z_j in double precision for the L columns of Zc (D values each, column stride LD)
-template <int D, int L, int LD, int LG>
-__device__ __forceinline__ void gram_columns64(const float* Zc, double* Gm) {
-    constexpr int NT = (L + 15) / 16;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int i16 = lane & 15, g = lane >> 4;
-    for (int p = wave; p < NT * (NT + 1) / 2; p += kEigWaves) {
-        int I = 0, rest = p;
-        while (rest >= NT - I) { rest -= NT - I; ++I; }
-        const int J = I + rest;
-        const float* za = Zc + (16 * I + i16) * LD + g;
-        const float* zb = Zc + (16 * J + i16) * LD + g;
-        v4d acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll 8
-        for (int k0 = 0; k0 < D; k0 += 4) acc = mfma16x16x4f64((double)za[k0], (double)zb[k0], acc);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const int i = 16 * I + g + 4 * t, j = 16 * J + i16;
-            if (i < L && j < L) {
-                Gm[i * LG + j] = acc[t];
-                Gm[j * LG + i] = acc[t];
-            }
-        }
-    }
-    __syncthreads();
-}
-
-// The Rayleigh-Ritz step on the N columns of Zc (LDS, column stride D + 4): with C = Z^T Z = W diag(l) W^T,
-// formed and solved in double precision, the columns of Z W diag(l)^-1/2 are orthonormal and
-// diagonalize the projected problem, which is what one-sided Jacobi sweeps over Z converge to.  They go
-// to Qc (zero where sqrt(l) is below kDeadRel of the largest), in descending order of l; sig[k] receives
-// sqrt(l_k).  Qc may share its memory with wa.  False (and Qc untouched unless it is wa): two of the
-// `wanted` leading eigenvalues are too close for this route.
-template <int D, int N>
-__device__ __forceinline__ bool ritz_rotate(const float* Zc, float* Qc, const TriLds<N, N>& w, double* scal, int* twist,
-                                            float* sig, int wanted) {
-    using T = TriCfg<N, N>;
-    constexpr int LD = D + 4, NT = (N + 15) / 16;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int i16 = lane & 15, g = lane >> 4;
-    double* Cm = w.wa;
-    gram_columns64<D, N, LD, N>(Zc, Cm);
-    TriRows<N> a;
-    if (wave < kTriWaves) {
-#pragma unroll
-        for (int m = 0; m < T::RS; ++m)
-#pragma unroll
-            for (int c = 0; c < T::NC; ++c) {
-                const int i = 16 * (m / 4) + 4 * wave + m % 4, j = (lane ^ (4 * wave)) + 64 * c;
-                a[m][c] = i < N && j < N ? Cm[i * N + j] : 0.0;
-            }
-    }
-    tri_reduce<N>(a, w.wb, w.U, w.dd, w.ee, w.ih);
-    const double bound = tri_values<N, (N <= 32 ? 8 : 4)>(w.dd, w.ee, w.es, w.t, w.lam, scal,
-                                                          reinterpret_cast<int*>(w.wb), N);
-    const double l0 = w.lam[0], dead = (double)kDeadRel * kDeadRel * l0;
-    const bool close = tid + 1 < wanted && w.lam[tid + 1] > dead && w.lam[tid] - w.lam[tid + 1] < kTriGap;
-    if (__syncthreads_or(close) || !(bound > kTriZero) || !(l0 > 0.0)) return false;
-    tri_vectors<N, N>(w.t, w.es, w.lam, w.wa, w.wb, twist, 0, N);
-    constexpr int TB = 8;
-    const int v = tid / TB, u = tid % TB;
-    double y[N / TB];
-    if (v < N) tri_load<N, N, TB>(w.wa, v, u, y);
-    tri_cross<N>(w.U, w.dd);
-    if (v < N) {
-        tri_back<N, TB>(w.U, w.ih, w.dd, u, y);
-        const double l = w.lam[v], rs = l > dead ? rsq64(l * bound) : 0.0;
-        if (u == 0) sig[v] = (float)(l > 0.0 ? l * bound * rsq64(l * bound) : 0.0);
-#pragma unroll
-        for (int q = 0; q < N / TB; ++q) w.wb[v * N + TB * q + u] = l > dead ? y[q] * rs : 0.0;
-    }
-    __syncthreads();
-    for (int J = wave; J < D / 16; J += kEigWaves) {
-#pragma unroll
-        for (int I = 0; I < NT; ++I) {
-            const bool in = 16 * I + i16 < N;
-            const double* wr = w.wb + (in ? 16 * I + i16 : 0) * N + g;
-            const float* zr = Zc + g * LD + 16 * J + i16;
-            v4d acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-            for (int k0 = 0; k0 < N; k0 += 4) acc = mfma16x16x4f64(in ? wr[k0] : 0.0, (double)zr[k0 * LD], acc);
-#pragma unroll
-            for (int t = 0; t < 4; ++t) Qc[(16 * I + g + 4 * t) * LD + 16 * J + i16] = (float)acc[t];
-        }
-    }
-    __syncthreads();
-    return true;
 }
 
 // The r leading eigenpairs straight from the D x D matrix in Gs (LDS, row stride GS), written to S and V.
@@ -954,256 +578,6 @@ __global__ __launch_bounds__(kEigThreads, (EigCfg<D, L, MANY>::groups * kEigWave
     if (tid == 0 && info) info[b] = status;
 }
 
-// ---- small problems of Algorithm 1 -----------------------------------------------------------------------
-// Cholesky factorization of the L x L matrix in A (LDS, row stride LR doubles, both triangles), in double precision
-// by the whole workgroup: a thread keeps its entries in registers, so a step is the store of the pivot row, one
-// barrier and a multiply-add.  The row of pivot k stays in A as it was when its turn came, A[k][j] = R[k][k] R[k][j];
-// inv[k] receives 1 / R[k][k]^2 and rs[k] 1 / R[k][k].  A pivot k that is not above limit * d0[k]
-// ends it (false, in every thread); with DROP, one that is not above `limit` drops its column (inv = rs = 0).
-template <int L, int LR, bool DROP>
-__device__ __forceinline__ bool cholesky64(double* A, double* inv, double* rs, const double* d0, double limit) {
-    const int tid = threadIdx.x;
-    constexpr int RP = kEigThreads / L, Q = (L + RP - 1) / RP;   // rows per pass of the threads, entries per thread
-    const int j = tid % L, i0 = tid / L;
-    double a[Q];
-#pragma unroll
-    for (int q = 0; q < Q; ++q) a[q] = i0 + q * RP < L ? A[(i0 + q * RP) * LR + j] : 0.0;
-    __syncthreads();
-    for (int k = 0; k < L; ++k) {
-        double* row = A + k * LR;
-#pragma unroll
-        for (int q = 0; q < Q; ++q)
-            if (i0 + q * RP == k) row[j] = a[q];
-        __syncthreads();
-        const double piv = row[k];
-        if constexpr (!DROP) {
-            if (!(piv > limit * d0[k]) || !(piv > 0.0)) return false;   // uniform
-        }
-        const bool live = !DROP || piv > limit;
-        const double r1 = live ? rsq64(piv) : 0.0, f = live ? rcp64(piv) : 0.0;
-        if (tid == 0) { inv[k] = f; rs[k] = r1; }
-        const double m = row[j] * f;
-#pragma unroll
-        for (int q = 0; q < Q; ++q)
-            if (i0 + q * RP < L) a[q] = fma(-m, row[i0 + q * RP], a[q]);
-    }
-    __syncthreads();
-    return true;
-}
-
-// Z <- Z R^-1 for the factor that cholesky64 left in A, columns of Z at Zc + c * LD; one thread per row.
-template <int D, int L, int LD, int LR>
-__device__ __forceinline__ void solve_rows64(float* Zc, const double* A, const double* inv, const double* rs) {
-    static_assert(LR % 2 == 0 && L % 2 == 0, "pairs of a row are read together");
-    const int a = threadIdx.x;
-    if (a < D) {
-        double x[L];
-#pragma unroll
-        for (int c = 0; c < L; ++c) x[c] = (double)Zc[c * LD + a];
-#pragma unroll
-        for (int k = 0; k < L; ++k) {
-            const double f = x[k] * inv[k];
-            const double2* row = reinterpret_cast<const double2*>(A + k * LR);
-#pragma unroll
-            for (int c2 = (k + 1) / 2; c2 < L / 2; ++c2) {
-                const double2 v = row[c2];
-                if (2 * c2 > k) x[2 * c2] = fma(-f, v.x, x[2 * c2]);
-                x[2 * c2 + 1] = fma(-f, v.y, x[2 * c2 + 1]);
-            }
-            Zc[k * LD + a] = (float)(x[k] * rs[k]);
-        }
-    }
-    __syncthreads();
-}
-
-// LDS of the last step, in floats: the columns, their images (also the first work array of the dense solve), and
-// the other work arrays; the Cholesky factor shares the memory of the latter.
-template <int D, int L>
-struct SmallCfg {
-    using C = EigCfg<D, L>;
-    static constexpr int LR = L + 2;
-    static constexpr size_t zc = (size_t)C::LP * C::LD;
-    static constexpr size_t qc = zc > 2 * (size_t)L * L ? zc : 2 * (size_t)L * L;
-    static constexpr size_t tri = 2 * TriLds<L, L>::kDoublesNoWa;
-    static_assert(tri >= 2 * ((size_t)L * LR + 3 * L), "the factor fits the work arrays");
-    static_assert(zc % 4 == 0 && qc % 4 == 0, "16-byte alignment of the work arrays");
-    static constexpr size_t floats = zc + qc + tri + 2 * C::LP;
-};
-
-// Last step of Algorithm 1 when it is run with passes over H: from W = H^T Y (d x r) and
-// Gy = Y^T Y (r x r) of the final Y = H Omega, the QR factor R of Y is the Cholesky factor of
-// Gy (Y = Q R  =>  Gy = R^T R), Q^T H = R^-T W^T, and the singular values s and right singular
-// vectors of Q^T H are those of (Q^T H)^T = W R^-1, from the eigenpairs of its Gram matrix in double precision
-// (ritz_rotate; one-sided Jacobi sweeps where two of its eigenvalues are too close for that route, or one is
-// too small).  One workgroup per user, all of it in LDS.  The time is that of its dependent chains (64 users, d = 128,
-// r = 32: 64 us, where float Cholesky with four barriers a column and the sweeps took 87).
-// info: 0 ok, > 0 Jacobi sweeps exhausted, -1 bad length, -2 Gy is not numerically
-// positive definite (Y has fewer than r independent columns).
-template <int D, int L>
-__global__ __launch_bounds__(kEigThreads) void rsvd_small_kernel(
-    const float* __restrict__ partials, int nsplit, const int32_t* __restrict__ lengths, int N,
-    float* __restrict__ S, float* __restrict__ V, int32_t* __restrict__ info, int max_sweeps) {
-    using C = EigCfg<D, L>;
-    using SC = SmallCfg<D, L>;
-    constexpr int LD = C::LD, TC = C::TC, LR = SC::LR;
-    extern __shared__ __attribute__((aligned(16))) float smem[];
-    float* Zc = smem;                  // [LP][LD] columns of W, then of W R^-1
-    float* Qc = Zc + SC::zc;           // [LP][LD] singular vectors
-    double* tri = reinterpret_cast<double*>(Qc + SC::qc);
-    float* nrm = reinterpret_cast<float*>(tri) + SC::tri;         // [LP] column norms
-    int* rankv = reinterpret_cast<int*>(nrm + C::LP);             // [LP]
-    double* Rm = tri;                  // [L][LR] Gy, then its Cholesky factor
-    double* inv = Rm + L * LR;         // [L]
-    double* rs = inv + L;              // [L]
-    double* d0 = rs + L;               // [L]
-    __shared__ int sh_bits;
-    __shared__ double sh_scal[1];
-    __shared__ int sh_twist[64];
-    const int tid = threadIdx.x, b = blockIdx.x;
-    const int r = L;
-    auto fail = [&](int code) {
-        for (int e = tid; e < D * r; e += kEigThreads) V[(size_t)b * D * r + e] = 0.f;
-        for (int e = tid; e < r; e += kEigThreads) S[(size_t)b * r + e] = 0.f;
-        if (tid == 0 && info) info[b] = code;
-    };
-    {
-        const int raw = lengths ? lengths[b] : N;
-        if (raw < r || raw > N) { fail(-1); return; }   // uniform over the workgroup
-    }
-    if (tid == 0) sh_bits = 0;
-    constexpr int NB = xty_blocks<D / 16, L / 16>();
-    add_xty_partials<D, L, true, LD, LR, double>(partials + (size_t)b * nsplit * (NB * 256), nsplit, NB, kEigThreads, Zc, Rm);
-    __syncthreads();
-    if (tid < L) d0[tid] = Rm[tid * LR + tid];
-    __syncthreads();
-    // A pivot below 1e-5 of its diagonal entry counts as breakdown: the results would carry a relative error of
-    // about 2^-24 / 1e-5, a percent (Gy is a float sum).
-    if (!cholesky64<L, LR, false>(Rm, inv, rs, d0, 1.0e-5)) { fail(-2); return; }
-    solve_rows64<D, L, LD, LR>(Zc, Rm, inv, rs);
-    int status = 0;
-    // singular values below this share of the largest go the other way: their squares would be short of digits
-    constexpr float kSmallRel = 1.0e-4f;
-    const float* cols = Qc;
-    if (!ritz_rotate<D, L>(Zc, Qc, TriLds<L, L>(tri, reinterpret_cast<double*>(Qc)), sh_scal, sh_twist, nrm, L) ||
-        !(nrm[L - 1] > kSmallRel * nrm[0])) {
-        __syncthreads();
-        cols = Zc;
-        const int col = tid / TC, cu = tid % TC;
-        auto column_norms = [&]() {
-            if (col < L) {
-                const float* z = Zc + col * LD;
-                float nn = 0.f;
-                for (int i = cu; i < D; i += TC) nn += z[i] * z[i];
-                nn = team_sum<TC>(nn);
-                if (cu == 0) { nrm[col] = nn; atomicMax(&sh_bits, __float_as_int(nn)); }
-            }
-            __syncthreads();
-        };
-        // padding columns of the sweeps are zero
-        for (int e = tid; e < (C::LP - L) * LD; e += kEigThreads) Zc[L * LD + e] = 0.f;
-        column_norms();
-        const float dead2 = kDeadRel * kDeadRel * __int_as_float(sh_bits);
-        status = max_sweeps;
-        for (int sw = 0; sw < max_sweeps; ++sw) {
-            const float mine = jacobi_sweep<D, L>(Zc, dead2);
-            const bool any = __syncthreads_or(mine > kSweepDone);
-            if (!any) { status = 0; break; }
-        }
-        column_norms();
-        if (col < L && cu == 0) nrm[col] = __builtin_amdgcn_sqrtf(nrm[col]);
-        __syncthreads();
-    }
-    if (tid < L) {
-        const float th = nrm[tid];
-        int rk = 0;
-        for (int k = 0; k < L; ++k) {
-            const float tk = nrm[k];
-            rk += (tk > th || (tk == th && k < tid)) ? 1 : 0;
-        }
-        rankv[tid] = rk;
-    }
-    __syncthreads();
-    // outputs: columns ranked by norm, normalized, sign fixed by the largest-magnitude entry
-    const int col = tid / TC, cu = tid % TC;
-    if (col < L) {
-        const int k = rankv[col];
-        const float* q = cols + col * LD;
-        float best = -1.f, nn = 0.f;
-        int bi = 0;
-        for (int i = cu; i < D; i += TC) {
-            const float a = fabsf(q[i]);
-            nn += a * a;
-            if (a > best) { best = a; bi = i; }
-        }
-        nn = team_sum<TC>(nn);
-        const float scale = nn > 0.f ? __builtin_amdgcn_rsqf(nn) : 0.f;
-        for (int m = 1; m < TC; m <<= 1) {
-            const float ob = __shfl_xor(best, m);
-            const int oi = __shfl_xor(bi, m);
-            if (ob > best || (ob == best && oi < bi)) { best = ob; bi = oi; }
-        }
-        const float sgn = (q[bi] < 0.f) ? -scale : scale;
-        for (int i = cu; i < D; i += TC) V[((size_t)b * D + i) * r + k] = sgn * q[i];
-        if (cu == 0) S[(size_t)b * r + k] = nrm[col];
-    }
-    if (tid == 0 && info) info[b] = status;
-}
-
-// Re-orthonormalisation of the power-iteration block between two passes over H when Algorithm 1
-// is run as printed: W (d x r, row-major) is replaced by an orthonormal basis of its range.
-// The printed algorithm has no such step; it changes nothing in exact arithmetic (every later
-// quantity depends on the block only through its range), and in float it is what keeps the
-// r columns from collapsing onto the leading singular vector: without it cond(H Omega) grows by
-// (s_1/s_r)^2 per power step.  W R^-1 with the Cholesky factor of W^T W, all in double precision: orthonormal to
-// about 1e-16 cond(W)^2, so one pass is enough where Gram-Schmidt in float took two (64 users, d = 128, r = 32:
-// 17 us instead of 22); columns that vanish are dropped as zeros.
-template <int D, int L>
-__global__ __launch_bounds__(kEigThreads) void orthonormalize_block_kernel(
-    const float* __restrict__ partials, int nsplit, int blocks, float* __restrict__ W) {
-    using C = EigCfg<D, L>;
-    constexpr int LD = C::LD, LR = L + 2;
-    extern __shared__ __attribute__((aligned(16))) float smem[];
-    float* Zc = smem;                                                  // [LP][LD]
-    double* Rm = reinterpret_cast<double*>(Zc + C::LP * LD);           // [L][LR]
-    double* inv = Rm + L * LR;                                         // [L]
-    double* rs = inv + L;                                              // [L]
-    const int tid = threadIdx.x, b = blockIdx.x;
-    add_xty_partials<D, L, false, LD, 1, double>(partials + (size_t)b * nsplit * (blocks * 256), nsplit, blocks,
-                                                 kEigThreads, Zc, nullptr);
-    __syncthreads();
-    gram_columns64<D, L, LD, LR>(Zc, Rm);
-    double top = 0.0;
-    for (int k = 0; k < L; ++k) top = fmax(top, Rm[k * LR + k]);
-    cholesky64<L, LR, true>(Rm, inv, rs, nullptr, (double)kDeadRel * kDeadRel * top);
-    solve_rows64<D, L, LD, LR>(Zc, Rm, inv, rs);
-    float* Wb = W + (size_t)b * D * L;
-    for (int e = tid; e < D * L; e += kEigThreads) Wb[e] = Zc[(e % L) * LD + e / L];
-}
-
-template <int D, int L>
-hipError_t launch_orthonormalize_t(const float* partials, int nsplit, bool gram, float* W, int B, hipStream_t stream) {
-    using C = EigCfg<D, L>;
-    const size_t lds = sizeof(float) * (size_t)C::LP * C::LD + sizeof(double) * ((size_t)L * (L + 2) + 2 * L);
-    auto kern = orthonormalize_block_kernel<D, L>;
-    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(B), dim3(kEigThreads), lds, stream, partials, nsplit,
-                       gram ? xty_blocks<D / 16, L / 16>() : (D / 16) * (L / 16), W);
-    return hipGetLastError();
-}
-
-template <int D, int L>
-hipError_t launch_rsvd_small_t(const float* partials, int nsplit, const int32_t* lengths, int B, int N,
-                               float* S, float* V, int32_t* info, hipStream_t stream) {
-    const size_t lds = sizeof(float) * SmallCfg<D, L>::floats;
-    auto kern = rsvd_small_kernel<D, L>;
-    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(B), dim3(kEigThreads), lds, stream, partials, nsplit, lengths, N, S, V,
-                       info, 30);
-    return hipGetLastError();
-}
-
 template <int D, int L, bool MANY = false>
 hipError_t launch_eig_t(const float* G, const float* partials, int nsplit, const int32_t* lengths, int B, int N,
                         int r, float* S, float* V, int32_t* info, const EigParams& prm, hipStream_t stream) {
@@ -1274,26 +648,6 @@ hipError_t launch_eig(const float* G, const float* partials, int nsplit, const i
         case 256: return launch_eig_d<256>(G, partials, nsplit, lengths, B, N, r, S, V, info, prm, stream);
         default: return hipErrorInvalidValue;
     }
-}
-
-hipError_t launch_orthonormalize_block(const float* partials, int nsplit, bool gram, float* W, int B, int d, int r,
-                                       hipStream_t stream) {
-#define SOLAR_ORTH_CASE(DD, LL) \
-    if (d == DD && r == LL) return launch_orthonormalize_t<DD, LL>(partials, nsplit, gram, W, B, stream);
-    SOLAR_ORTH_CASE(64, 16) SOLAR_ORTH_CASE(64, 32) SOLAR_ORTH_CASE(64, 48) SOLAR_ORTH_CASE(64, 64)
-    SOLAR_ORTH_CASE(128, 16) SOLAR_ORTH_CASE(128, 32) SOLAR_ORTH_CASE(128, 48) SOLAR_ORTH_CASE(128, 64)
-#undef SOLAR_ORTH_CASE
-    return hipErrorInvalidValue;
-}
-
-hipError_t launch_rsvd_small(const float* partials, int nsplit, const int32_t* lengths, int B, int N, int d,
-                             int r, float* S, float* V, int32_t* info, hipStream_t stream) {
-#define SOLAR_RSVD_CASE(DD, LL) \
-    if (d == DD && r == LL) return launch_rsvd_small_t<DD, LL>(partials, nsplit, lengths, B, N, S, V, info, stream);
-    SOLAR_RSVD_CASE(64, 16) SOLAR_RSVD_CASE(64, 32) SOLAR_RSVD_CASE(64, 48) SOLAR_RSVD_CASE(64, 64)
-    SOLAR_RSVD_CASE(128, 16) SOLAR_RSVD_CASE(128, 32) SOLAR_RSVD_CASE(128, 48) SOLAR_RSVD_CASE(128, 64)
-#undef SOLAR_RSVD_CASE
-    return hipErrorInvalidValue;
 }
 
 }  // namespace solar
