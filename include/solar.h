@@ -284,7 +284,8 @@ solar_status solar_gram(const void* X, const int32_t* lengths, int B, int N, int
  *            positive definite (X Omega has fewer than r independent columns: rank(X) < r, or
  *            a degenerate Omega)
  * Supported: d in {64, 128}, r in {16, 32, 48, 64}, r <= d.  Workspace:
- * solar_rsvd_workspace_bytes(B, N, d, r) bytes, 256-byte aligned.
+ * solar_rsvd_workspace_bytes(B, N, d, r) bytes, 256-byte aligned, for either type (B*N*r floats
+ * of them hold X Omega, which bf16 inputs do not store and do not touch).
  */
 size_t solar_rsvd_workspace_bytes(int B, int N, int d, int r);
 solar_status solar_svd_factorize_rsvd(const void* X, const int32_t* lengths, int B, int N, int d,

@@ -271,7 +271,7 @@ solar_status solar_svd_factorize_static(const void* X, const int32_t* lengths, i
 size_t solar_rsvd_workspace_bytes(int B, int N, int d, int r) {
     if (B <= 0 || N <= 0 || d <= 0 || r <= 0 || !rsvd_supported(d, r)) return 0;
     return align256(sizeof(float) * (size_t)B * N * r) + align256(sizeof(float) * (size_t)B * d * r) +
-           align256(sizeof(float) * (size_t)B * r * r) + align256(sizeof(float) * xty_partial_floats(B, N, d, r));
+           align256(sizeof(float) * xty_partial_floats(B, N, d, r));
 }
 
 solar_status solar_svd_factorize_rsvd(const void* X, const int32_t* lengths, int B, int N, int d, int r,
@@ -285,10 +285,10 @@ solar_status solar_svd_factorize_rsvd(const void* X, const int32_t* lengths, int
     const size_t need = solar_rsvd_workspace_bytes(B, N, d, r);
     if (!workspace || workspace_bytes < need || ((uintptr_t)workspace & 255)) return SOLAR_ERR_WORKSPACE;
     char* base = static_cast<char*>(workspace);
-    float* Y = reinterpret_cast<float*>(base);
+    float* Y = reinterpret_cast<float*>(base);   // float inputs only
     base += align256(sizeof(float) * (size_t)B * N * r);
     float* Wb = reinterpret_cast<float*>(base);
-    base += align256(sizeof(float) * (size_t)B * d * r) + align256(sizeof(float) * (size_t)B * r * r);
+    base += align256(sizeof(float) * (size_t)B * d * r);
     float* partials = reinterpret_cast<float*>(base);
     hipStream_t st = (hipStream_t)stream;
     const bool bf16 = t == SOLAR_BF16;
