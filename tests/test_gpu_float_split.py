@@ -64,10 +64,11 @@ def test_gram_float_extreme(d, N, value):
     for b in range(3):
         with np.errstate(invalid="ignore"):
             want, size = x[b].T @ x[b], np.abs(x[b]).T @ np.abs(x[b])
+            error = np.abs(got[b] - want)
         assert np.array_equal(np.isnan(got[b]), np.isnan(want))
         small = size < 0.5 * big
         assert small.sum() >= (d - 1) ** 2
-        assert (np.abs(got[b] - want)[small] <= N * 2.0**-24 * size[small]).all()
+        assert (error[small] <= N * 2.0**-24 * size[small]).all()
         over = np.abs(want) > 1.01 * big
         assert np.array_equal(got[b][over], np.sign(want[over]) * np.inf)
 
@@ -129,4 +130,35 @@ def test_attention_float_extreme(d, r, B, N, M, value, query):
         w = np.exp(s - s.max(1, keepdims=True))
         want = (w / w.sum(1, keepdims=True)) @ p @ v.T
         # scores of magnitude up to 60 in float move a weight by 2^-24 * 60 each way
+        assert np.abs(got[b] - want).max() / np.abs(want).max() < 1e-5
+
+
+@pytest.mark.parametrize("d,r", [(64, 12), (128, 20), (128, 32), (128, 40), (64, 48), (128, 64), (256, 30)])
+@pytest.mark.parametrize("B,N,M", [(44, 700, 700), (64, 520, 1030), (128, 330, 1024)])
+def test_attention_float_two_query_blocks(d, r, B, N, M):
+    """Batches of 256 and more workgroups of 128 queries, where a wave takes two blocks of sixteen queries (with the
+    sequence shared between two groups of waves, and not from 1024 workgroups on): full chunks of 32 ranks, an odd last
+    block, both, ragged, at least three steps of the loop.  A few users against double precision."""
+    torch, sb = _binding()
+    print(f"[case] two query blocks d={d} r={r} B={B} N={N} M={M}", flush=True)
+    rng = np.random.default_rng(r + N)
+    V = np.stack([np.linalg.qr(rng.standard_normal((d, r)))[0] for _ in range(B)]).astype(np.float32)
+    P = rng.standard_normal((B, N, r), dtype=np.float32)
+    Q = rng.standard_normal((B, M, d), dtype=np.float32)
+    lengths = rng.integers(N // 2, N + 1, size=B).astype(np.int32)
+    lengths[0], lengths[1] = N, r
+    for b in range(B):
+        P[b, lengths[b]:] = np.nan
+    scale = 30.0 / (4 * np.sqrt(r) + 8)
+    O = torch.empty((B, M, d), device="cuda")
+    sb.solar_svd_attention(torch.from_numpy(Q).cuda(), torch.ones((B, r), device="cuda"), torch.from_numpy(V).cuda(),
+                           torch.from_numpy(P).cuda(), torch.from_numpy(lengths).cuda(), N, float(scale),
+                           sb.SOLAR_ATTN_SEQ_SOFTMAX, O)
+    got = O.cpu().numpy()
+    assert np.isfinite(got).all()
+    for b in (0, 1, 2, B // 2, B - 1):
+        p, v = P[b, :lengths[b]].astype(np.float64), V[b].astype(np.float64)
+        s = np.float64(np.float32(scale)) * (Q[b].astype(np.float64) @ v) @ p.T
+        w = np.exp(s - s.max(1, keepdims=True))
+        want = (w / w.sum(1, keepdims=True)) @ p @ v.T
         assert np.abs(got[b] - want).max() / np.abs(want).max() < 1e-5
