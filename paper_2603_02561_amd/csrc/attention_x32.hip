@@ -938,10 +938,11 @@ __global__ __launch_bounds__(kThreads) void attention_seq_x32_kernel(
 
 // Which form: rounds of workgroups times the thousands of cycles of one, both measured (one to 24 users, N = 300
 // to 20000).  A block of 32 rows costs a wave 0.6 (0.85 with 64 ranks) in the common form, where eight waves share
-// the conversion of a tile, and 0.95 (1.5) when it converts its own; with the projection in the loop 0.7 to 1.5
-// against 2.1 to 8.5, because every wave then reads all of V from LDS for every block.  The split form pays
-// while its workgroups do not need many more rounds: one user, N = 20000, M = 1000, r = 32 takes 41 us instead of
-// 168 (64 ranks: 58 instead of 223), 24 users 145 instead of 177; 64 users stay in the common form.
+// the conversion of a tile, and 0.95 (1.5, in several rounds 1.6) when it converts its own; with the projection in
+// the loop 0.7 to 1.5 against 2.1 to 8.5, because every wave then reads all of V from LDS for every block.  The split
+// form pays while its workgroups do not need many more rounds: one user, N = 20000, M = 1000, r = 32 takes 41 us
+// instead of 168 (64 ranks: 58 instead of 223), 24 users 145 instead of 177; 64 users stay in the common form, and so
+// do four with N = 40000, M = 6500, 64 ranks (482 to 495 split, 442).
 inline int rounds_of(int B, int mtiles) {
     return B < 8 ? ceil_div(B * mtiles, 256) : ceil_div(ceil_div(B, 8) * mtiles, 32);
 }
@@ -949,8 +950,9 @@ template <int D, int RP, bool FUSED>
 bool split_pays(int B, int N, int M) {
     const double blocks = ceil_div(N, 32);
     const double block = FUSED ? (RP == 32 ? 0.4 + D / 230.0 : 0.7 + D / 180.0) : (RP == 32 ? 0.6 : 0.85);
-    const double block_split = FUSED ? RP / 32 * (D / 30.5) : (RP == 32 ? 0.95 : 1.5);
-    return rounds_of(B, ceil_div(M, kQW)) * (30.0 + block_split * blocks / kWaves) <
+    const int rounds = rounds_of(B, ceil_div(M, kQW));
+    const double block_split = FUSED ? RP / 32 * (D / 30.5) : (RP == 32 ? 0.95 : (rounds > 1 ? 1.6 : 1.5));
+    return rounds * (30.0 + block_split * blocks / kWaves) <
            rounds_of(B, ceil_div(M, kWaves * kQW)) * (23.0 + block * blocks);
 }
 
