@@ -328,7 +328,7 @@ def main() -> int:
         "exponentials": n_exp, "peak_Texp_per_s": exp_peak,
         "alone": {"achieved": n_exp / (solo["attention"] * 1e-3) / 1e12,
                   "frac": n_exp / (solo["attention"] * 1e-3) / 1e12 / exp_peak}}
-    kernels["eig"] = {"kernel": kernel_names["eig"], "bound": "latency (serial Jacobi rounds, one "
+    kernels["eig"] = {"kernel": kernel_names["eig"], "bound": "latency (dependent steps, one "
                       "workgroup per user; no roofline)", "pipelined": {"ms": eig_ms},
                       "alone": {"ms": solo["eig"]}}
     # dominant kernel = the roofline-bound kernel with the most GPU time

@@ -20,6 +20,8 @@
  *     out of every softmax, whatever they contain.
  *   - X and Q have element type `t` (float or bf16 bit patterns); every output
  *     is float.
+ *   - Float inputs: the matrix products keep 24 bits of every value from 2^-110 (8e-34) up;
+ *     smaller ones keep fewer (relative error 3e-5 at 1e-36).
  *   - Supported shapes: d in {64, 128, 256}; 1 <= r <= min(d, 64) (r <= 32 when
  *     d = 256); N, M, B >= 1.  Anything else returns SOLAR_ERR_UNSUPPORTED.
  *   - Errors: a status code is returned, nothing is printed and nothing aborts.
@@ -83,7 +85,9 @@ solar_status solar_info_status(const int32_t* info_host, int B);
  * without an input built to provoke it.  Not for production use; both are off (0) at start.
  *   SOLAR_DEBUG_EIG_MAX_ITER        value > 0 caps the power steps of the eigen-iteration in
  *                                   solar_svd_factorize (users that hit the cap report it in
- *                                   `info`); 0 restores the default cap of 40
+ *                                   `info`) and makes wide ranks, which are solved directly
+ *                                   otherwise, take the iteration too; 0 restores the default
+ *                                   cap of 40 and the direct solution
  *   SOLAR_DEBUG_FORCE_GUARDED_PASS  nonzero makes the fp16 attention kernel of mode 0 skip its
  *                                   optimistic pass and walk the sequence with the guarded pass
  *                                   (the one that moves the softmax reference) straight away
@@ -189,9 +193,10 @@ solar_status solar_svd_attention(const void* Q, const float* S, const float* V, 
  * "SVD-Attention", the product U Sigma that replaces U) is formed tile by tile inside the attention
  * kernel and never written, so solar_svd_factorize can be called with P = NULL:
  *   O = softmax_n(scale * (Q V) (X V)^T) (X V) V^T   over the rows n < lengths[b].
- * Every workgroup of a user repeats that user's projection (ceil(M/256) times in all); the call
- * pays when the factors are used for one candidate set, solar_svd_attention with a stored P when
- * they are used for many.
+ * Every workgroup of a user repeats that user's projection: ceil(M/256) times in all, or ceil(M/32)
+ * times where few users would leave most of the GPU idle and a workgroup takes 32 queries.  The
+ * call pays when the factors are used for one candidate set, solar_svd_attention with a stored P
+ * when they are used for many.
  *   Q  in [B,M,d] bf16     X  in [B,N,d] bf16     S, V  in  as written by solar_svd_factorize
  *   O  out [B,M,d] float
  * Supported: t = SOLAR_BF16, d in {64, 128, 256}, r a multiple of 4, r <= 64 (r <= 32 when d = 256),

@@ -21,6 +21,7 @@
 // hundred vector instructions per 64 rows).  B = 32, N = 4096, M = 512,
 // d = 128, r = 16: 64.8 -> 61.2 us, 58.2 with the loads two steps ahead; B = 64, N = 1500, M = 1200, r = 64: 422 -> 289 -> 274; errors against double precision fall
 // from 7.7e-7 to 5.8e-7 (geometric mean over twelve shapes).
+// Values of P or Qt below 2^-110 keep fewer bits (there is no bf16 below 2^-133).
 // The products with V in the prologue and the epilogue stay on the float instruction.
 //
 // attention_tokens_kernel -- the literal r-token form, with or without softmax:
@@ -340,7 +341,7 @@ __global__ __launch_bounds__(64 * QG * NS) void attention_seq_kernel(
     // A value of P above 3.39e38 makes its scores NaN, and so can a product that overflows (its terms have different signs)
     // where the float product is an infinity and its weight zero.  A wave whose sums are not finite
     // walks its share again on the float instruction, P read from memory and Qt put together again.  The loop above is
-    // the same instruction for instruction (72 shapes: 0.998 of the time on average, 0.86 to 1.04 by register count).
+    // the same instruction for instruction (72 shapes: 1.000 of the time on average, 0.86 to 1.04 by register count).
     bool finite = true;
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {

@@ -60,7 +60,8 @@ static hipError_t gram_allow_lds(K kern, size_t bytes) {
 // are not below 2^-25 of it, smallest first, in float accumulators.  Six products over 32 rows take 96 cycles
 // of the matrix unit where the float instruction takes 256, and round an accumulator once per 32 rows instead
 // of once per four.  B = 32, N = 4096, d = 128 (67 MB): 26.6 -> 20.1 us; B = 64, N = 2048, d = 256: 200 -> 117 us.  Errors against
-// double precision are smaller (7.3e-8 -> 6.4e-8 of the norm, geometric mean over 30 batches).
+// double precision are smaller (7.3e-8 -> 6.4e-8 of the norm, geometric mean over 30 batches).  Values below 2^-110
+// keep fewer bits: there is no bf16 below 2^-133.
 template <int CPL>
 struct SplitFrags {
     v4u term[3][CPL];   // [term][column fragment]: the lane's eight rows

@@ -6,12 +6,13 @@
 // Both are Out[rows x d] = scale * In[rows x d] * W[d x d] with a float matrix W, per user or shared.
 //
 // Bound by memory.  W is split once per workgroup into three bf16 matrices that add up to it exactly (24
-// bits) and kept in LDS; the products run on the 32x32x16 bf16 instruction with float accumulation.  A bf16
+// bits; fewer for values below 2^-110, whose terms are below the smallest bf16) and kept in LDS; the products run on the
+// 32x32x16 bf16 instruction with float accumulation.  A bf16
 // row takes three of them, each product exact; a float row is split the same way and takes the six whose
 // size is above 2^-24 of the leading one, which is the rounding of a float product.  That is a third (or
 // two thirds) of the time of the float instruction for the same precision: 64000 rows of d = 128 take
-// 12.6 us from bf16 to bf16 (2.6 TB/s) and 21.3 from float to float, of d = 256 33.9 and 62.1; with the
-// float instruction, 16 rows per wave and a copy of W per 64 rows 31.5, 38.5, 154.9 and 189.4.
+// 12.6 us from bf16 to bf16 (2.6 TB/s) and 22 from float to float, of d = 256 35 and 62; with the
+// float instruction, 16 rows per wave and a copy of W per 64 rows 31.5, 38.5, 155 and 189.
 #include "common.h"
 #include "kernels.h"
 

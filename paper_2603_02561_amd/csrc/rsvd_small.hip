@@ -93,7 +93,7 @@ struct SmallCfg {
 // vectors of Q^T H are those of (Q^T H)^T = W R^-1, from the eigenpairs of its Gram matrix in double precision
 // (ritz_rotate; one-sided Jacobi sweeps where two of its eigenvalues are too close for that route, or one is
 // too small).  One workgroup per user, all of it in LDS.  The time is that of its dependent chains (64 users, d = 128,
-// r = 32: 64 us, where float Cholesky with four barriers a column and the sweeps took 87).
+// r = 32: 60 us, where float Cholesky with four barriers a column and the sweeps took 87).
 // info: 0 ok, > 0 Jacobi sweeps exhausted, -1 bad length, -2 Gy is not numerically
 // positive definite (Y has fewer than r independent columns).
 template <int D, int L>
@@ -213,7 +213,7 @@ __global__ __launch_bounds__(kEigThreads) void rsvd_small_kernel(
 // r columns from collapsing onto the leading singular vector: without it cond(H Omega) grows by
 // (s_1/s_r)^2 per power step.  W R^-1 with the Cholesky factor of W^T W, all in double precision: orthonormal to
 // about 1e-16 cond(W)^2, so one pass is enough where Gram-Schmidt in float took two (64 users, d = 128, r = 32:
-// 17 us instead of 22); columns that vanish are dropped as zeros.
+// 18 us instead of 22); columns that vanish are dropped as zeros.
 template <int D, int L>
 __global__ __launch_bounds__(kEigThreads) void orthonormalize_block_kernel(
     const float* __restrict__ partials, int nsplit, int blocks, float* __restrict__ W) {
