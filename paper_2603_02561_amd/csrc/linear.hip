@@ -238,14 +238,15 @@ hipError_t launch_d(const void* In, const float* W, size_t w_stride, int B, int 
     // one workgroup per compute unit (the images of W take more than half of its LDS), none without a block
     // of rows for every wave
     constexpr int NZ = D / C::NC;
-    const int want = ceil_div(ceil_div(rows, 32), kRowWaves), room = ceil_div(256, B * NZ);
-    dim3 grid(want < room ? want : room, B, NZ), block(kRowWaves * 64);
     const bool in_place = NZ > 1 && In == Out && in_bf16 == out_bf16;
+    const int nz = in_place ? 1 : NZ;
+    const int want = ceil_div(ceil_div(rows, 32), kRowWaves), room = ceil_div(256, B * nz);
+    const dim3 grid(want < room ? want : room, B, nz), block(kRowWaves * 64);
 #define SOLAR_ROWGEMM(IB, OB)                                                                        \
     do {                                                                                             \
         auto kern = rowgemm_kernel<D, IB, OB, false>;                                                \
         if constexpr (NZ > 1 && IB == OB) {                                                          \
-            if (in_place) { kern = rowgemm_kernel<D, IB, OB, true>; grid.z = 1; }                    \
+            if (in_place) kern = rowgemm_kernel<D, IB, OB, true>;                                    \
         }                                                                                            \
         hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), C::lds_bytes);         \
         if (e != hipSuccess) return e;                                                               \
