@@ -13,16 +13,18 @@
 // orthogonal diagonalizes Q^T G^2 Q, which is the Rayleigh-Ritz step for G^2 on span(Q), and
 // the normalized columns are the next orthonormal basis.  ritz_rotate does it through the
 // eigenvectors of Z^T Z in double precision; the narrowest blocks and those with coinciding
-// eigenvalues take one-sided (Hestenes) Jacobi sweeps over the columns of Z.  Both are insensitive
+// eigenvalues take one-sided (Hestenes) Jacobi sweeps over the columns of Z, and so does d = 64, r = 9 .. 16 with more
+// users than compute units.  Both are insensitive
 // to the huge dynamic range of the block (G Omega is dominated by the leading
 // eigenvectors) and to rank deficiency (columns that vanish are dropped).  The power
 // step after a Jacobi phase yields the residuals |G q_i - theta_i q_i| of the Ritz
 // pairs; the iteration ends when every wanted pair is below tol_res * theta_max, and a
 // failed check doubles the number of Gram-Schmidt steps before the next Jacobi phase.
 //
-// The phase is bound by latency, not by throughput: a Jacobi sweep is L-1 rounds of
-// L/2 independent column rotations with a workgroup barrier after each round.  The
-// kernel runs eight waves (two per SIMD), gives every column pair a team of up to 16
+// The phase is bound by latency, not by throughput: Gram-Schmidt passes, the reduction of the dense solver and
+// Jacobi sweeps are chains of dependent steps with a workgroup barrier after each (d = 128, 40 columns, thousands of cycles:
+// staging and start 18, four products 33, two Gram-Schmidt passes 53, Ritz step 119, checks and output 28).  The
+// kernel runs eight waves (two per SIMD), gives every column pair of a sweep a team of up to 16
 // lanes whose partial dot products are combined with DPP lane permutations, and keeps
 // every trip count a compile-time constant.
 #include "column_block.h"

@@ -39,6 +39,7 @@ int eig_block_columns(int d, int r);
 hipError_t launch_eig(const float* G, const float* partials, int nsplit, const int32_t* lengths, int B, int N,
                       int d, int r, float* S, float* V, int32_t* info, const EigParams& prm, hipStream_t stream);
 
+// rsvd_small.hip
 // The small problems of Algorithm 1 (rsvd shapes only), from partial blocks of nsplit chunks per user (xty_partials.h):
 // W [B][d][r] <- an orthonormal basis of the range of each user's H^T Y; `gram` says whether a chunk also holds
 // the blocks of Y^T Y, which launch_rsvd_small needs
