@@ -74,6 +74,40 @@ struct TriLds {
     }
 };
 
+// The iterate in registers: wave w holds the rows of the blocks w, w + 8 of 16 (d = 64: waves 4 .. 7 hold none),
+// lane (i, g) = (l % 16, l / 16) of block n the rows 4 g + t of column 16 c + i in component t of [n][c].  That is how the
+// matrix unit leaves a product, and it is an operand as it stands wherever rows are contracted (the order of a
+// contraction is free).
+template <int D, int LP>
+struct Iterate {
+    static constexpr int NB = D > 128 ? D / 128 : 1, NC = LP / 16;
+    static constexpr int W = min_c(kEigWaves, D / 16);   // waves that hold rows
+    static constexpr int LDI = D + 8;                    // bf16 elements per column of an image
+    typedef v4f Regs[NB][NC];
+};
+
+// LDS of one pass over the panels of a block (basis_panels in eig.hip), in floats at `base`
+template <int D, int LP>
+struct BasisLds {
+    using I = Iterate<D, LP>;
+    static constexpr int kT = 20;                        // row stride of the 16 x 16 blocks that change hands
+    static constexpr size_t gram = (size_t)I::W * 512, part = (size_t)I::W * (I::NC - 1) * 256, sum = (I::NC - 1) * 256;
+    static constexpr size_t floats = gram + 512 + part + sum + 16 * kT + (size_t)I::W * I::NB * 16 * kT;
+    double* gm;        // [W][16][16] the waves' shares of the panel's Gram matrix
+    double* gs;        // [16][16] their sum
+    float *cp, *cs;    // [W][NC-1][256] shares of Qp^T Z, [NC-1][256] their sums
+    float* tm;         // [16][kT] per column the multipliers of the elimination and the reciprocal of the norm
+    float* tr;         // [W][NB][16][kT] the wave's rows of the panel, rows first
+    __device__ __forceinline__ explicit BasisLds(float* base) {
+        gm = reinterpret_cast<double*>(base);
+        gs = gm + I::W * 256;
+        cp = base + gram + 512;
+        cs = cp + part;
+        tm = cs + sum;
+        tr = tm + 16 * kT;
+    }
+};
+
 // MANY: for batches of more users than compute units
 template <int D, int L, bool MANY = false>
 struct EigCfg {
@@ -81,10 +115,13 @@ struct EigCfg {
     static constexpr int LD = D + 4;
     // lanes per column outside the Jacobi rounds
     static constexpr int TC = min_c(min_c(64, D), pow2floor_c(kEigThreads / L));
-    // G is staged in LDS when it fits beside the two iterate blocks
+    // G is staged in LDS when it fits, on its way to registers or to the direct solution
     static constexpr bool GLDS = D <= 128;
-    static constexpr int GS = GLDS ? D + 4 : D;
-    static constexpr size_t base_floats = (size_t)2 * LP * LD + 3 * LP + 8 + (GLDS ? (size_t)D * GS : 0);
+    static constexpr int GS = D + 4;
+    // two blocks of columns, or the images of one
+    static constexpr size_t x_floats = (size_t)2 * LP * LD;
+    static_assert(2 * x_floats >= (size_t)3 * LP * (D + 8), "three images of 16-bit values");
+    static constexpr size_t base_floats = x_floats + 4 * LP;
     // Wide blocks are solved directly: the reduction of the whole matrix is then cheaper than the
     // power steps, Gram-Schmidt passes and Ritz steps of the iteration, and takes the same time for every
     // spectrum (16 users, d = 128, r = 64: 214 us per launch, where iterating took 360 for
@@ -101,8 +138,10 @@ struct EigCfg {
     static constexpr size_t ritz_floats = ritz ? 2 * TriLds<ritz ? L : 16, ritz ? L : 16>::kDoublesNoWa : 0;
     static constexpr int RB = D == 128 || L <= 40 ? 32 : 64;   // eigenvectors per pass of the direct solution
     static constexpr size_t direct_floats = direct ? 2 * TriLds<direct ? D : 16, RB>::kDoubles : 0;
-    static constexpr size_t lds_floats =
-        base_floats + ritz_floats > direct_floats ? base_floats + ritz_floats : direct_floats;
+    static constexpr size_t scratch_floats = ritz_floats > BasisLds<D, LP>::floats ? ritz_floats : BasisLds<D, LP>::floats;
+    static constexpr size_t stage_floats = GLDS ? (size_t)D * GS : 0;
+    static constexpr size_t own_floats = base_floats + scratch_floats > stage_floats ? base_floats + scratch_floats : stage_floats;
+    static constexpr size_t lds_floats = own_floats > direct_floats ? own_floats : direct_floats;
     // Workgroups that registers and LDS let share a compute unit, which is what counts with more users than compute
     // units: the waves of one fill the gaps in the chains of the others.  1024 users at d = 64: r = 8 137 us with one, 84 with
     // six; r = 24, direct, 279 and 197 with two (where iterating takes 168 for inputs of rank r, 215 to 290 for
@@ -225,7 +264,7 @@ __device__ __forceinline__ float jacobi_sweep(float* Zc, float dead2) {
     using J = JacobiCfg<D, L>;
     constexpr int T = J::T, G = J::G, CH = J::CH, LD = EigCfg<D, L>::LD;
     constexpr bool NB = T == 16;   // measured: teams of 16 lanes gain from it, teams of 8 lose
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = fresh_tid(), lane = tid & 63, wave = tid >> 6;
     const int u = tid % T;
     float offmax = 0.f;
     v4f a[CH], c[CH];
@@ -302,7 +341,7 @@ constexpr double kTriZero = 1.0e-80;
 template <int D, int L, int LD, int LG>
 __device__ __forceinline__ void gram_columns64(const float* Zc, double* Gm) {
     constexpr int NT = (L + 15) / 16;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tid = fresh_tid(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i16 = lane & 15, g = lane >> 4;
     for (int p = wave; p < NT * (NT + 1) / 2; p += kEigWaves) {
         int I = 0, rest = p;
@@ -335,8 +374,11 @@ template <int D, int N>
 __device__ __forceinline__ bool ritz_rotate(const float* Zc, float* Qc, const TriLds<N, N>& w, double* scal, int* twist,
                                             float* sig, int wanted) {
     using T = TriCfg<N, N>;
+    // stride of the columns of W: a multiple of 16 would put 16 lanes on four banks
+    constexpr int LW = N + 2;
+    static_assert(LW * N <= T::WB, "W in a work array");
     constexpr int LD = D + 4, NT = (N + 15) / 16;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tid = fresh_tid(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i16 = lane & 15, g = lane >> 4;
     double* Cm = w.wa;
     gram_columns64<D, N, LD, N>(Zc, Cm);
@@ -367,18 +409,20 @@ __device__ __forceinline__ bool ritz_rotate(const float* Zc, float* Qc, const Tr
         const double l = w.lam[v], rs = l > dead ? rsq64(l * bound) : 0.0;
         if (u == 0) sig[v] = (float)(l > 0.0 ? l * bound * rsq64(l * bound) : 0.0);
 #pragma unroll
-        for (int q = 0; q < N / TB; ++q) w.wb[v * N + TB * q + u] = l > dead ? y[q] * rs : 0.0;
+        for (int q = 0; q < N / TB; ++q) w.wb[v * LW + TB * q + u] = l > dead ? y[q] * rs : 0.0;
     }
     __syncthreads();
     for (int J = wave; J < D / 16; J += kEigWaves) {
+        double zr[N / 4];
+#pragma unroll
+        for (int k = 0; k < N / 4; ++k) zr[k] = (double)Zc[(4 * k + g) * LD + 16 * J + i16];
 #pragma unroll
         for (int I = 0; I < NT; ++I) {
-            const bool in = 16 * I + i16 < N;
-            const double* wr = w.wb + (in ? 16 * I + i16 : 0) * N + g;
-            const float* zr = Zc + g * LD + 16 * J + i16;
+            const bool in = 16 * I + 15 < N || 16 * I + i16 < N;
+            const double* wr = w.wb + (in ? 16 * I + i16 : 0) * LW + g;
             v4d acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-            for (int k0 = 0; k0 < N; k0 += 4) acc = mfma16x16x4f64(in ? wr[k0] : 0.0, (double)zr[k0 * LD], acc);
+            for (int k = 0; k < N / 4; ++k) acc = mfma16x16x4f64(in ? wr[4 * k] : 0.0, zr[k], acc);
 #pragma unroll
             for (int t = 0; t < 4; ++t) Qc[(16 * I + g + 4 * t) * LD + 16 * J + i16] = (float)acc[t];
         }

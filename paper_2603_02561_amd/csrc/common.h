@@ -53,6 +53,14 @@ __device__ __forceinline__ float wave_xor_max(float v, int mask) {
     return fmaxf(v, __shfl_xor(v, mask));
 }
 
+// threadIdx.x, as a value that the compiler takes for new: the addresses that a phase derives from it are formed
+// there, in a few instructions, and not ahead of the loop around it, from where dozens of them went to scratch.
+__device__ __forceinline__ int fresh_tid() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
 // Valid length of user b clamped to [0, N].
 __device__ __forceinline__ int user_len(const int32_t* lengths, int b, int N) {
     int len = lengths ? lengths[b] : N;

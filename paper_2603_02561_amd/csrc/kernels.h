@@ -29,13 +29,13 @@ struct EigParams {
     float tol_orth;     // a sweep whose largest |cos| is below this ends the Jacobi phase
     int max_iter;       // cap on power steps
     int sweeps;         // cap on Jacobi sweeps per power step
-    int mgs_steps;      // leading power steps that use a Gram-Schmidt pass instead of a Ritz step
+    int mgs_steps;      // leading power steps after which only a basis is taken instead of a Ritz step
     bool direct;        // wide blocks: solve G itself instead of iterating
 };
 EigParams eig_default_params();
 int eig_block_columns(int d, int r);
 // partials != nullptr (with nsplit blocks per user, the layout gram_partial_kernel writes):
-// G is not read, the kernel sums the partial blocks itself
+// G is not read, the kernel sums the partial blocks itself; d <= 128 takes them and nothing else
 hipError_t launch_eig(const float* G, const float* partials, int nsplit, const int32_t* lengths, int B, int N,
                       int d, int r, float* S, float* V, int32_t* info, const EigParams& prm, hipStream_t stream);
 

@@ -90,7 +90,7 @@ struct TriCfg {
     // exchange buffers: partial products [2][waves][PS] and the rows that hold the next pivot [2][16][PS]
     static constexpr int EX = (2 * kTriWaves + 32) * PS;
     static constexpr int WA = N * RB;
-    static constexpr int WB = (N * RB > EX) ? N * RB : EX;
+    static constexpr int WB = (N * (RB + 2) > EX) ? N * (RB + 2) : EX;
     static constexpr int VEC = 6 * N + 16 + 64;        // d, e, 1/h, scaled e, (d, e^2) and a chunk, lambda
     static_assert(N % 8 == 0 && N >= 16 && N <= 128, "multiples of eight");
 };
@@ -241,13 +241,13 @@ __device__ __forceinline__ void tri_reduce(TriRows<N>& a, double* ex, double* U,
                                            double* dd, double* ee, double* ih) {
     using T = TriCfg<N, 8>;
     constexpr int NC = T::NC, PS = T::PS, W = kTriWaves;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tid = fresh_tid(), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (wave >= W) {
 #pragma unroll 1
         for (int k = 0; k < N; ++k) __syncthreads();    // one for the first row, N - 2 steps, one at the end
         return;
     }
-    const int col = (threadIdx.x & 63) ^ (4 * wave);
+    const int col = (tid & 63) ^ (4 * wave);
     double* row0 = ex + (2 * W + 16) * PS;
     if (wave == 0) {
 #pragma unroll
@@ -339,7 +339,7 @@ __device__ __forceinline__ void sturm_count_ge(const double2* t, double la, doub
 template <int N, int TP>
 __device__ __forceinline__ double tri_values(const double* dd, const double* ee, double* es, double2* t, double* lam,
                                              double* scal, int* cnt, int R) {
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int tid = fresh_tid(), lane = tid & 63;
     if (tid < 64) {
         double bmax = 0.0;
         for (int i = lane; i < N; i += 64)
@@ -411,7 +411,7 @@ __device__ __forceinline__ void tri_factor(const double2* t, const double* es, d
 template <int N, int RB>
 __device__ __forceinline__ void tri_vectors(const double2* t, const double* es, const double* lam, double* wa,
                                             double* wb, int* twist, int v0, int nb) {
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int tid = fresh_tid(), lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (wave == 0) {
         if (lane < nb) tri_factor<N, RB, 1>(t, es, lam[v0 + lane], wa + lane);
@@ -484,7 +484,7 @@ __device__ __forceinline__ void tri_load(const double* wa, int v, int u, double 
 // cross[k] = u_k . u_(k+1) of the reflectors in U, for k = 0 .. N - 4, one team of eight lanes each.
 template <int N>
 __device__ __forceinline__ void tri_cross(const double* U, double* cross) {
-    const int team = threadIdx.x >> 3, s = threadIdx.x & 7;
+    const int tid = fresh_tid(), team = tid >> 3, s = tid & 7;
     for (int k = team; k < N - 3; k += kTriThreads / 8) {
         const double *uk = U + tri_row(N, k), *ul = U + tri_row(N, k + 1);
         double d = 0.0;

@@ -57,6 +57,23 @@ def test_routes(lib, d, r, noise):
     check(X, *factors(lib, X, r), r)
 
 
+# the orthonormal basis is taken in panels of 16 columns of a block of r + 8 (rounded up to 8): ranks that end inside a
+# panel, with it and in the next one, blocks of one to three panels, the last of 8 or 16 columns
+@pytest.mark.parametrize("d,r,ranks", [(64, 8, (3, 8)), (64, 16, (1, 16)), (128, 8, (2, 7)), (128, 16, (5, 15)), (128, 24, (16, 17)),
+                                       (128, 32, (15, 16, 31)), (128, 40, (17, 32, 33)), (256, 32, (5, 16, 17))])
+@pytest.mark.parametrize("size", [2.0 ** -12, 1.0, 2.0 ** 12])
+def test_rank_below_r(lib, d, r, ranks, size):
+    g = np.random.default_rng(d + r)
+    print(f"[case] ranks {ranks} d={d} r={r} size={size}", flush=True)
+    X = np.empty((len(ranks), 600, d), dtype=np.float32)
+    for b, k in enumerate(ranks):
+        X[b] = size * (g.standard_normal((600, k)) / (1.0 + np.arange(k)) ** 0.5) @ g.standard_normal((k, d))
+    info, S, V = factors(lib, X, r)
+    check(X, info, S, V, r)
+    for b, k in enumerate(ranks):
+        assert np.all(S[b][k:] < 4e-3 * S[b][0])      # what is left is the rounding of X and G
+
+
 @pytest.mark.parametrize("d,r", [(64, 12), (64, 40), (128, 24), (128, 64), (256, 16)])
 def test_coinciding_eigenvalues(lib, d, r):
     """Rows that are unit vectors: G is diagonal with integer entries, several of them equal."""
