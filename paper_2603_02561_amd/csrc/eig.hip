@@ -256,12 +256,7 @@ __device__ __forceinline__ int rank_of(const float* v, int e, float& top) {
     return (int)team_sum<8>((float)rk);
 }
 
-// a += x[lane I of the row of 16 lanes] * y
-template <int I>
-__device__ __forceinline__ void fmac_bcast64(double& a, double x, double y) {
-    asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(a) : "v"(x), "v"(y), "n"(I));
-}
-// the same in float, with x = a
+// a += a[lane I of the row of 16 lanes] * y
 template <int I>
 __device__ __forceinline__ void fmac_own_bcast(float& a, float y) {
     a = fmaf(__int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(a), 0x150 + I, 0xf, 0xf, true)), y, a);
@@ -276,7 +271,10 @@ __device__ __forceinline__ void fmac_own_bcast(float& a, float y) {
 // the vector ALU's doubles share, for 64 cycles: 280 to 440 cycles a step, 150 this way.
 template <int I, int KN, int K>
 __device__ __forceinline__ void eliminate_rows(double (&a)[16], double nra) {
-    if constexpr (I < KN) {
+    if constexpr (I + 3 < KN) {
+        fmac_bcast64<I>(a[I], a[I + 1], a[I + 2], a[I + 3], a[K], nra);
+        eliminate_rows<I + 4, KN, K>(a, nra);
+    } else if constexpr (I < KN) {
         fmac_bcast64<I>(a[I], a[K], nra);
         eliminate_rows<I + 1, KN, K>(a, nra);
     }
@@ -285,7 +283,6 @@ template <int K, int KN>
 __device__ __forceinline__ void panel_steps(double (&a)[16], float (&m)[16], double dead2) {
     if constexpr (K + 1 < KN) {
         const double piv = readlane64(a[K], K);
-        // (the broadcasts read a[K] at the earliest five instructions after it was written, which they need)
         const double nra = a[K] * (piv > dead2 ? -rcp64(piv) : 0.0);
         eliminate_rows<K + 1, KN, K>(a, nra);
         m[K] = (float)nra;
@@ -463,8 +460,8 @@ __device__ __forceinline__ bool eig_direct(const float* Gs, double* sm, double* 
         __syncthreads();
     }
     tri_cross<D>(w.U, w.dd);
-    float* out = reinterpret_cast<float*>(w.wa);         // [D][r]
-    static_assert(2 * T::WA >= D * RMAX, "V in a work array");
+    float* out = reinterpret_cast<float*>(w.wb);         // [D][r + 1]
+    static_assert(2 * T::WB >= D * (RMAX + 1), "V in a work array");
     if (v < r) {
         tri_back<D, TB>(w.U, w.ih, w.dd, u, y);
         const double l = w.lam[v];
@@ -477,13 +474,15 @@ __device__ __forceinline__ bool eig_direct(const float* Gs, double* sm, double* 
         for (int m = 1; m < TB; m <<= 1) best = max(best, (uint64_t)__shfl_xor((unsigned long long)best, m));
         const float sgn = (best & 1) ? -1.f : 1.f;
 #pragma unroll
-        for (int q = 0; q < D / TB; ++q) out[eig_row<D>(TB * q + u) * r + v] = live ? sgn * (float)y[q] : 0.f;
+        for (int q = 0; q < D / TB; ++q) out[eig_row<D>(TB * q + u) * (r + 1) + v] = live ? sgn * (float)y[q] : 0.f;
         if (u == 0) S[v] = live ? (float)(l * bound * rsq64(l * bound)) : 0.f;
     }
-    // by way of LDS, in whole lines (16 users, d = 64, r = 20: 1.5 us less than the lanes' own stores)
+    // by way of LDS, a row of V to a wave (16 users, d = 64, r = 20: 1.5 us less than the lanes' own stores)
     __syncthreads();
-    for (int e = tid; e < D * r / 4; e += kEigThreads)
-        reinterpret_cast<v4f*>(V)[e] = reinterpret_cast<const v4f*>(out)[e];
+    if (lane < r) {
+#pragma unroll 4
+        for (int i = wave; i < D; i += kEigWaves) V[(size_t)i * r + lane] = out[i * (r + 1) + lane];
+    }
     return true;
 }
 

@@ -2,9 +2,9 @@
 // Householder tridiagonalization, multisection on Sturm counts for the wanted eigenvalues, twisted
 // factorizations for their eigenvectors, and the reflectors applied backwards.
 //
-// The phase is bound by the length of its dependent chain, not by arithmetic: one Householder step is
-// two wave-wide sums, a reciprocal square root, a reciprocal, and one exchange of partial sums between
-// the waves.  Double precision costs nothing against float here (a v_fma_f64 issues like a v_fma_f32,
+// The phase is bound by instructions, not by arithmetic: a wave issues one in five cycles whatever it is, and one Householder
+// step is some two hundred, of which the two wave-wide sums, the reciprocals and the exchange of partial sums between
+// the waves are the part that all waves repeat.  Double precision costs nothing against float here (a v_fma_f64 issues like a v_fma_f32,
 // 9 cycles dependent and 5 independent, measured) except in the wave sums, and it is what lets the
 // eigenvectors be computed independently of each other: their mutual orthogonality is about
 // 1e-15 / gap, where gap is the distance of neighbouring eigenvalues relative to the norm.
@@ -39,6 +39,38 @@ __device__ __forceinline__ double readlane64(double v, int lane) {
     x.d = v;
     y.i[0] = __builtin_amdgcn_readlane(x.i[0], lane);
     y.i[1] = __builtin_amdgcn_readlane(x.i[1], lane);
+    return y.d;
+}
+
+// a_k += x[lane I + k of the row of 16 lanes] * y: the broadcast is an operand of the multiply-add.  It may not read what
+// the vector ALU wrote in the last two instructions, which the compiler does not see to in here: hence the wait in front, and
+// one statement for four (or eight) of them.
+#define SOLAR_FMAC_BCAST(A, X, Y, I) "v_fmac_f64_dpp %" #A ", %" #X ", %" #Y " row_newbcast:%" #I " row_mask:0xf bank_mask:0xf\n\t"
+template <int I>
+__device__ __forceinline__ void fmac_bcast64(double& a0, double x, double y) {
+    asm("s_nop 1\n\t" SOLAR_FMAC_BCAST(0, 1, 2, 3) : "+v"(a0) : "v"(x), "v"(y), "n"(I));
+}
+template <int I>
+__device__ __forceinline__ void fmac_bcast64(double& a0, double& a1, double& a2, double& a3, double x, double y) {
+    asm("s_nop 1\n\t" SOLAR_FMAC_BCAST(0, 4, 5, 6) SOLAR_FMAC_BCAST(1, 4, 5, 7) SOLAR_FMAC_BCAST(2, 4, 5, 8) SOLAR_FMAC_BCAST(3, 4, 5, 9)
+        : "+v"(a0), "+v"(a1), "+v"(a2), "+v"(a3)
+        : "v"(x), "v"(y), "n"(I), "n"(I + 1), "n"(I + 2), "n"(I + 3));
+}
+// p += the sum of x[lane I + k of the row of 16 lanes] * y_k
+template <int I>
+__device__ __forceinline__ void fmac_bcast64_sum(double& p, double x, double y0, double y1, double y2, double y3) {
+    asm("s_nop 1\n\t" SOLAR_FMAC_BCAST(0, 1, 2, 6) SOLAR_FMAC_BCAST(0, 1, 3, 7) SOLAR_FMAC_BCAST(0, 1, 4, 8) SOLAR_FMAC_BCAST(0, 1, 5, 9)
+        : "+v"(p)
+        : "v"(x), "v"(y0), "v"(y1), "v"(y2), "v"(y3), "n"(I), "n"(I + 1), "n"(I + 2), "n"(I + 3));
+}
+#undef SOLAR_FMAC_BCAST
+
+// v of the lane whose number is byte / 4
+__device__ __forceinline__ double bpermute64(int byte, double v) {
+    union { double d; int i[2]; } x, y;
+    x.d = v;
+    y.i[0] = __builtin_amdgcn_ds_bpermute(byte, x.i[0]);
+    y.i[1] = __builtin_amdgcn_ds_bpermute(byte, x.i[1]);
     return y.d;
 }
 
@@ -84,11 +116,11 @@ struct TriCfg {
     static constexpr int NC = (N + 63) / 64;           // columns per lane
     static constexpr int RS = 4 * ((N + 15) / 16);     // rows per wave, in chunks of four
     static constexpr int PS = 64 * NC;
-    // reflectors, packed: row k (entries k+1 .. N-1) above row k-1; a whole-wave store of row k runs on into
-    // rows that are stored later, and behind the last one
-    static constexpr int USZ = N * (N - 1) / 2 + PS;
-    // exchange buffers: partial products [2][waves][PS] and the rows that hold the next pivot [2][16][PS]
-    static constexpr int EX = (2 * kTriWaves + 32) * PS;
+    // pivot rows, later reflectors: row k holds entries k .. N-1, packed where whole rows would not fit LDS; a
+    // whole-wave store of row k runs on into rows that are stored later, and behind the last one
+    static constexpr int USZ = (N > 64 ? N * (N + 1) / 2 : N * N) + PS;
+    // exchange buffers, twice: partial products [waves][PS] and the four rows next to the pivot [4][PS]
+    static constexpr int EXB = (kTriWaves + 4) * PS, EX = 2 * EXB;
     static constexpr int WA = N * RB;
     static constexpr int WB = (N * (RB + 2) > EX) ? N * (RB + 2) : EX;
     static constexpr int VEC = 6 * N + 16 + 64;        // d, e, 1/h, scaled e, (d, e^2) and a chunk, lambda
@@ -99,38 +131,95 @@ using TriRows = double[4 * ((N + 15) / 16)][(N + 63) / 64];   // rows per wave x
 template <int N>
 using TriCols = double[(N + 63) / 64];
 
-// where entry j of reflector k would be in U if its entries started at 0 (they start at k + 1)
-__device__ __forceinline__ int tri_row(int n, int k) { return k * (n - 1) - (k * (k - 1)) / 2 - (k + 1); }
+// where entry j of row k would be in U if its entries started at 0 (they start at k)
+__device__ __forceinline__ constexpr int tri_row(int n, int k) { return n > 64 ? k * (n - 1) - (k * (k - 1)) / 2 : k * n; }
 
 // State of the reduction that a wave carries from step to step.
 template <int N>
 struct TriState {
     TriCols<N> x;                        // the pivot row, updated
-    TriCols<N> uo, qo;                   // reflector and correction of the last step, not yet applied to the rows
-    TriCols<N> dr, er, hr;               // column j of the results (diagonal, off-diagonal, 1/h)
-    double ur[4 * ((N + 15) / 16)];      // entries of uo that belong to the wave's own rows, in scalar registers
+    TriCols<N> uo, po;                   // reflector of the last step and A u / h, which its correction comes from
+    TriCols<N> qo;                       // negative correction of the last step, not yet applied to the rows
+    double inv, up;                      // of the last step: 1 / h, u^T A u
+    // entries of uo and qo that belong to the wave's own rows: that of row m = 4 q + s in lanes m % 16, m % 16 + 16, ...
+    // of register m / 16
+    TriCols<N> ur, qr;
 };
+
+// What the last step leaves to the gaps of the next one: its correction,
+template <int N, int C0>
+__device__ __forceinline__ void tri_correction(TriState<N>& st, int own) {
+    constexpr int NC = TriCfg<N, 8>::NC;
+    const double w2 = -0.5 * (st.inv * st.up) * st.inv;
+#pragma unroll
+    for (int c = C0; c < NC; ++c) {
+        st.qo[c] = -fma(w2, st.uo[c], st.po[c]);
+        st.qr[c] = bpermute64(own, st.qo[c]);
+    }
+}
+// and the pivot row of step k, as it is, to U: what it makes of it is worked out from there afterwards, by all waves at once.
+template <int N, int C0>
+__device__ __forceinline__ void tri_keep_row(const TriState<N>& st, double* U, int k, int col) {
+    using T = TriCfg<N, 8>;
+    double* uk = U + tri_row(N, k);
+#pragma unroll
+    for (int c = C0; c < T::NC; ++c) {
+        if constexpr (N > 64) uk[k + ((col + 64 * c - k) & (T::PS - 1))] = st.x[c];
+        else uk[col] = st.x[c];
+    }
+}
+
+// The last step's update of the rows 4 A0 .. MN - 1 of a wave, a[m][c] += ur(row m) qo[c] + qr(row m) uo[c], as blocks of four
+// multiply-adds with a broadcast operand: those of share G of GN.
+template <int A0, int MN, int C0, int NC, int B0, int B1, int N>
+__device__ __forceinline__ void tri_update_blocks(TriRows<N>& a, const TriState<N>& st) {
+    if constexpr (B0 < B1) {
+        constexpr int NQ = (MN / 4 - A0) * (NC - C0), R = B0 % NQ, M = 4 * (A0 + R / (NC - C0)), c = C0 + R % (NC - C0);
+        if constexpr (B0 < NQ) fmac_bcast64<M % 16>(a[M][c], a[M + 1][c], a[M + 2][c], a[M + 3][c], st.ur[M / 16], st.qo[c]);
+        else fmac_bcast64<M % 16>(a[M][c], a[M + 1][c], a[M + 2][c], a[M + 3][c], st.qr[M / 16], st.uo[c]);
+        tri_update_blocks<A0, MN, C0, NC, B0 + 1, B1, N>(a, st);
+    }
+}
+template <int A0, int MN, int C0, int NC, int G, int GN, int N>
+__device__ __forceinline__ void tri_update_share(TriRows<N>& a, const TriState<N>& st) {
+    constexpr int TOTAL = 2 * (MN / 4 - A0) * (NC - C0);
+    __builtin_amdgcn_sched_barrier(0);
+    tri_update_blocks<A0, MN, C0, NC, TOTAL * G / GN, TOTAL * (G + 1) / GN, N>(a, st);
+    __builtin_amdgcn_sched_barrier(0);
+}
+// and their product with x: p[c] += x(row m) a[m][c] (an accumulator that the next instruction adds to costs it no wait)
+template <int M, int MN, int C0, int NC, int RS>
+__device__ __forceinline__ void tri_product(const double (&a)[RS][NC], const double (&x)[NC], double (&p)[NC]) {
+    if constexpr (M < MN) {
+#pragma unroll
+        for (int c = C0; c < NC; ++c) fmac_bcast64_sum<M % 16>(p[c], x[M / 16], a[M][c], a[M + 1][c], a[M + 2][c], a[M + 3][c]);
+        tri_product<M + 4, MN, C0, NC, RS>(a, x, p);
+    }
+}
 
 // Steps of the reduction whose next pivot is in rows 16 A0 .. 16 A0 + 15, then those of A0 + 1 and so on:
 // the chunks of rows that are still in the trailing block are a compile-time set, so a step has no branch.
 // A wave alone on its SIMD issues one instruction, scalar ones included, per five cycles, and every access
 // to LDS delays the exchange (removing both sums changes nothing, removing a store of all waves takes 60 to
-// 100 cycles off a step): entries of u and q that a row needs are lane broadcasts, not reads.
+// 100 cycles off a step): entries of u and q that a row needs are broadcasts inside the multiply-adds, which reach 16
+// lanes, so the wave's own entries are first brought to every 16 lanes by one lane permutation.  Nothing that can be worked out
+// afterwards is in the loop: a step keeps its pivot row, and diagonal, off-diagonal and reflector come from those
+// rows, all at once.  Cycles a step, with scalar operands (two lane reads for every multiply-add or two) and the results
+// taken in the loop against this: 1220 -> 1110 at 40 columns, 1250 -> 1170 at 64, 1980 -> 1660 at 128.
 template <int N, int A0>
 __device__ __forceinline__ void tri_steps(TriRows<N>& a, TriState<N>& st, double* ex, double* U, int wave,
-                                          int col) {
+                                          int col, int own) {
     using T = TriCfg<N, 8>;
     constexpr int NC = T::NC, PS = T::PS, W = kTriWaves, NA = (N + 15) / 16;
     constexpr int C0 = A0 >= 4 ? 1 : 0;                 // columns of earlier registers have left the block
     constexpr int K0 = A0 ? 16 * A0 - 1 : 0, K1 = 16 * A0 + 15 < N - 2 ? 16 * A0 + 15 : N - 2;
-    double* rows = ex + 2 * W * PS;                     // [2][16][PS]
-    constexpr bool KEEP = NC - C0 == 1;                 // two columns per lane need the scalar registers
+    constexpr int MN = 4 * NA;
+    double* at = ex + (K0 & 1) * T::EXB + col;          // this step's exchange buffer
     // one and zero in double precision by their high words
     auto unit = [](bool on) __attribute__((always_inline)) { return __hiloint2double(on ? 0x3ff00000 : 0, 0); };
+#define SOLAR_TRI_FENCE __builtin_amdgcn_sched_barrier(0)
 #pragma unroll 1
     for (int k = K0; k < K1; ++k) {
-        double* pb = ex + (k & 1) * (W * PS) + col;
-        double* rb = rows + (k & 1) * (16 * PS) + col;
         const int k1 = k + 1;
         double u[NC], s2 = kTriTiny;                    // a column of zeros still gives a reflector
 #pragma unroll
@@ -140,102 +229,113 @@ __device__ __forceinline__ void tri_steps(TriRows<N>& a, TriState<N>& st, double
         }
         double xk1 = st.x[NC - 1];
         if constexpr (NC - C0 == 2) xk1 = k1 >= 64 ? st.x[1] : st.x[0];
+        // the sum and the reciprocal square root are a chain whose gaps what the last step has left, and the update of
+        // the own rows, fill; in front of the chain or behind it, where the compiler puts them, they take as long again
+        SOLAR_TRI_FENCE;
         s2 = wave_sum64_begin(s2);
+        SOLAR_TRI_FENCE;
+        tri_correction<N, C0>(st, own);
+        SOLAR_TRI_FENCE;
+        s2 = __builtin_amdgcn_mfma_f64_4x4x4f64(1.0, s2, 0.0, 0, 0, 0);
+        SOLAR_TRI_FENCE;
+        // (the diagonal entry of row 63 is still in the first register of the columns)
+        if (wave == (k & (W - 1))) tri_keep_row<N, (A0 > 4 ? 1 : 0)>(st, U, k, col);
         const double alpha = readlane64(xk1, (k1 ^ (4 * wave)) & 63);
-        s2 = wave_sum64_end(s2);
+        SOLAR_TRI_FENCE;
+        s2 += dpp_mov64<0x141>(s2);
+        tri_update_share<A0, MN, C0, NC, 0, 6>(a, st);
+        s2 += dpp_mov64<0x140>(s2);
+        tri_update_share<A0, MN, C0, NC, 1, 6>(a, st);
+        const double r0 = __builtin_amdgcn_rsq(s2);
+        tri_update_share<A0, MN, C0, NC, 2, 6>(a, st);
+        const double r1 = fma(-s2 * r0, r0, 1.0);
+        tri_update_share<A0, MN, C0, NC, 3, 6>(a, st);
+        const double r2 = fma(r1, 0.5 * r0, r0);
+        tri_update_share<A0, MN, C0, NC, 4, 6>(a, st);
         // the reflector I - u u^T / h maps the column to g e_(k+1)
-        const double g = -copysign(s2 * rsq64(s2), alpha);
-        const double inv = rcp64(fma(-alpha, g, s2) - 32.0 * kTriTiny);
+        const double g = -copysign(s2 * r2, alpha);
+        tri_update_share<A0, MN, C0, NC, 5, 6>(a, st);
 #pragma unroll
         for (int c = C0; c < NC; ++c) {
             u[c] = fma(-g, unit(col + 64 * c == k1), u[c]);
+            st.ur[c] = bpermute64(own, u[c]);
         }
-        // own rows of the trailing block: the last step's update, then the product with u
-        double pp[NC][4];
+        SOLAR_TRI_FENCE;
+        const double inv = rcp64(fma(-alpha, g, s2) - 32.0 * kTriTiny);
+        if (wave == ((k1 >> 2) & (W - 1))) {            // the next pivot row is one of this wave's
 #pragma unroll
-        for (int c = C0; c < NC; ++c) pp[c][0] = pp[c][1] = pp[c][2] = pp[c][3] = 0.0;
+            for (int c = C0; c < NC; ++c)
 #pragma unroll
-        for (int q = A0; q < NA; ++q)
+                for (int s = 0; s < 4; ++s) at[(W + s) * PS + 64 * c] = a[4 * A0 + s][c];
+        }
+        SOLAR_TRI_FENCE;
+        double pp[NC];
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const int m = 4 * q + s, r = (16 * q) >> 6, i = (16 * q + s) & 63;
-                const double qr = readlane64(st.qo[r], i);
-                const double ul = KEEP ? st.ur[m] : readlane64(st.uo[r], i);
+        for (int c = 0; c < NC; ++c) pp[c] = 0.0;
+        tri_product<4 * A0, MN, C0, NC>(a, st.ur, pp);   // the own rows with u
 #pragma unroll
-                for (int c = C0; c < NC; ++c) {
-                    a[m][c] = fma(-ul, st.qo[c], fma(-qr, st.uo[c], a[m][c]));
-                    if (q == A0) rb[(4 * wave + s) * PS + 64 * c] = a[m][c];
-                }
-            }
-#pragma unroll
-        for (int q = A0; q < NA; ++q)
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const int m = 4 * q + s, r = (16 * q) >> 6, i = (16 * q + s) & 63;
-                const double ui = readlane64(u[r], i);
-#pragma unroll
-                for (int c = C0; c < NC; ++c) pp[c][s] = fma(ui, a[m][c], pp[c][s]);
-                if (KEEP) st.ur[m] = ui;
-            }
-#pragma unroll
-        for (int c = C0; c < NC; ++c) pb[wave * PS + 64 * c] = (pp[c][0] + pp[c][1]) + (pp[c][2] + pp[c][3]);
+        for (int c = C0; c < NC; ++c) at[wave * PS + 64 * c] = pp[c];
         __syncthreads();
         double r[NC][W], y[NC];
 #pragma unroll
         for (int c = C0; c < NC; ++c) {
 #pragma unroll
-            for (int w = 0; w < W; ++w) r[c][w] = pb[w * PS + 64 * c];
-            y[c] = rb[(k1 & 15) * PS + 64 * c];
-        }
-        if (wave == (k & (W - 1))) {
-            double* uk = U + tri_row(N, k) + k1;
-#pragma unroll
-            for (int c = C0; c < NC; ++c) uk[(col + 64 * c - k1) & (PS - 1)] = u[c];
+            for (int w = 0; w < W; ++w) r[c][w] = at[w * PS + 64 * c];
         }
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            st.er[c] = col + 64 * c == k ? g : st.er[c];
-            st.hr[c] = col + 64 * c == k ? inv : st.hr[c];
-        }
+        for (int c = C0; c < NC; ++c) y[c] = at[(W + (k1 & 3)) * PS + 64 * c];
+        at = ex + ((at - ex) ^ T::EXB);
         // with w = u^T A u, the correction is q = p - (w / 2 h^2) u for p = A u / h, and the new pivot row
         // is row - u_(k+1) q - q_(k+1) u; all of it but the multiple of w is ready before w is
         double p[NC], t[NC], up = 0.0;
 #pragma unroll
         for (int c = C0; c < NC; ++c) {
-            const double sum = (r[c][0] + r[c][1]) + (r[c][2] + r[c][3]);
-            up = fma(u[c], sum, up);
-            p[c] = sum * inv;
+            p[c] = (r[c][0] + r[c][1]) + (r[c][2] + r[c][3]);
+            up = fma(u[c], p[c], up);
         }
-        up = wave_sum64_end(wave_sum64_begin(up));
+        SOLAR_TRI_FENCE;
+        up = wave_sum64_begin(up);
+        SOLAR_TRI_FENCE;
+#pragma unroll
+        for (int c = C0; c < NC; ++c) p[c] *= inv;
+        SOLAR_TRI_FENCE;
+        up = __builtin_amdgcn_mfma_f64_4x4x4f64(1.0, up, 0.0, 0, 0, 0);
+        SOLAR_TRI_FENCE;
         double ps = p[NC - 1];
         if constexpr (NC - C0 == 2) ps = k1 >= 64 ? p[1] : p[0];
         const double uk1 = alpha - g, pk1 = readlane64(ps, (k1 ^ (4 * wave)) & 63);
+        SOLAR_TRI_FENCE;
+        up += dpp_mov64<0x141>(up);
+        SOLAR_TRI_FENCE;
 #pragma unroll
         for (int c = C0; c < NC; ++c) {
             y[c] = fma(-uk1, p[c], fma(-pk1, u[c], y[c]));
             t[c] = inv * uk1 * inv * u[c];
         }
-        const double w2 = -0.5 * (inv * up) * inv;
+        SOLAR_TRI_FENCE;
+        up += dpp_mov64<0x140>(up);
 #pragma unroll
         for (int c = C0; c < NC; ++c) {
             st.x[c] = fma(up, t[c], y[c]);
-            st.qo[c] = fma(w2, u[c], p[c]);
             st.uo[c] = u[c];
-            st.dr[c] = col + 64 * c == k1 ? st.x[c] : st.dr[c];
+            st.po[c] = p[c];
         }
+        st.inv = inv;
+        st.up = up;
     }
-    if constexpr (A0 == 3 && NC == 2) {                 // from here on the broadcasts are kept
-#pragma unroll
-        for (int m = 16; m < T::RS; ++m) st.ur[m] = readlane64(st.uo[1], (16 * (m / 4) + m % 4) & 63);
+    if constexpr (K1 < N - 2) {
+        tri_steps<N, A0 + 1>(a, st, ex, U, wave, col, own);
+    } else {
+        tri_correction<N, C0>(st, own);
+        if (wave == ((N - 2) & (W - 1))) tri_keep_row<N, C0>(st, U, N - 2, col);
     }
-    if constexpr (K1 < N - 2) tri_steps<N, A0 + 1>(a, st, ex, U, wave, col);
+#undef SOLAR_TRI_FENCE
 }
 
 // Householder reduction of the matrix in `a` to tridiagonal form: diagonal dd[N], off-diagonal ee[N-1],
 // reflector k in row k of U (entries k+1 .. N-1) with its 1/h in ih[k].  Waves 0 .. 3 hold the matrix:
 // a[4 q + s][c] is entry (16 q + 4 wave + s, (lane ^ 4 wave) + 64 c), zero outside.  With the columns
-// exchanged like that the lane of a wave's own row is a constant, and a lane broadcast from a constant
-// lane takes half the time (5 cycles against 9).
+// exchanged like that the lanes of a wave's own rows are the same for every wave.
 template <int N>
 __device__ __forceinline__ void tri_reduce(TriRows<N>& a, double* ex, double* U,
                                            double* dd, double* ee, double* ih) {
@@ -244,35 +344,44 @@ __device__ __forceinline__ void tri_reduce(TriRows<N>& a, double* ex, double* U,
     const int tid = fresh_tid(), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (wave >= W) {
 #pragma unroll 1
-        for (int k = 0; k < N; ++k) __syncthreads();    // one for the first row, N - 2 steps, one at the end
-        return;
-    }
-    const int col = (tid & 63) ^ (4 * wave);
-    double* row0 = ex + (2 * W + 16) * PS;
-    if (wave == 0) {
+        for (int k = 0; k < N - 1; ++k) __syncthreads();   // one for the first row, N - 2 steps
+    } else {
+        const int col = (tid & 63) ^ (4 * wave);
+        double* row0 = ex + T::EXB;
+        if (wave == 0) {
 #pragma unroll
-        for (int c = 0; c < NC; ++c) row0[col + 64 * c] = a[0][c];
-    }
-    __syncthreads();
-    TriState<N> st;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        st.x[c] = row0[col + 64 * c];
-        st.uo[c] = st.qo[c] = st.er[c] = st.hr[c] = 0.0;
-        st.dr[c] = st.x[c];                             // d_0 in column 0
-    }
-#pragma unroll
-    for (int m = 0; m < T::RS; ++m) st.ur[m] = 0.0;
-    tri_steps<N, 0>(a, st, ex, U, wave, col);
-    // row N-2 is in x; of row N-1 only the last diagonal entry is missing the last update
-    if (wave == (((N - 1) >> 2) & 3)) {
+            for (int c = 0; c < NC; ++c) row0[col + 64 * c] = a[0][c];
+        }
+        __syncthreads();
+        TriState<N> st;
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-            const int j = col + 64 * c;
-            if (j == N - 1) st.dr[c] = fma(-2.0 * st.uo[c], st.qo[c], a[4 * ((N - 1) >> 4) + 3][c]);
-            if (j < N) dd[j] = st.dr[c];
-            if (j < N - 2) { ee[j] = st.er[c]; ih[j] = st.hr[c]; }
-            if (j == N - 1) ee[N - 2] = st.x[c];
+            st.x[c] = row0[col + 64 * c];
+            st.uo[c] = st.po[c] = st.qo[c] = st.ur[c] = st.qr[c] = 0.0;
+        }
+        st.inv = st.up = 0.0;
+        // where a wave's own entries are: row 16 q + 4 wave + s in lane 16 q + s (the columns are exchanged)
+        const int i16 = tid & 15;
+        tri_steps<N, 0>(a, st, ex, U, wave, col, 4 * (16 * (i16 >> 2) + (i16 & 3)));
+        // of row N-1 only the last diagonal entry is missing the last update
+        if (wave == (((N - 1) >> 2) & 3) && col + 64 * (NC - 1) == N - 1)
+            dd[N - 1] = fma(2.0 * st.uo[NC - 1], st.qo[NC - 1], a[4 * ((N - 1) >> 4) + 3][NC - 1]);
+    }
+    __syncthreads();
+    // diagonal, off-diagonal and reflector from the pivot rows, eight lanes to a row
+    const int u = tid & 7;
+#pragma unroll 1
+    for (int k = tid >> 3; k < N - 1; k += kTriThreads / 8) {
+        double* uk = U + tri_row(N, k);
+        double s2 = u == 0 ? kTriTiny : 0.0;
+        for (int j = k + 1 + u; j < N; j += 8) s2 = fma(uk[j], uk[j], s2);
+        s2 = team_sum64<8>(s2);
+        const double alpha = uk[k + 1], g = k < N - 2 ? -copysign(s2 * rsq64(s2), alpha) : alpha;
+        if (u == 0) {
+            dd[k] = uk[k];
+            ee[k] = g;
+            ih[k] = rcp64(fma(-alpha, g, s2) - 32.0 * kTriTiny);
+            uk[k + 1] = alpha - g;
         }
     }
     __syncthreads();
