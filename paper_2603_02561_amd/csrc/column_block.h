@@ -394,7 +394,7 @@ __device__ __forceinline__ bool ritz_rotate(const float* Zc, float* Qc, const Tr
     }
     tri_reduce<N>(a, w.wb, w.U, w.dd, w.ee, w.ih);
     const double bound = tri_values<N, (N <= 32 ? 8 : 4)>(w.dd, w.ee, w.es, w.t, w.lam, scal,
-                                                          reinterpret_cast<int*>(w.wb), N);
+                                                          w.wb, N);
     const double l0 = w.lam[0], dead = (double)kDeadRel * kDeadRel * l0;
     const bool close = tid + 1 < wanted && w.lam[tid + 1] > dead && w.lam[tid] - w.lam[tid + 1] < kTriGap;
     if (__syncthreads_or(close) || !(bound > kTriZero) || !(l0 > 0.0)) return false;

@@ -445,7 +445,7 @@ __device__ __forceinline__ bool eig_direct(const float* Gs, double* sm, double* 
     __syncthreads();
     tri_reduce<D>(a, w.wb, w.U, w.dd, w.ee, w.ih);
     const double bound = tri_values<D, (RMAX <= 32 ? 8 : 4)>(w.dd, w.ee, w.es, w.t, w.lam, scal,
-                                                             reinterpret_cast<int*>(w.wb), r);
+                                                             w.wb, r);
     const double l0 = w.lam[0], dead = (double)kDeadRel * l0;
     const bool any = bound > kTriZero && l0 > 0.0;
     const bool close = tid + 1 < r && w.lam[tid + 1] > dead && w.lam[tid] - w.lam[tid + 1] < kTriGap;

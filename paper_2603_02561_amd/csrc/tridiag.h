@@ -122,7 +122,8 @@ struct TriCfg {
     // exchange buffers, twice: partial products [waves][PS] and the four rows next to the pivot [4][PS]
     static constexpr int EXB = (kTriWaves + 4) * PS, EX = 2 * EXB;
     static constexpr int WA = N * RB;
-    static constexpr int WB = (N * (RB + 2) > EX) ? N * (RB + 2) : EX;
+    static constexpr int GRID = 1024 + N;              // of tri_values
+    static constexpr int WB0 = N * (RB + 2) > EX ? N * (RB + 2) : EX, WB = WB0 > GRID ? WB0 : GRID;
     static constexpr int VEC = 6 * N + 16 + 64;        // d, e, 1/h, scaled e, (d, e^2) and a chunk, lambda
     static_assert(N % 8 == 0 && N >= 16 && N <= 128, "multiples of eight");
 };
@@ -387,16 +388,23 @@ __device__ __forceinline__ void tri_reduce(TriRows<N>& a, double* ex, double* U,
     __syncthreads();
 }
 
-// Numbers of eigenvalues >= la and >= lb of the tridiagonal matrix (t[i].x = d_i, t[i].y = e_(i-1)^2,
-// t[0].y = 0), from the signs of its leading minors.  Two points per lane share the reads of t, which
+// What the minors say at a point: the number of eigenvalues >= the point, and (DET) the determinant of T - point as m 2^e.
+struct SturmPoint {
+    int c, e;
+    double m;
+};
+
+// The tridiagonal matrix (t[i].x = d_i, t[i].y = e_(i-1)^2, t[0].y = 0) at two points, from its leading minors and their
+// signs.  Two points per lane share the reads of t, which
 // four waves could not feed to one point each (a 16-byte read occupies the LDS port for 8 cycles per
 // wave, even of one address).  The recurrences are rescaled every 16 steps: a minor shrinks by about
 // |lambda| per step at most, and no wanted eigenvalue is below 1e-10 of the norm.
-template <int N>
-__device__ __forceinline__ void sturm_count_ge(const double2* t, double la, double lb, int& ca, int& cb) {
+template <int N, bool DET>
+__device__ __forceinline__ void sturm_points(const double2* t, double la, double lb, SturmPoint& a, SturmPoint& b) {
     double p = 1.0, pm = 0.0, r = 1.0, rm = 0.0;
     uint32_t bp = 0, br = 0;
     int np = 0, nr = 0;
+    if constexpr (DET) a.e = b.e = 0;
     auto load = [&](double2 (&v)[8], int i0) __attribute__((always_inline)) {
 #pragma unroll
         for (int s = 0; s < 8; ++s) v[s] = t[i0 + s];
@@ -436,18 +444,56 @@ __device__ __forceinline__ void sturm_count_ge(const double2* t, double la, doub
         pm = __builtin_amdgcn_ldexp(pm, ep);
         r = __builtin_amdgcn_ldexp(r, er);
         rm = __builtin_amdgcn_ldexp(rm, er);
+        if constexpr (DET) {
+            a.e -= ep;
+            b.e -= er;
+        }
     }
-    ca = N - np;
-    cb = N - nr;
+    a.c = N - np;
+    b.c = N - nr;
+    if constexpr (DET) {
+        a.m = p;
+        b.m = r;
+    }
 }
 
-// The R largest eigenvalues of the tridiagonal matrix, scaled by a power of two so that its norm is at
-// most one: lam[0..R-1] descending, to 2^-49 absolute.  256 threads (one wave per SIMD) first count
-// at 512 points for all eigenvalues together; then TP lanes share an eigenvalue and cut its interval
-// into 2 TP + 1 parts per round.  Returns the scale (0: the matrix is zero).
-template <int N, int TP>
-__device__ __forceinline__ double tri_values(const double* dd, const double* ee, double* es, double2* t, double* lam,
-                                             double* scal, int* cnt, int R) {
+// the largest (UP) or smallest v of a team of TP lanes
+template <int TP, bool UP>
+__device__ __forceinline__ double team_end64(double v) {
+    auto step = [](double x, double y) __attribute__((always_inline)) { return UP ? fmax(x, y) : fmin(x, y); };
+    v = step(v, dpp_mov64<0xB1>(v));
+    v = step(v, dpp_mov64<0x4E>(v));
+    if constexpr (TP == 8) v = step(v, dpp_mov64<0x141>(v));
+    return v;
+}
+
+// What the minors say at the point x of a team, from the lane that has it among its own two; `f` if none has.
+template <int TP>
+__device__ __forceinline__ SturmPoint team_point(double x, bool is_a, bool is_b, const SturmPoint& a, const SturmPoint& b,
+                                                 const SturmPoint& f, int lane) {
+    SturmPoint o;
+    const double m = is_a ? a.m : b.m;
+    const int ec = is_a ? (a.e << 8) + a.c : (b.e << 8) + b.c;   // counts are at most 128
+    const uint32_t team = (uint32_t)(__ballot(is_a || is_b) >> (lane & ~(TP - 1))) & ((1u << TP) - 1u);
+    const int src = 4 * ((lane & ~(TP - 1)) + __builtin_ctz(team | (1u << TP)));
+    const double mo = bpermute64(src, m);
+    const int eco = __builtin_amdgcn_ds_bpermute(src, ec);
+    o.m = team ? mo : f.m;
+    o.e = team ? eco >> 8 : f.e;
+    o.c = team ? eco & 255 : f.c;
+    return o;
+}
+
+// Eigenvalues below kTriDead of the norm are not resolved: kDeadRel^2 of the largest, which the norm is at most four times
+// of, is above it, and smaller ones are dropped by every caller.
+constexpr double kTriDead = 3.637978807091713e-12;      // 2^-38
+constexpr double kTriDone = 1.7763568394002505e-15;     // 2^-49
+constexpr double kNear = 0.01;   // share of an interval where the first guess is trusted to be
+
+// The matrix scaled by a power of two so that its norm is at most one, as t and es; the scale (0: the matrix is zero) in
+// scal[0].  Wave 0; no barrier.
+template <int N>
+__device__ __forceinline__ void tri_scale(const double* dd, const double* ee, double* es, double2* t, double* scal) {
     const int tid = fresh_tid(), lane = tid & 63;
     if (tid < 64) {
         double bmax = 0.0;
@@ -463,15 +509,25 @@ __device__ __forceinline__ double tri_values(const double* dd, const double* ee,
             if (i) es[i - 1] = e1;
         }
     }
+}
+
+// The R largest eigenvalues of the scaled matrix, lam[0..R-1] descending, to 2^-49 absolute.  256 threads (one wave per SIMD)
+// first count at 512 points for all eigenvalues together; then TP lanes share an eigenvalue and cut its interval
+// into 2 TP + 1 parts per round.  Returns the scale.
+template <int N, int TP>
+__device__ __forceinline__ double tri_values_even(const double* dd, const double* ee, double* es, double2* t, double* lam,
+                                                  double* scal, int* cnt, int R) {
+    const int tid = fresh_tid(), lane = tid & 63;
+    tri_scale<N>(dd, ee, es, t, scal);
     __syncthreads();
     const double bound = scal[0];
     // positive semidefinite up to rounding: [-2^-20, 1] holds every eigenvalue that matters
     constexpr double kLo = -9.5367431640625e-07, kStep = (1.0 - kLo) / 512;
     if (tid < 256) {
-        int c0, c1;
-        sturm_count_ge<N>(t, fma(kStep, (double)tid, kLo), fma(kStep, (double)(tid + 256), kLo), c0, c1);
-        cnt[tid] = c0;
-        cnt[tid + 256] = c1;
+        SturmPoint a, b;
+        sturm_points<N, false>(t, fma(kStep, (double)tid, kLo), fma(kStep, (double)(tid + 256), kLo), a, b);
+        cnt[tid] = a.c;
+        cnt[tid + 256] = b.c;
     }
     __syncthreads();
     if (tid < 256) {
@@ -485,15 +541,107 @@ __device__ __forceinline__ double tri_values(const double* dd, const double* ee,
 #pragma unroll 1
         for (int it = 0; it < rounds; ++it) {
             w *= 1.0 / (2 * TP + 1);
-            int c0, c1;
-            sturm_count_ge<N>(t, fma(w, (double)(pt + 1), lo), fma(w, (double)(pt + 1 + TP), lo), c0, c1);
-            const uint64_t m0 = __ballot(c0 > k), m1 = __ballot(c1 > k);
+            SturmPoint a, b;
+            sturm_points<N, false>(t, fma(w, (double)(pt + 1), lo), fma(w, (double)(pt + 1 + TP), lo), a, b);
+            const uint64_t m0 = __ballot(a.c > k), m1 = __ballot(b.c > k);
             constexpr uint32_t kTeam = (1u << TP) - 1u;
             const int sh = lane & ~(TP - 1);
             const int above = __popc((uint32_t)(m0 >> sh) & kTeam) + __popc((uint32_t)(m1 >> sh) & kTeam);
             lo = fma(w, (double)above, lo);
         }
         if (pt == 0 && v < R) lam[v] = fma(0.5, w, lo);
+    }
+    __syncthreads();
+    return bound;
+}
+
+// The R largest eigenvalues of the tridiagonal matrix, scaled by a power of two so that its norm is at
+// most one: lam[0..R-1] descending, to 2^-49 absolute.  256 threads (one wave per SIMD) first count
+// at 512 points for all eigenvalues together, half of them spread evenly, half evenly in the logarithm below 2^-8 (a
+// Gram matrix of iterated columns has its smallest eigenvalues there).  Then TP lanes share an eigenvalue and look at 2 TP
+// points per round: as long as its interval holds others too, evenly spread; once it is alone, half of them so and
+// half around the zero of the line through the determinants at the ends, at distances that the last round's miss
+// suggests (the miss of that zero falls with the square of the width).  Counts decide what is kept, so a bad guess costs a
+// round that cuts to a fifth or ninth.  Five to eight rounds, where cutting into 2 TP + 1 parts takes 10 or 13: 31 -> 25
+// thousand cycles at 40 columns, 38 -> 31 at 64, 91 -> 60 at 128.  Up to 32 columns a round of counts is so short that what
+// the guess costs (two hundred instructions) is not saved, and the parts stay even (24 columns: 14 thousand against 16).
+// Returns the scale (0: the matrix is zero).
+template <int N, int TP>
+__device__ __forceinline__ double tri_values(const double* dd, const double* ee, double* es, double2* t, double* lam,
+                                             double* scal, double* work, int R) {
+    if constexpr (N <= 32) return tri_values_even<N, TP>(dd, ee, es, t, lam, scal, reinterpret_cast<int*>(work), R);
+    const int tid = fresh_tid(), lane = tid & 63;
+    int* cnt = reinterpret_cast<int*>(work);             // [512], [512] and [512]: what the minors say on the grid
+    int* ex2 = cnt + 512;
+    double* det = work + 512;
+    int* pos = reinterpret_cast<int*>(det + 512);        // [N] point of the grid below eigenvalue k
+    static_assert(TriCfg<N, 8>::GRID >= 1024 + N / 2, "all of them in a work array");
+    tri_scale<N>(dd, ee, es, t, scal);
+    if (tid >= 64 && tid < 64 + N) pos[tid - 64] = 0;
+    __syncthreads();
+    const double bound = scal[0];
+    // positive semidefinite up to rounding: [-2^-20, 1] holds every eigenvalue that matters
+    constexpr double kLo = -9.5367431640625e-07;
+    // 0: kLo; 1 .. 255: 2^(-38 + 30 (i - 1) / 254); 256 .. 511: evenly from 2^-8; 512: 1
+    auto grid = [&](int i) __attribute__((always_inline)) {
+        const float l = __builtin_amdgcn_exp2f(-38.f + (30.f / 254.f) * (float)(i - 1));
+        return i == 0 ? kLo : i < 256 ? (double)l : i < 512 ? fma((double)(i - 256), (1.0 - 0.00390625) / 256, 0.00390625 + 1e-6) : 1.0;
+    };
+    if (tid < 256) {
+        SturmPoint a, b;
+        sturm_points<N, true>(t, grid(tid), grid(tid + 256), a, b);
+        cnt[tid] = a.c;
+        ex2[tid] = a.e;
+        det[tid] = a.m;
+        cnt[tid + 256] = b.c;
+        ex2[tid + 256] = b.e;
+        det[tid + 256] = b.m;
+    }
+    __syncthreads();
+    if (tid < 512) {
+        const int top = cnt[tid] < R ? cnt[tid] : R;
+        for (int k = tid < 511 ? cnt[tid + 1] : 0; k < top; ++k) pos[k] = tid;
+    }
+    __syncthreads();
+    if (tid < 256) {
+        const int v = tid / TP, pt = tid % TP;
+        const int k = v < R ? v : R - 1;
+        const int at = pos[k];
+        double lo = grid(at), hi = grid(at + 1);
+        SturmPoint fl = {cnt[at], ex2[at], det[at]}, fh = {-1, 0, 0.0};   // nothing is known at 1
+        if (at < 511) fh = SturmPoint{cnt[at + 1], ex2[at + 1], det[at + 1]};
+        double near = kNear * (hi - lo);                 // distance of the innermost points around the guess
+        constexpr int H = TP / 2;
+        const int ring = pt < H ? H - 1 - pt : pt - H;   // 0: innermost
+        const double far = (pt < H ? -1.0 : 1.0) * (ring == 0 ? 1.0 : ring == 1 ? 64.0 : ring == 2 ? 512.0 : 4096.0);
+        const double even_half = (pt + 1) * (1.0 / (TP + 1)), even_a = (pt + 1) * (1.0 / (2 * TP + 1)),
+                     even_b = (pt + 1 + TP) * (1.0 / (2 * TP + 1));
+#pragma unroll 1
+        for (int it = 0; it < 20; ++it) {
+            const double w = hi - lo;
+            if (!__any(w > kTriDone && hi > kTriDead)) break;
+            const bool alone = fl.c == k + 1 && fh.c == k;
+            // zero of the line through the determinants at the ends
+            const double ratio = fmax(__builtin_amdgcn_ldexp(fh.m, fh.e - fl.e) * rcp64(fl.m), -1.0e100);
+            const double guess = fma(w, rcp64(1.0 - ratio), lo);
+            const double xa = fma(w, alone ? even_half : even_a, lo);
+            const double aim = fmin(fmax(fma(near, far, guess), lo), hi), xb = alone ? aim : fma(w, even_b, lo);
+            SturmPoint a, b;
+            sturm_points<N, true>(t, xa, xb, a, b);
+            const bool ua = a.c > k, ub = b.c > k;
+            const double l2 = team_end64<TP, true>(fmax(fmax(lo, ua ? xa : lo), ub ? xb : lo));
+            const double h2 = team_end64<TP, false>(fmin(fmin(hi, ua ? hi : xa), ub ? hi : xb));
+            fl = team_point<TP>(l2, ua && xa == l2, ub && xb == l2, a, b, fl, lane);
+            fh = team_point<TP>(h2, !ua && xa == h2, !ub && xb == h2, a, b, fh, lane);
+            // the miss of the guess was at most the distance to the further end; the next one's is smaller by the square
+            // of the ratio of the widths
+            const double w2 = h2 - l2, shrink = w2 * rcp64(w);
+            const double miss = fmax(fabs(h2 - guess), fabs(guess - l2));
+            near = fmin(alone ? fmax(miss * shrink * shrink, 0.25 * kTriDone) : w2, kNear * w2);
+            lo = l2;
+            hi = h2;
+        }
+        if (pt == 0 && v < R) lam[v] = fma(0.5, hi - lo, lo);
     }
     __syncthreads();
     return bound;
