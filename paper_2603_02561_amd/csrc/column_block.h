@@ -143,10 +143,9 @@ struct EigCfg {
     static constexpr size_t own_floats = base_floats + scratch_floats > stage_floats ? base_floats + scratch_floats : stage_floats;
     static constexpr size_t lds_floats = own_floats > direct_floats ? own_floats : direct_floats;
     // Workgroups that registers and LDS let share a compute unit, which is what counts with more users than compute
-    // units: the waves of one fill the gaps in the chains of the others.  1024 users at d = 64: r = 8 137 us with one, 84 with
-    // six; r = 24, direct, 279 and 197 with two (where iterating takes 168 for inputs of rank r, 215 to 290 for
-    // singular values ~ k^-1/2 and k^-1).  r > 32 takes the eigenvectors in one pass and 86 KB for it: alone
-    // on its compute unit it is as fast for many users (r = 40: 309) as iterating is at best.
+    // units: the waves of one fill the gaps in the chains of the others.  1024 users at d = 64: r = 8 78 us with
+    // two, 97 with three, whose 80 registers spill 46 (r = 16 121 and 151); r = 20, direct, 172 with two.  r > 32 takes the
+    // eigenvectors in one pass and 104 KB for it: alone on its compute unit 274 (r = 40).
     static constexpr int groups = D == 64 && !ritz && L <= 40 ? 2 : 1;
     static_assert(groups * (sizeof(float) * lds_floats + 1024) <= 160 * 1024, "LDS");
 };

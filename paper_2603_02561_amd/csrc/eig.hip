@@ -24,9 +24,9 @@
 // The block stays in registers, a wave holding whole rows of it, which is how the products leave it and how the basis wants
 // it; columns of floats in LDS exist only where a Ritz step or a sweep needs them.  What bounds the phase is latency:
 // factorizations of the panels, the reduction of the dense solver and Jacobi sweeps are chains of dependent steps
-// (d = 128, 40 columns, thousands of cycles: staging and start 9, four products 15, two bases 36, Ritz step 114,
-// checks and output 9; with the block in LDS, products on the float instruction and a modified Gram-Schmidt pass over the
-// columns 18, 30, 56, 118, 28; 64 users 109 -> 84 us, d = 256 178 -> 122).  A wave that has its SIMD to itself issues an
+// (d = 128, 40 columns, thousands of cycles: staging and start 9, four products 16, two bases 38, Ritz step 109,
+// checks and output 10; with the block in LDS, products on the float instruction and a modified Gram-Schmidt pass over the
+// columns 18, 30, 56, 118, 28; 64 users 109 -> 83 us, d = 256 178 -> 118).  A wave that has its SIMD to itself issues an
 // instruction in five cycles, so the chains count their instructions; dozens of lane addresses that the compiler formed ahead
 // of the loop and then kept in scratch cost as much as a Gram-Schmidt pass (fresh_tid).  The
 // kernel runs eight waves (two per SIMD), gives every column pair of a sweep a team of up to 16

@@ -563,7 +563,7 @@ __device__ __forceinline__ double tri_values_even(const double* dd, const double
 // half around the zero of the line through the determinants at the ends, at distances that the last round's miss
 // suggests (the miss of that zero falls with the square of the width).  Counts decide what is kept, so a bad guess costs a
 // round that cuts to a fifth or ninth.  Five to eight rounds, where cutting into 2 TP + 1 parts takes 10 or 13: 31 -> 25
-// thousand cycles at 40 columns, 38 -> 31 at 64, 91 -> 60 at 128.  Up to 32 columns a round of counts is so short that what
+// thousand cycles at 40 columns, 38 -> 28 at 64, 91 -> 60 at 128.  Up to 32 columns a round of counts is so short that what
 // the guess costs (two hundred instructions) is not saved, and the parts stay even (24 columns: 14 thousand against 16).
 // Returns the scale (0: the matrix is zero).
 template <int N, int TP>
