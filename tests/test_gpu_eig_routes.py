@@ -74,6 +74,29 @@ def test_rank_below_r(lib, d, r, ranks, size):
         assert np.all(S[b][k:] < 4e-3 * S[b][0])      # what is left is the rounding of X and G
 
 
+# spectra that are hard on the search for eigenvalues, at the widths of the dense solver (24 to 48 columns in the Ritz step, 64 and
+# 128 directly): several of them between two points of the grid (pairs, levels), alone in an interval with the next one
+# close to its end (pairs), at the top of the interval searched (large), and over the whole range (geometric)
+# (An error of 3e-7 in an eigenvalue, relative to the largest, is one of 3e-7 / 2 s_k in s_k: 1e-6 at 0.15.  With small ones crowded
+# at 0.004 the residual that ends the iteration, 5e-6, allows 6e-4 there, and 3e-4 is met.)
+@pytest.mark.parametrize("d,r", [(64, 12), (64, 20), (64, 48), (128, 16), (128, 24), (128, 32), (128, 40), (128, 64), (256, 32)])
+@pytest.mark.parametrize("kind", ["geometric", "pairs", "levels", "large"])
+def test_spectra(lib, d, r, kind):
+    g = np.random.default_rng(7 * d + r)
+    k = np.arange(r)
+    sigma = {"geometric": 0.005 ** (k / (r - 1)),
+             "pairs": (1.0 + (k // 2)) ** -0.5 * (1.0 + 1e-5 * (k % 2)),
+             "levels": np.where(k < r // 2, 1.0, 0.1) * (1.0 + 1e-4 * g.standard_normal(r)),
+             "large": np.where(k == 0, 1.0, 0.3 - 0.15 * k / r)}[kind]
+    X = np.empty((2, 500, d), dtype=np.float32)
+    for b in range(2):
+        U, _ = np.linalg.qr(g.standard_normal((500, r)))
+        W, _ = np.linalg.qr(g.standard_normal((d, r)))
+        X[b] = (U * (20.0 * sigma)) @ W.T
+    print(f"[case] spectrum {kind} d={d} r={r}", flush=True)
+    check(X, *factors(lib, X, r), r)
+
+
 @pytest.mark.parametrize("d,r", [(64, 12), (64, 40), (128, 24), (128, 64), (256, 16)])
 def test_coinciding_eigenvalues(lib, d, r):
     """Rows that are unit vectors: G is diagonal with integer entries, several of them equal."""
