@@ -23,7 +23,9 @@ namespace solar {
 
 constexpr int kTriThreads = 512;
 constexpr int kTriWaves = 4;   // waves that hold the matrix
-constexpr double kTriTiny = 1.0e-180;
+// What a column's sum of squares starts at (1e-180 in each of 64 lanes), so that a column of zeros still gives a proper reflector:
+// u^2 = kTriSeed, and with half of it taken off h = u^2 / 2.  The loop of the reduction and the pass behind it must agree in this.
+constexpr double kTriSeed = 6.4e-179;
 
 template <int CTRL>
 __device__ __forceinline__ double dpp_mov64(double v) {
@@ -222,7 +224,7 @@ __device__ __forceinline__ void tri_steps(TriRows<N>& a, TriState<N>& st, double
 #pragma unroll 1
     for (int k = K0; k < K1; ++k) {
         const int k1 = k + 1;
-        double u[NC], s2 = kTriTiny;                    // a column of zeros still gives a reflector
+        double u[NC], s2 = kTriSeed / 64;
 #pragma unroll
         for (int c = C0; c < NC; ++c) {
             u[c] = st.x[c] * unit(col + 64 * c > k);
@@ -262,7 +264,7 @@ __device__ __forceinline__ void tri_steps(TriRows<N>& a, TriState<N>& st, double
             st.ur[c] = bpermute64(own, u[c]);
         }
         SOLAR_TRI_FENCE;
-        const double inv = rcp64(fma(-alpha, g, s2) - 32.0 * kTriTiny);
+        const double inv = rcp64(fma(-alpha, g, s2) - kTriSeed / 2);
         if (wave == ((k1 >> 2) & (W - 1))) {            // the next pivot row is one of this wave's
 #pragma unroll
             for (int c = C0; c < NC; ++c)
@@ -374,14 +376,14 @@ __device__ __forceinline__ void tri_reduce(TriRows<N>& a, double* ex, double* U,
 #pragma unroll 1
     for (int k = tid >> 3; k < N - 1; k += kTriThreads / 8) {
         double* uk = U + tri_row(N, k);
-        double s2 = u == 0 ? kTriTiny : 0.0;
+        double s2 = u == 0 ? kTriSeed : 0.0;
         for (int j = k + 1 + u; j < N; j += 8) s2 = fma(uk[j], uk[j], s2);
         s2 = team_sum64<8>(s2);
         const double alpha = uk[k + 1], g = k < N - 2 ? -copysign(s2 * rsq64(s2), alpha) : alpha;
         if (u == 0) {
             dd[k] = uk[k];
             ee[k] = g;
-            ih[k] = rcp64(fma(-alpha, g, s2) - 32.0 * kTriTiny);
+            ih[k] = rcp64(fma(-alpha, g, s2) - kTriSeed / 2);
             uk[k + 1] = alpha - g;
         }
     }

@@ -97,6 +97,38 @@ def test_spectra(lib, d, r, kind):
     check(X, *factors(lib, X, r), r)
 
 
+# Householder reductions that meet columns of exact zeros: a Gram matrix that is diagonal or falls into blocks, in the order of X
+# and permuted (users 0 and 1).  No two eigenvalues coincide, so d = 64, r >= 17 and d = 128, r >= 41 are solved directly.
+@pytest.mark.parametrize("d,r", [(64, 8), (64, 16), (64, 17), (64, 20), (64, 48), (64, 64), (128, 32), (128, 41), (128, 64), (256, 32)])
+@pytest.mark.parametrize("kind", ["diagonal", "first column zero", "first column alone", "two blocks", "three columns zero"])
+def test_zero_columns(lib, d, r, kind):
+    g = np.random.default_rng(3 * d + r)
+    print(f"[case] zero columns: {kind} d={d} r={r}", flush=True)
+    w = (1.0 + np.arange(d)) ** -0.5
+    X = np.empty((2, 400, d), dtype=np.float32)
+    for b in range(2):
+        order = np.arange(d) if b == 0 else g.permutation(d)
+        x = g.standard_normal((400, d)) * w[order]
+        if kind == "diagonal":
+            x = np.zeros((400, d))
+            x[np.arange(d), np.arange(d)] = w[order]
+        elif kind == "first column zero":
+            x[:, 0] = 0.0
+        elif kind == "first column alone":
+            x[:, 0] = 0.0
+            x[0] = 0.0
+            x[0, 0] = 15.0
+        elif kind == "two blocks":
+            # for user 0 one in front of the other in the solver's order of the columns, for user 1 anyhow
+            half = np.arange(d) % (d // 16) < d // 32 if b == 0 else order < d // 2
+            x[:200, half] = 0.0
+            x[200:, ~half] = 0.0
+        else:
+            x[:, order[[1, d // 3, d // 2]]] = 0.0
+        X[b] = x
+    check(X, *factors(lib, X, r), r)
+
+
 @pytest.mark.parametrize("d,r", [(64, 12), (64, 40), (128, 24), (128, 64), (256, 16)])
 def test_coinciding_eigenvalues(lib, d, r):
     """Rows that are unit vectors: G is diagonal with integer entries, several of them equal."""
