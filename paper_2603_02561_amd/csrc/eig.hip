@@ -87,6 +87,27 @@ __device__ __forceinline__ void split3_eight(v4f lo, v4f hi, v4u (&o)[3]) {
         }
 }
 
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_rows(float v) {     // v where the rows of ROWS do not take part
+    const int i = __float_as_int(v);
+    return __int_as_float(__builtin_amdgcn_update_dpp(i, i, CTRL, ROWS, 0xf, false));
+}
+// In lane 63: the largest of the wave's values, none of them negative.
+__device__ __forceinline__ float wave_top(float v) {
+    v = fmaxf(v, dpp_mov<0xB1>(v));
+    v = fmaxf(v, dpp_mov<0x4E>(v));
+    v = fmaxf(v, dpp_mov<0x141>(v));
+    v = fmaxf(v, dpp_mov<0x140>(v));
+    v = fmaxf(v, dpp_rows<0x142, 0xa>(v));               // row_bcast15: rows 1 and 3 take over the row before
+    return fmaxf(v, dpp_rows<0x143, 0xc>(v));            // row_bcast31
+}
+
+// The iteration runs on 2^-ge G, with ge even and the largest entry, which is on the diagonal, brought to about one: squares of
+// columns of G Q, in the panels, the sweeps and the residuals, would leave the range of a float for s_1 above 4e9 or below
+// 1e-10, and the factors would come out as those of a zero matrix, or as NaN.  A power of two changes no rounding.
+__device__ __forceinline__ int gram_exponent(int top_bits) { return min(top_bits >> 23 & ~1, 252) - 126; }
+__device__ __forceinline__ float gram_scale(int ge) { return __int_as_float((127 - ge) << 23); }
+
 // G as the operand of G Q: the wave's rows, three bf16 terms per value (what is left after three is below 2^-26), lane
 // (i, g) holding entries 32 k + 8 g .. + 7 of row i of a block in chunk k.  Up to d = 128 they stay in registers for the
 // whole solve; at d = 256 that would take 192 of them, so the rows come from L2 for every product, three chunks ahead, and
@@ -99,11 +120,11 @@ struct GramRows {
     v4f ring[RING][NB][2];
     const float* rows;                                   // of this lane, in memory (d = 256)
 
-    __device__ __forceinline__ void keep(const float* Gs, int stride, int wave, int i16, int g) {
+    __device__ __forceinline__ void keep(const float* Gs, int stride, float scale, int wave, int i16, int g) {
 #pragma unroll
         for (int k = 0; k < NK; ++k) {
             const float* src = Gs + (16 * wave + i16) * stride + 32 * k + 8 * g;
-            split3_eight(*reinterpret_cast<const v4f*>(src), *reinterpret_cast<const v4f*>(src + 4), a[k]);
+            split3_eight(scale * *reinterpret_cast<const v4f*>(src), scale * *reinterpret_cast<const v4f*>(src + 4), a[k]);
         }
     }
     __device__ __forceinline__ void load(int k) {
@@ -144,20 +165,21 @@ __device__ __forceinline__ void store_images(uint16_t* img, const typename Itera
         }
 }
 
-// z = (G - shift I) q on the bf16 instruction: the six products of terms above 2^-25 of a product of two values, smallest
-// first.  Against the float instruction (256 cycles per 32 rows and 16 x 16 block instead of 96, and G from LDS) the four
+// z = (2^-ge G - shift I) q on the bf16 instruction: the six products of terms above 2^-25 of a product of two values, smallest
+// first.  (Rows that stay in registers have the factor in them; otherwise it is applied behind the products, a twentieth of the
+// multiplications that the rows would take on their way.)  Against the float instruction (256 cycles per 32 rows and 16 x 16 block instead of 96, and G from LDS) the four
 // products of a solve at d = 128, 40 columns take 15 thousand cycles instead of 30, at d = 256 65
 // instead of 140.
 template <int D, int LP>
 __device__ __forceinline__ void multiply(GramRows<D>& G, const uint16_t* img, const typename Iterate<D, LP>::Regs& q,
-                                         float shift, typename Iterate<D, LP>::Regs& z) {
+                                         float shift, int ge, typename Iterate<D, LP>::Regs& z) {
     const int lane = fresh_tid() & 63, i16 = lane & 15, g = lane >> 4;
     using I = Iterate<D, LP>;
     constexpr int NB = I::NB, NC = I::NC, NK = D / 32;
 #pragma unroll
     for (int n = 0; n < NB; ++n)
 #pragma unroll
-        for (int c = 0; c < NC; ++c) z[n][c] = -shift * q[n][c];
+        for (int c = 0; c < NC; ++c) z[n][c] = -(GramRows<D>::kKept ? shift : __builtin_amdgcn_ldexpf(shift, ge)) * q[n][c];
     const uint16_t* base = img + i16 * I::LDI + 8 * g;
 #pragma unroll
     for (int k = 0; k < NK; ++k) {
@@ -183,6 +205,13 @@ __device__ __forceinline__ void multiply(GramRows<D>& G, const uint16_t* img, co
             for (int n = 0; n < NB; ++n)
 #pragma unroll
                 for (int c = 0; c < NC; ++c) z[n][c] = mfma16x16x32bf16(a[n][kA[p]], b[c][kB[p]], z[n][c]);
+    }
+    if constexpr (!GramRows<D>::kKept) {
+        const float scale = gram_scale(ge);
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+#pragma unroll
+            for (int c = 0; c < NC; ++c) z[n][c] *= scale;
     }
 }
 
@@ -505,12 +534,14 @@ __global__ __launch_bounds__(kEigThreads, (EigCfg<D, L, MANY>::groups * kEigWave
     float* scratch = reinterpret_cast<float*>(order + LP);   // of the basis, the column sums and the dense solver, in turn
     float* Gs = smem;                                    // [D][GS] at the start, when C::GLDS
     __shared__ int sh_bits;
+    __shared__ int sh_ge;
+    __shared__ int sh_top[kEigWaves];                    // largest entry of G that a wave met, as bits
     __shared__ float sh_rate[2];
     __shared__ double sh_scal[1];
     __shared__ int sh_twist[64];
     const int tid = threadIdx.x, lane = tid & 63, i16 = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const bool holds = wave < I::W;
+    const bool holds = I::W == kEigWaves || wave < I::W;   // known from d = 128 on: no branch around what the waves do
     const int b = blockIdx.x;
     const float* Gb = G + (size_t)b * D * D;
 
@@ -529,6 +560,7 @@ __global__ __launch_bounds__(kEigThreads, (EigCfg<D, L, MANY>::groups * kEigWave
     // `meanwhile` runs while the loads are on their way.
     auto stage = [&](auto&& meanwhile) __attribute__((always_inline)) {
         v4f probe = v4f{0.f, 0.f, 0.f, 0.f};             // NaN where an entry was not finite
+        float top = 0.f;
         if constexpr (C::GLDS) {
             // G from the split-N partial blocks of the Gram kernel: per chunk and fragment pair
             // (s1 <= s2 of CPL = D/16 column fragments) a 16 x 16 block in MFMA layout, lane
@@ -570,7 +602,10 @@ __global__ __launch_bounds__(kEigThreads, (EigCfg<D, L, MANY>::groups * kEigWave
                     while (rest >= CPL - s1) { rest -= CPL - s1; ++s1; }
                     const int s2 = s1 + rest;
 #pragma unroll
-                    for (int t = 0; t < 4; ++t) probe[t] = fmaf(acc[i][t], 0.f, probe[t]);
+                    for (int t = 0; t < 4; ++t) {
+                        probe[t] = fmaf(acc[i][t], 0.f, probe[t]);
+                        top = fmaxf(top, acc[i][t]);
+                    }
                     const int a = 16 * s1 + 4 * g, c = 16 * s2 + i16;
 #pragma unroll
                     for (int t = 0; t < 4; ++t) Gs[(a + t) * C::GS + c] = acc[i][t];
@@ -582,7 +617,10 @@ __global__ __launch_bounds__(kEigThreads, (EigCfg<D, L, MANY>::groups * kEigWave
             static_assert(D <= kEigThreads, "a thread to an entry of the diagonal");
             meanwhile();
             probe[0] = v * 0.f;
+            top = fmaxf(v, 0.f);
         }
+        top = wave_top(top);
+        if (lane == 63) sh_top[wave] = __float_as_int(top);
         return (probe[0] + probe[1]) + (probe[2] + probe[3]) != 0.f;
     };
     // A G with entries that are not finite has no factors.  Neither solver would say so: norms and maxima drop NaN,
@@ -627,10 +665,17 @@ __global__ __launch_bounds__(kEigThreads, (EigCfg<D, L, MANY>::groups * kEigWave
         draw();
     }
     GramRows<D> Gr;
-    if constexpr (GramRows<D>::kKept) {
-        if (holds) Gr.keep(Gs, C::GS, wave, i16, g);
-    } else {
-        Gr.rows = Gb + (size_t)(16 * wave + i16) * D + 8 * g;
+    {
+        int top = 0;
+#pragma unroll
+        for (int w = 0; w < kEigWaves; ++w) top = max(top, sh_top[w]);
+        const int ge = gram_exponent(top);
+        if (tid == 0) sh_ge = ge;                        // read where it is needed: a register less
+        if constexpr (GramRows<D>::kKept) {
+            if (holds) Gr.keep(Gs, C::GS, gram_scale(ge), wave, i16, g);
+        } else {
+            Gr.rows = Gb + (size_t)(16 * wave + i16) * D + 8 * g;
+        }
     }
     __syncthreads();                                     // G is in registers
 
@@ -661,7 +706,7 @@ __global__ __launch_bounds__(kEigThreads, (EigCfg<D, L, MANY>::groups * kEigWave
             shift = 0.5f * cheb_b * (1.f + __cosf((2 * cheb_j + 1) * 1.57079632679f / cheb_k));
             ++cheb_j;
         }
-        if (holds) multiply<D, LP>(Gr, img, q, shift, z);
+        if (holds) multiply<D, LP>(Gr, img, q, shift, GramRows<D>::kKept ? 0 : __builtin_amdgcn_readfirstlane(sh_ge), z);
         if (have_ritz) {
             // Rayleigh quotients and residuals of the pairs
             double qz[NC];                               // what S comes from: no rounding beside that of z
@@ -830,7 +875,7 @@ __global__ __launch_bounds__(kEigThreads, (EigCfg<D, L, MANY>::groups * kEigWave
         if (u == 0 && c < L && rankv[c] < r) {
             resid[c] = (best & 1) ? -1.f : 1.f;
             order[rankv[c]] = c;
-            S[(size_t)b * r + rankv[c]] = sqrtf(fmaxf(theta[c], 0.f));
+            S[(size_t)b * r + rankv[c]] = __builtin_amdgcn_ldexpf(sqrtf(fmaxf(theta[c], 0.f)), sh_ge / 2);
         }
     }
     __syncthreads();

@@ -129,6 +129,27 @@ def test_zero_columns(lib, d, r, kind):
     check(X, *factors(lib, X, r), r)
 
 
+# Inputs of every size whose Gram matrix a float holds, on every route (257 users: sweeps at d = 64, r = 12; user 1 has coinciding
+# eigenvalues, which leads wide and medium blocks back to the sweeps).  A size that is a power of two changes no rounding.
+@pytest.mark.parametrize("d,r,B", [(64, 8, 2), (64, 12, 2), (64, 12, 257), (64, 20, 2), (64, 64, 2), (128, 8, 2), (128, 32, 2),
+                                   (128, 64, 2), (256, 16, 2), (256, 32, 2)])
+def test_size_of_inputs(lib, d, r, B):
+    g = np.random.default_rng(d + r)
+    x = np.zeros((2, 300, d), dtype=np.float32)
+    x[0] = g.standard_normal((300, r)) / np.sqrt(1 + np.arange(r)) @ g.standard_normal((r, d))
+    x[1, np.arange(d), np.arange(d)] = 16.0 * np.where(np.arange(d) < r, (1 + np.arange(d) // 3) ** -0.5, 0.01)
+    X = np.tile(x, (-(-B // 2), 1, 1))[:B]
+    info0, S0, V0 = factors(lib, X, r)
+    check(x[:1], info0[:1], S0[:1], V0[:1], r)
+    for k in (-50, -33, -20, 23, 33, 43, 53):
+        print(f"[case] size 2^{k} d={d} r={r} B={B}", flush=True)
+        info, S, V = factors(lib, np.float32(2.0 ** k) * X, r)
+        assert np.array_equal(info, info0), (k, info)
+        check(np.float32(2.0 ** k) * x[:1], info[:1], S[:1], V[:1], r)
+        if k > -50:                                       # below, low bits of the products of X^T X are denormal
+            assert np.array_equal(S, S0 * 2.0 ** k) and np.array_equal(V, V0), k
+
+
 @pytest.mark.parametrize("d,r", [(64, 12), (64, 40), (128, 24), (128, 64), (256, 16)])
 def test_coinciding_eigenvalues(lib, d, r):
     """Rows that are unit vectors: G is diagonal with integer entries, several of them equal."""
