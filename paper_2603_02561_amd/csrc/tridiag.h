@@ -46,7 +46,7 @@ __device__ __forceinline__ double readlane64(double v, int lane) {
 
 // a_k += x[lane I + k of the row of 16 lanes] * y: the broadcast is an operand of the multiply-add.  It may not read what
 // the vector ALU wrote in the last two instructions, which the compiler does not see to in here: hence the wait in front, and
-// one statement for four (or eight) of them.
+// one statement for four of them (whose results may therefore not share a register with an operand, "&").
 #define SOLAR_FMAC_BCAST(A, X, Y, I) "v_fmac_f64_dpp %" #A ", %" #X ", %" #Y " row_newbcast:%" #I " row_mask:0xf bank_mask:0xf\n\t"
 template <int I>
 __device__ __forceinline__ void fmac_bcast64(double& a0, double x, double y) {
@@ -55,14 +55,14 @@ __device__ __forceinline__ void fmac_bcast64(double& a0, double x, double y) {
 template <int I>
 __device__ __forceinline__ void fmac_bcast64(double& a0, double& a1, double& a2, double& a3, double x, double y) {
     asm("s_nop 1\n\t" SOLAR_FMAC_BCAST(0, 4, 5, 6) SOLAR_FMAC_BCAST(1, 4, 5, 7) SOLAR_FMAC_BCAST(2, 4, 5, 8) SOLAR_FMAC_BCAST(3, 4, 5, 9)
-        : "+v"(a0), "+v"(a1), "+v"(a2), "+v"(a3)
+        : "+&v"(a0), "+&v"(a1), "+&v"(a2), "+&v"(a3)
         : "v"(x), "v"(y), "n"(I), "n"(I + 1), "n"(I + 2), "n"(I + 3));
 }
 // p += the sum of x[lane I + k of the row of 16 lanes] * y_k
 template <int I>
 __device__ __forceinline__ void fmac_bcast64_sum(double& p, double x, double y0, double y1, double y2, double y3) {
     asm("s_nop 1\n\t" SOLAR_FMAC_BCAST(0, 1, 2, 6) SOLAR_FMAC_BCAST(0, 1, 3, 7) SOLAR_FMAC_BCAST(0, 1, 4, 8) SOLAR_FMAC_BCAST(0, 1, 5, 9)
-        : "+v"(p)
+        : "+&v"(p)
         : "v"(x), "v"(y0), "v"(y1), "v"(y2), "v"(y3), "n"(I), "n"(I + 1), "n"(I + 2), "n"(I + 3));
 }
 #undef SOLAR_FMAC_BCAST
