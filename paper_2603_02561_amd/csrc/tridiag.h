@@ -519,6 +519,7 @@ __device__ __forceinline__ void tri_scale(const double* dd, const double* ee, do
 template <int N, int TP>
 __device__ __forceinline__ double tri_values_even(const double* dd, const double* ee, double* es, double2* t, double* lam,
                                                   double* scal, int* cnt, int R) {
+    static_assert(TP == 8, "32 eigenvalues at most");
     const int tid = fresh_tid(), lane = tid & 63;
     tri_scale<N>(dd, ee, es, t, scal);
     __syncthreads();
@@ -539,7 +540,7 @@ __device__ __forceinline__ double tri_values_even(const double* dd, const double
 #pragma unroll
         for (int s = 256; s; s >>= 1) at += cnt[at + s] > k ? s : 0;
         double lo = fma(kStep, (double)at, kLo), w = kStep;
-        constexpr int rounds = TP == 8 ? 10 : 13;        // 17^10 > 2^40, 9^13 > 2^41, after the first 2^9
+        constexpr int rounds = 10;                       // 17^10 > 2^40, after the first 2^9
 #pragma unroll 1
         for (int it = 0; it < rounds; ++it) {
             w *= 1.0 / (2 * TP + 1);
@@ -569,9 +570,8 @@ __device__ __forceinline__ double tri_values_even(const double* dd, const double
 // the guess costs (two hundred instructions) is not saved, and the parts stay even (24 columns: 14 thousand against 16).
 // Returns the scale (0: the matrix is zero).
 template <int N, int TP>
-__device__ __forceinline__ double tri_values(const double* dd, const double* ee, double* es, double2* t, double* lam,
-                                             double* scal, double* work, int R) {
-    if constexpr (N <= 32) return tri_values_even<N, TP>(dd, ee, es, t, lam, scal, reinterpret_cast<int*>(work), R);
+__device__ __forceinline__ double tri_values_guided(const double* dd, const double* ee, double* es, double2* t, double* lam,
+                                                    double* scal, double* work, int R) {
     const int tid = fresh_tid(), lane = tid & 63;
     int* cnt = reinterpret_cast<int*>(work);             // [512], [512] and [512]: what the minors say on the grid
     int* ex2 = cnt + 512;
@@ -600,10 +600,9 @@ __device__ __forceinline__ double tri_values(const double* dd, const double* ee,
         det[tid + 256] = b.m;
     }
     __syncthreads();
-    if (tid < 512) {
-        const int top = cnt[tid] < R ? cnt[tid] : R;
-        for (int k = tid < 511 ? cnt[tid + 1] : 0; k < top; ++k) pos[k] = tid;
-    }
+    static_assert(kTriThreads == 512, "a thread to a point");
+    const int over = cnt[tid] < R ? cnt[tid] : R;
+    for (int k = tid < 511 ? cnt[tid + 1] : 0; k < over; ++k) pos[k] = tid;
     __syncthreads();
     if (tid < 256) {
         const int v = tid / TP, pt = tid % TP;
@@ -647,6 +646,13 @@ __device__ __forceinline__ double tri_values(const double* dd, const double* ee,
     }
     __syncthreads();
     return bound;
+}
+
+template <int N, int TP>
+__device__ __forceinline__ double tri_values(const double* dd, const double* ee, double* es, double2* t, double* lam,
+                                             double* scal, double* work, int R) {
+    if constexpr (N <= 32) return tri_values_even<N, TP>(dd, ee, es, t, lam, scal, reinterpret_cast<int*>(work), R);
+    else return tri_values_guided<N, TP>(dd, ee, es, t, lam, scal, work, R);
 }
 
 // multipliers of the factorization of T - l I from the top (DIR = 1) or the bottom (DIR = -1)
