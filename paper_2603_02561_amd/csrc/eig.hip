@@ -461,6 +461,7 @@ __device__ __forceinline__ bool eig_direct(const float* Gs, double* sm, double* 
                                            float* V) {
     constexpr int TB = RMAX <= 32 && D == 128 ? 16 : 8;
     using T = TriCfg<D, RB>;
+    static_assert(RMAX * TB <= kEigThreads, "a team to a vector");
     const TriLds<D, RB> w(sm, nullptr);
     const int tid = fresh_tid(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     TriRows<D> a;
@@ -652,7 +653,8 @@ __global__ __launch_bounds__(kEigThreads, (EigCfg<D, L, MANY>::groups * kEigWave
     bool by_ritz = true;
     if constexpr (C::direct) {
         if (prm.direct) {
-            if (eig_direct<D, L - 8, C::RB, C::GS>(Gs, reinterpret_cast<double*>(smem), sh_scal, sh_twist, r,
+            constexpr int RMAX = L == D ? D : L - 8;     // a block as wide as G serves every rank up to d
+            if (eig_direct<D, RMAX, C::RB, C::GS>(Gs, reinterpret_cast<double*>(smem), sh_scal, sh_twist, r,
                                             S + (size_t)b * r, V + (size_t)b * D * r)) {
                 if (tid == 0 && info) info[b] = 0;
                 return;
