@@ -16,6 +16,12 @@ constexpr int kEigWaves = kEigThreads / 64;
 // A column of the iterate whose norm falls below this fraction of the largest column norm
 // is rounding noise of the float Gram matrix (about sqrt(d) * 2^-24 relative) and is dropped.
 constexpr float kDeadRel = 1.0e-5f;
+// The same between power steps, relative to the largest column of the first panel, which mixes all eigenvectors and is up to four
+// times the largest eigenvalue, while what is left of a column when its turn comes in the panels can be a fraction of its own: with
+// 1e-5 here too, values just above that limit were lost (d = 128, r = 40: s_k = k^-3/2, the last at 3.95e-3 s_1, for 467 of
+// 512 users, levels of six down to 3.9e-3 for 29; now for none).  At 1e-6 columns of rounding noise make first checks fail, 1.3 to 1.8 times
+// as long; at 3e-6 the slowest spectrum found takes 1.09 times as long (0.8^k, d = 128, r = 40).
+constexpr float kBasisDead = 3.0e-6f;
 // Rotations are skipped below kSkipCos.  The Jacobi phase converges quadratically: a sweep whose
 // largest |cos| was c leaves about c^2 behind (L * c^2 at worst), so the phase ends after the
 // first sweep that met no |cos| above kSweepDone = 5e-4, with a few 1e-6 left; the residual

@@ -332,7 +332,7 @@ __device__ __forceinline__ void panel_solve(float (&z)[NV], const float (&m)[16]
 // Gram matrix of a panel is formed and factored in double precision, Q_p = Z_p R^-1, and Q_p is projected out of the
 // columns after it, both on the float instruction.  Only the factorization, 16 steps of one wave, is a
 // chain; column by column (modified Gram-Schmidt, a team of lanes per column) a pass was one chain of all columns: 28
-// thousand cycles at d = 128, 40 columns, and 45 at d = 256, now 17 and 28.  Columns that collapse below kDeadRel of the largest of the first panel are dropped (zero).
+// thousand cycles at d = 128, 40 columns, and 45 at d = 256, now 17 and 28.  Columns that collapse below kBasisDead of the largest of the first panel are dropped (zero).
 // pivot2[j] receives the squared norm that column j had when it was normalized (the squared diagonal of the
 // triangular factor, which tends to the eigenvalues of G in decreasing order).  No barrier before the first
 // and after the last access to LDS.
@@ -375,7 +375,7 @@ __device__ __forceinline__ void basis_panels(typename Iterate<D, LP>::Regs& z, t
             top = fmaxf(top, dpp_mov<0x4E>(top));
             top = fmaxf(top, dpp_mov<0x141>(top));
             top = fmaxf(top, dpp_mov<0x140>(top));
-            dead2 = (double)kDeadRel * (double)kDeadRel * (double)top;
+            dead2 = (double)kBasisDead * (double)kBasisDead * (double)top;
         }
         float m[16];
         panel_steps<0, KN>(a, m, dead2);

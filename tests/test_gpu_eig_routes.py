@@ -150,6 +150,24 @@ def test_size_of_inputs(lib, d, r, B):
             assert np.array_equal(S, S0 * 2.0 ** k) and np.array_equal(V, V0), k
 
 
+# Many values a little above the limit of 1e-5 of the largest eigenvalue (3.2e-3 of s_1), and more below it: levels of six down to
+# 1.5e-5, and (k + 1)^-3, 1.56e-5 at k = 39.  None above it may be dropped.  S is met to 1e-4 of s_1; a value that is lost is 3.9e-3 off.
+@pytest.mark.parametrize("kind,d,r", [("levels", 64, 48), ("levels", 128, 32), ("levels", 128, 40), ("levels", 256, 32),
+                                      ("power", 128, 40)])
+def test_values_above_the_limit(lib, kind, d, r):
+    print(f"[case] values above the limit: {kind} d={d} r={r}", flush=True)
+    g = np.random.default_rng(d * r)
+    U, _ = np.linalg.qr(g.standard_normal((64, 300, d)))
+    W, _ = np.linalg.qr(g.standard_normal((64, d, d)))
+    k = np.arange(d)
+    sigma, above = (4.0 ** -(k // 6), 30) if kind == "levels" else ((1.0 + k) ** -1.5, 40)
+    X = np.matmul(U * (30.0 * sigma), W.transpose(0, 2, 1)).astype(np.float32)
+    info, S, V = factors(lib, X, r)
+    assert np.all(info == 0), info
+    lost = np.abs(S[:, :above] / 30.0 - sigma[:above]).max(axis=1) > 1e-3
+    assert not np.any(lost), np.flatnonzero(lost)
+
+
 @pytest.mark.parametrize("d,r", [(64, 12), (64, 40), (128, 24), (128, 64), (256, 16)])
 def test_coinciding_eigenvalues(lib, d, r):
     """Rows that are unit vectors: G is diagonal with integer entries, several of them equal."""
