@@ -31,6 +31,11 @@ constexpr float kBasisDead = 3.0e-6f;
 // the others, so the launch is no shorter with 1e-3.)
 constexpr float kSkipCos = 1.0e-7f;
 constexpr float kSweepDone = 5.0e-4f;
+// The same where coinciding eigenvalues led to the sweeps: a rotation between two of those is by up to 45 degrees and carries what the
+// sweep met over to columns that it had dealt with, so what is left is of the order of c and not of c^2.  With 5e-4 V^T V was more than
+// 2e-5 off for one user in eight with six-fold eigenvalues, 3e-4 at most; now 1e-6.  Costs up to 8 % where pairs coincide, and saves as much
+// as it costs or more with larger groups, whose checks failed for it (d = 128, r = 64: 530 -> 444 us).
+constexpr float kSweepDoneTied = 2.0e-5f;
 
 __host__ __device__ constexpr int pow2floor_c(int x) {
     int p = 1;

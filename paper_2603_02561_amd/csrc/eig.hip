@@ -832,7 +832,7 @@ __global__ __launch_bounds__(kEigThreads, (EigCfg<D, L, MANY>::groups * kEigWave
             const float dead2 = kDeadRel * kDeadRel * column_norms();
             for (int sw = 0; sw < prm.sweeps; ++sw) {
                 const float mine = jacobi_sweep<D, L>(Zc, dead2);
-                const bool any = __syncthreads_or(mine > prm.tol_orth);
+                const bool any = __syncthreads_or(mine > (C::ritz || C::direct ? prm.tol_orth_tied : prm.tol_orth));
                 if (!any) { orth_ok = true; break; }
             }
             // normalize; drop columns that are numerically zero
@@ -938,6 +938,7 @@ EigParams eig_default_params() {
     EigParams p;
     p.tol_res = 5.0e-6f;
     p.tol_orth = kSweepDone;
+    p.tol_orth_tied = kSweepDoneTied;
     p.max_iter = 40;
     p.sweeps = 12;
     p.mgs_steps = 2;

@@ -27,6 +27,7 @@ hipError_t launch_gram(const void* X, const int32_t* lengths, int B, int N, int 
 struct EigParams {
     float tol_res;      // residual tolerance relative to the largest Ritz value
     float tol_orth;     // a sweep whose largest |cos| is below this ends the Jacobi phase
+    float tol_orth_tied;   // the same where the sweeps are the way out for coinciding eigenvalues
     int max_iter;       // cap on power steps
     int sweeps;         // cap on Jacobi sweeps per power step
     int mgs_steps;      // leading power steps after which only a basis is taken instead of a Ritz step

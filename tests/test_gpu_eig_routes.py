@@ -181,6 +181,23 @@ def test_coinciding_eigenvalues(lib, d, r):
     check(X, *factors(lib, X, r), r)
 
 
+# Six-fold eigenvalues, which lead to the sweeps on every route: vectors of one eigenvalue are as orthogonal as others.
+@pytest.mark.parametrize("d,r", [(64, 16), (64, 24), (64, 48), (128, 16), (128, 32), (128, 64), (256, 16), (256, 32)])
+def test_coinciding_levels(lib, d, r):
+    print(f"[case] six-fold eigenvalues d={d} r={r}", flush=True)
+    g = np.random.default_rng(d + 3 * r)
+    U, _ = np.linalg.qr(g.standard_normal((64, 300, d)))
+    W, _ = np.linalg.qr(g.standard_normal((64, d, d)))
+    sigma = 4.0 ** -(np.arange(d) // 6)
+    X = np.matmul(U * (30.0 * sigma), W.transpose(0, 2, 1)).astype(np.float32)
+    info, S, V = factors(lib, X, r)
+    n = min(r, 24)                                        # levels down to 1/64 of s_1
+    check(X, info, S[:, :n], V[:, :, :n], n)
+    n = min(r, 30)
+    VV = np.matmul(V[:, :, :n].transpose(0, 2, 1), V[:, :, :n])
+    assert np.abs(VV - np.eye(n)).max() < 2e-5
+
+
 def test_zero_matrix(lib):
     for d, r in ((64, 8), (64, 40), (128, 16), (128, 64)):
         info, S, V = factors(lib, np.zeros((1, 100, d), dtype=np.float32), r)
