@@ -123,7 +123,9 @@ size_t solar_workspace_bytes(int B, int N, int d, int r, int M, solar_dtype t);
  *                        largest eigenvalue of G) is treated as rank deficiency: it
  *                        comes back as S = 0 with a zero column of V, which is how
  *                        the caller sees that it was dropped; the 1e-4 contract then
- *                        holds against the factorization without it.
+ *                        holds against the factorization without it.  Where the factors are iterated (d = 64,
+ *                        r <= 16; d = 128, r <= 40; d = 256) or wanted values coincide, a component less than a
+ *                        fifth above that limit (3.8e-3 of s_1) may still be dropped.
  *   P        out [B,N,r] = X V, rows at or past the valid length are zero; may be
  *                        NULL if only modes 1 and 2 or solar_svd_attention_from_x
  *                        will be used

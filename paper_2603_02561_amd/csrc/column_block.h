@@ -33,8 +33,8 @@ constexpr float kSkipCos = 1.0e-7f;
 constexpr float kSweepDone = 5.0e-4f;
 // The same where coinciding eigenvalues led to the sweeps: a rotation between two of those is by up to 45 degrees and carries what the
 // sweep met over to columns that it had dealt with, so what is left is of the order of c and not of c^2.  With 5e-4 V^T V was more than
-// 2e-5 off for one user in eight with six-fold eigenvalues, 3e-4 at most; now 1e-6.  Costs up to 8 % where pairs coincide, and saves as much
-// as it costs or more with larger groups, whose checks failed for it (d = 128, r = 64: 530 -> 444 us).
+// 2e-5 off for one user in eight with six-fold eigenvalues, 3e-4 at most; now 1e-6.  It costs 3 to 9 % where pairs
+// coincide and up to 16 % with larger groups, where it also saves checks that failed for it (d = 128: r = 64 502 -> 445 us, r = 16 132 -> 107).
 constexpr float kSweepDoneTied = 2.0e-5f;
 
 __host__ __device__ constexpr int pow2floor_c(int x) {
@@ -143,7 +143,7 @@ struct EigCfg {
     // (16 users, inputs of rank r: d = 128, r = 32 from 142 to 113 us, r = 16 from 82 to 67; d = 256,
     // r = 32 from 253 to 178, of which 55 are the wider reads of the products G Q), except the narrowest,
     // where it is no faster (d = 64, r = 8: 38 us).  It takes the whole register file for one workgroup: at d = 64 the
-    // sweeps, of which three fit a compute unit, are faster for more users than compute units (r = 16, 256 users 52
+    // sweeps, of which two fit a compute unit, are faster for more users than compute units (r = 16, 256 users 52
     // us against 58, 1024 users 196 against 128).
     static constexpr bool ritz = !direct && (D > 64 || L > 16) && !MANY;
     static constexpr size_t ritz_floats = ritz ? 2 * TriLds<ritz ? L : 16, ritz ? L : 16>::kDoublesNoWa : 0;

@@ -26,7 +26,7 @@
 // factorizations of the panels, the reduction of the dense solver and Jacobi sweeps are chains of dependent steps
 // (d = 128, 40 columns, thousands of cycles: staging and start 9, four products 16, two bases 38, Ritz step 109,
 // checks and output 10; with the block in LDS, products on the float instruction and a modified Gram-Schmidt pass over the
-// columns 18, 30, 56, 118, 28; 64 users 109 -> 83 us, d = 256 178 -> 118).  A wave that has its SIMD to itself issues an
+// columns 18, 30, 56, 118, 28; 64 users 109 -> 83 us, d = 256 178 -> 114).  A wave that has its SIMD to itself issues an
 // instruction in five cycles, so the chains count their instructions; dozens of lane addresses that the compiler formed ahead
 // of the loop and then kept in scratch cost as much as a Gram-Schmidt pass (fresh_tid).  The
 // kernel runs eight waves (two per SIMD), gives every column pair of a sweep a team of up to 16
@@ -542,7 +542,8 @@ __global__ __launch_bounds__(kEigThreads, (EigCfg<D, L, MANY>::groups * kEigWave
     __shared__ int sh_twist[64];
     const int tid = threadIdx.x, lane = tid & 63, i16 = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const bool holds = I::W == kEigWaves || wave < I::W;   // known from d = 128 on: no branch around what the waves do
+    // known from d = 128 on: loads and products do not stand behind a branch (d = 256, r = 32, 16 users 119 -> 114 us)
+    const bool holds = I::W == kEigWaves || wave < I::W;
     const int b = blockIdx.x;
     const float* Gb = G + (size_t)b * D * D;
 
