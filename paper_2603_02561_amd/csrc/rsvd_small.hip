@@ -163,7 +163,7 @@ __global__ __launch_bounds__(kEigThreads) void rsvd_small_kernel(
         status = max_sweeps;
         for (int sw = 0; sw < max_sweeps; ++sw) {
             const float mine = jacobi_sweep<D, L>(Zc, dead2);
-            const bool any = __syncthreads_or(mine > kSweepDone);
+            const bool any = __syncthreads_or(mine > kSweepDoneTied);
             if (!any) { status = 0; break; }
         }
         column_norms();

@@ -152,3 +152,26 @@ def test_rsvd_argument_errors(lib):
                                       raise_on_error=False)
     assert rc == 3
     assert lib.solar_rsvd_workspace_bytes(2, 100, 256, 16) == 0   # d = 256 is not supported on this route
+
+
+@pytest.mark.parametrize("d,r", [(64, 64), (128, 48), (128, 64)])
+def test_equal_singular_values(lib, d, r):
+    """Singular values that all coincide: the vectors, which come from sweeps then, are orthogonal to 2e-5 all the same
+    (float products of 24-bit values, and a sweep that meets no cosine above 2e-5 ends the phase)."""
+    import torch
+    print(f"[case] equal singular values d={d} r={r}", flush=True)
+    g = np.random.default_rng(d + r)
+    B, N = 128, 400
+    U, _ = np.linalg.qr(g.standard_normal((B, N, r)))
+    W, _ = np.linalg.qr(g.standard_normal((B, d, r)))
+    X = torch.from_numpy((30.0 * np.matmul(U, W.transpose(0, 2, 1))).astype(np.float32)).cuda()
+    omega = torch.from_numpy(g.standard_normal((B, d, r)).astype(np.float32)).cuda()
+    S, V, P = (torch.empty(s, dtype=torch.float32, device="cuda") for s in ((B, r), (B, d, r), (B, N, r)))
+    info = torch.zeros(B, dtype=torch.int32, device="cuda")
+    ws = torch.empty(lib.solar_rsvd_workspace_bytes(B, N, d, r), dtype=torch.uint8, device="cuda")
+    lib.solar_svd_factorize_rsvd(X, None, r, omega, 0, S, V, P, info, ws)
+    torch.cuda.synchronize()
+    ok = info.cpu().numpy() == 0                          # -2: a start block whose Gram matrix breaks down in float
+    v = V.cpu().numpy().astype(np.float64)[ok]
+    assert ok.sum() > B // 2
+    assert np.abs(np.matmul(v.transpose(0, 2, 1), v) - np.eye(r)).max() < 2e-5
